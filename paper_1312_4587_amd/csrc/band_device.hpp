@@ -1,0 +1,127 @@
+// Device code of the banded density scatter shared by its own kernels and the
+// compact evaluation kernels: the walk over a band's entries and their
+// fixed-point accumulation in LDS.
+#pragma once
+
+#include "fftpl_internal.hpp"
+
+namespace fftpl {
+
+// The entries of band `band` (band = nb: the tall cells) lie in one slice per
+// region: slice k holds blk_cnt[band][k] entries from index
+// k * stride + blk_off[band][k].  A block of NTB threads walks them in chunks
+// of NTB slices: the chunk's counts are scanned, and the chunk's entries are
+// taken in windows of NTB * KB.  For each window every slice writes its own
+// number into an LDS owner map at the window positions it covers (slices
+// longer than a wavefront are written by the whole wavefront), so a
+// thread finds the slice of its entry with one LDS read (a binary search over
+// the scan, ten dependent LDS reads per entry, cost the walk more than its
+// loads).  Thread t takes window entries t, t + NTB, ...: KB of them, whose
+// indices are all known before f(index) uses any, so the caller can issue
+// their loads together.  Every thread of the block must call it; `owner`
+// holds NTB * KB entries.
+template <int NTB, int KB, typename F>
+__device__ __forceinline__ void walk_band(const BandLayout& L, int band, int64_t stride,
+                                          int* pre, int64_t* start, unsigned short* owner,
+                                          F f) {
+  static_assert(NTB <= 65536, "slice numbers are u16");
+  constexpr int W = NTB * KB;
+  const int t = threadIdx.x;
+  for (int k0 = 0; k0 < L.nblk; k0 += NTB) {
+    const int k = k0 + t;
+    const int c = k < L.nblk ? L.blk_cnt[(size_t)band * L.nblk + k] : 0;
+    const int o = k < L.nblk ? L.blk_off[(size_t)band * L.nblk + k] : 0;
+    int tot;
+    const int ex = block_exclusive_scan<NTB>(c, &tot);
+    pre[t] = ex;
+    start[t] = (int64_t)k * stride + o;
+    for (int w0 = 0; w0 < tot; w0 += W) {
+      // a slice of up to 64 window entries is written by its own thread,
+      // a longer one by its whole wavefront
+      const int a = max(ex, w0), e = min(ex + c, w0 + W);
+      const bool big = e - a > kWave;
+      if (!big)
+        for (int v = a; v < e; ++v) owner[v - w0] = (unsigned short)t;
+      unsigned long long bm = __ballot(big);
+      while (bm) {
+        const int l = __ffsll((long long)bm) - 1;
+        bm &= bm - 1;
+        const int ba = __shfl(a, l), be = __shfl(e, l), bt = __shfl(t, l);
+        for (int v = ba + (t & (kWave - 1)); v < be; v += kWave) owner[v - w0] = (unsigned short)bt;
+      }
+      __syncthreads();
+      int64_t idx[KB];
+#pragma unroll
+      for (int j = 0; j < KB; ++j) {
+        const int v = w0 + j * NTB + t;
+        idx[j] = -1;
+        if (v < tot) {
+          const int sl = owner[v - w0];
+          idx[j] = start[sl] + (v - pre[sl]);
+        }
+      }
+      f(idx);
+      __syncthreads();   // owner, pre and start are rewritten next
+    }
+  }
+}
+
+// Fixed-point LDS add of an overlap v in [0, 1] (units of 2^-31; a sum of
+// up to 2^32 entries stays inside 64 bits).
+constexpr double kAccUnit = 1.0 / 2147483648.0;
+__device__ __forceinline__ void add_fixed(unsigned long long* a, float v) {
+  atomicAdd(a, (unsigned long long)__float2uint_rn(v * 2147483648.0f));
+}
+
+// The overlaps of one cell with rows r0 .. r0 + R - 1.
+__device__ __forceinline__ void add_span(const Span& sx, const Span& sy, int r0, int R, int n,
+                                         unsigned long long* acc) {
+  const int ya = max(sy.i0, r0), yb = min(sy.i1, r0 + R - 1);
+  for (int iy = ya; iy <= yb; ++iy) {
+    const float oy = span_overlap(sy, iy);
+    unsigned long long* row = acc + (iy - r0) * n;
+    for (int ix = sx.i0; ix <= sx.i1; ++ix) add_fixed(&row[ix], span_overlap(sx, ix) * oy);
+  }
+}
+
+// LDS of a band walk by NTB threads taking KB entries each.
+template <int NTB, int KB>
+struct WalkLds {
+  int64_t start[NTB];
+  int pre[NTB];
+  unsigned short owner[NTB * KB];
+};
+
+// Adds the cells of band `band` (rows r0 .. r0 + R - 1) into acc (R rows of n
+// fixed-point bins, cleared by the caller): the band's entries, then the
+// cells too tall to be listed per band, one thread per cell.
+template <int NTB, int KB>
+__device__ __forceinline__ void band_accumulate(const GridF& g, const BandLayout& L, int band,
+                                                const float* __restrict__ x,
+                                                const float* __restrict__ y,
+                                                const float* __restrict__ w,
+                                                const float* __restrict__ h,
+                                                unsigned long long* acc, WalkLds<NTB, KB>& lds) {
+  const int n = g.n, R = L.rows, r0 = band * R;
+  walk_band<NTB, KB>(L, band, L.region, lds.pre, lds.start, lds.owner,
+                     [&](const int64_t (&idx)[KB]) {
+    float4 q[KB];
+#pragma unroll
+    for (int j = 0; j < KB; ++j) q[j] = L.entries[idx[j] >= 0 ? idx[j] : 0];
+#pragma unroll
+    for (int j = 0; j < KB; ++j) {
+      if (idx[j] < 0) continue;
+      const Span sx = span_from_edges(q[j].x, q[j].y, n);
+      const Span sy = span_from_edges(q[j].z, q[j].w, n);
+      add_span(sx, sy, r0, R, n, acc);
+    }
+  });
+  walk_band<NTB, 1>(L, L.nb, L.cpk, lds.pre, lds.start, lds.owner, [&](const int64_t (&idx)[1]) {
+    if (idx[0] < 0) return;
+    const int i = L.big[idx[0]];
+    add_span(cell_span(x[i], w[i], g.xl, g.inv_bw, n), cell_span(y[i], h[i], g.yl, g.inv_bh, n),
+             r0, R, n, acc);
+  });
+}
+
+}  // namespace fftpl

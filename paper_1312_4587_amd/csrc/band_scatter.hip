@@ -1,7 +1,7 @@
 // Banded density scatter (Eq. (2), Section III-B) without float atomics in
 // global memory, which retire at roughly 20 G/s on the whole chip whatever
 // their scope:
-//   place: each block of kCellsPerBlock cells histograms the bands its cells
+//   place: each block of cpk cells histograms the bands its cells
 //          touch in LDS (plus one slot for cells too tall to list per band),
 //          scans the histogram, and writes each cell's edges (bin units)
 //          into every band it touches, in a region of its own sliced by band
@@ -22,20 +22,37 @@
 #include <algorithm>
 #include <mutex>
 
-#include "fftpl_internal.hpp"
+#include "band_device.hpp"
 
 namespace fftpl {
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
-                       size_t* bytes_out) {
+BandLayout band_shape(int n, int m) {
   BandLayout L;
   L.n = n;
-  L.rows = (n + 255) / 256;              // <= 4 rows for n <= 1024: rows*n <= 4096
-  L.nb = (n + L.rows - 1) / L.rows;      // <= 256 bands; the last may be short
+  // Two rows at least (a row pair is what one FFT block transforms), at most
+  // 4 for n <= 1024: rows * n <= 4096 bins, at most 256 bands, the last short.
+  L.rows = n <= 512 ? 2 : (n + 255) / 256;
+  L.nb = (n + L.rows - 1) / L.rows;
   L.m = m;
-  L.nblk = m > 0 ? (m + kCellsPerBlock - 1) / kCellsPerBlock : 1;
+  // Cells per counting block: the fewest (512 threads times 1, 2, 4 or 8
+  // cells) that need no more blocks than there are CUs, else 8.  A block is a
+  // chain of load, count, scan and store whose length follows its cells:
+  // k_band_place at 200k cells 11.4 us in 49 blocks of 4096 cells, 7.6 us in
+  // 196 of 1024; at 123k cells 10.6 us, 6.9 us in 242 of 512; 2.1M cells keep
+  // 4096.
+  int cb = 1;
+  while (cb < kCellBatch && (int64_t)kBandThreads * cb * kNumCus < m) cb *= 2;
+  L.cpk = kBandThreads * cb;
+  L.region = kMaxBands * L.cpk;
+  L.nblk = m > 0 ? (m + L.cpk - 1) / L.cpk : 1;
+  return L;
+}
+
+BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
+                       size_t* bytes_out) {
+  BandLayout L = band_shape(n, m);
   L.nwa = (num_nets + 255) / 256;
   // wirelength partials: 4 per 256 nets (slot path) or 2 per net block of at
   // least kXchMinTarget pins (exchange path)
@@ -49,11 +66,11 @@ BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
   off = align256(off + sizeof(float2) * (size_t)m);
   const size_t o_pg = off;
   off = align256(off + sizeof(float2) * (size_t)num_pins);
-  const size_t nreg = (size_t)L.nblk * kBandRegion;   // entries of all regions
+  const size_t nreg = (size_t)L.nblk * L.region;   // entries of all regions
   const size_t o_en = off;
   off = align256(off + sizeof(float4) * nreg);
   const size_t o_big = off;
-  off = align256(off + sizeof(int32_t) * (size_t)L.nblk * kCellsPerBlock);
+  off = align256(off + sizeof(int32_t) * (size_t)L.nblk * L.cpk);
   const size_t o_ep = off;
   off = align256(off + sizeof(int32_t) * (size_t)m);
   const size_t o_eg = off;
@@ -81,21 +98,22 @@ BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
 namespace {
 
 constexpr int NT = kBandThreads;
-constexpr int NTA = kAccThreads;
-constexpr int B = kCellBatch;
+constexpr int B = kCellBatch;   // entries a thread of a band walk takes together
 
+template <int CB>
 struct CellBatch {
-  float x[B], y[B], w[B], h[B];
+  float x[CB], y[CB], w[CB], h[CB];
 };
 
-__device__ __forceinline__ void load_batch(CellBatch& c, int base, int m,
+template <int CB>
+__device__ __forceinline__ void load_batch(CellBatch<CB>& c, int base, int m,
                                            const float* __restrict__ x,
                                            const float* __restrict__ y,
                                            const float* __restrict__ w,
                                            const float* __restrict__ h) {
   // unconditional (index clamped, m >= 1) so the whole batch is in flight
 #pragma unroll
-  for (int j = 0; j < B; ++j) {
+  for (int j = 0; j < CB; ++j) {
     const int i = min(base + j * NT + (int)threadIdx.x, m - 1);
     c.x[j] = x[i];
     c.y[j] = y[i];
@@ -106,66 +124,9 @@ __device__ __forceinline__ void load_batch(CellBatch& c, int base, int m,
 
 }  // namespace
 
-// The entries of band `band` (band = nb: the tall cells) lie in one slice per
-// region: slice k holds blk_cnt[band][k] entries from index
-// k * stride + blk_off[band][k].  A block of NTB threads walks them in chunks
-// of NTB slices: the chunk's counts are scanned, and the chunk's entries are
-// taken in windows of NTB * KB.  For each window every slice writes its own
-// number into an LDS owner map at the window positions it covers (slices
-// longer than a wavefront are written by the whole wavefront), so a
-// thread finds the slice of its entry with one LDS read (a binary search over
-// the scan, ten dependent LDS reads per entry, cost the walk more than its
-// loads).  Thread t takes window entries t, t + NTB, ...: KB of them, whose
-// indices are all known before f(index) uses any, so the caller can issue
-// their loads together.  Every thread of the block must call it; `owner`
-// holds NTB * KB entries.
-template <int NTB, int KB, typename F>
-__device__ __forceinline__ void walk_band(const BandLayout& L, int band, int64_t stride,
-                                          int* pre, int64_t* start, unsigned short* owner,
-                                          F f) {
-  static_assert(NTB <= 65536, "slice numbers are u16");
-  constexpr int W = NTB * KB;
-  const int t = threadIdx.x;
-  for (int k0 = 0; k0 < L.nblk; k0 += NTB) {
-    const int k = k0 + t;
-    const int c = k < L.nblk ? L.blk_cnt[(size_t)band * L.nblk + k] : 0;
-    const int o = k < L.nblk ? L.blk_off[(size_t)band * L.nblk + k] : 0;
-    int tot;
-    const int ex = block_exclusive_scan<NTB>(c, &tot);
-    pre[t] = ex;
-    start[t] = (int64_t)k * stride + o;
-    for (int w0 = 0; w0 < tot; w0 += W) {
-      // a slice of up to 64 window entries is written by its own thread,
-      // a longer one by its whole wavefront
-      const int a = max(ex, w0), e = min(ex + c, w0 + W);
-      const bool big = e - a > kWave;
-      if (!big)
-        for (int v = a; v < e; ++v) owner[v - w0] = (unsigned short)t;
-      unsigned long long bm = __ballot(big);
-      while (bm) {
-        const int l = __ffsll((long long)bm) - 1;
-        bm &= bm - 1;
-        const int ba = __shfl(a, l), be = __shfl(e, l), bt = __shfl(t, l);
-        for (int v = ba + (t & (kWave - 1)); v < be; v += kWave) owner[v - w0] = (unsigned short)bt;
-      }
-      __syncthreads();
-      int64_t idx[KB];
-#pragma unroll
-      for (int j = 0; j < KB; ++j) {
-        const int v = w0 + j * NTB + t;
-        idx[j] = -1;
-        if (v < tot) {
-          const int sl = owner[v - w0];
-          idx[j] = start[sl] + (v - pre[sl]);
-        }
-      }
-      f(idx);
-      __syncthreads();   // owner, pre and start are rewritten next
-    }
-  }
-}
-
-template <int NB>
+// CB: the most cells per thread among the batch's designs (a design with fewer
+// per block leaves the rest of its threads' slots empty).
+template <int NB, int CB>
 __global__ void __launch_bounds__(kBandThreads) k_band_place(BandBatch<NB> bb) {
   // design blockIdx.y of the batch; blocks past its count of cell blocks idle
   const BandReq& q = bb.r[blockIdx.y];
@@ -180,17 +141,17 @@ __global__ void __launch_bounds__(kBandThreads) k_band_place(BandBatch<NB> bb) {
   __shared__ int hist[257], cur[257];   // the bands, then the tall cells
   for (int b = t; b <= L.nb; b += NT) hist[b] = 0;
   __syncthreads();
-  const int c0 = k * kCellsPerBlock;   // one batch of B cells per thread
-  CellBatch c;
+  const int c0 = k * L.cpk, c1 = min(L.m, c0 + L.cpk);   // one batch of cells per thread
+  CellBatch<CB> c;
   load_batch(c, c0, L.m, x, y, w, h);
-  float4 e[B];
-  int b0[B], nbd[B];   // first band, bands listed (0: none, -1: tall)
+  float4 e[CB];
+  int b0[CB], nbd[CB];   // first band, bands listed (0: none, -1: tall)
 #pragma unroll
-  for (int j = 0; j < B; ++j) {
+  for (int j = 0; j < CB; ++j) {
     const int i = c0 + j * NT + t;
     nbd[j] = 0;
     b0[j] = 0;
-    if (i >= L.m) continue;
+    if (i >= c1) continue;
     const Span sx = cell_span(c.x[j], c.w[j], g.xl, g.inv_bw, g.n);
     const Span sy = cell_span(c.y[j], c.h[j], g.yl, g.inv_bh, g.n);
     if (sx.i0 > sx.i1 || sy.i0 > sy.i1) continue;
@@ -215,11 +176,11 @@ __global__ void __launch_bounds__(kBandThreads) k_band_place(BandBatch<NB> bb) {
     cur[t] = off;
   }
   __syncthreads();
-  const int64_t rbase = (int64_t)k * kBandRegion;
+  const int64_t rbase = (int64_t)k * L.region;
 #pragma unroll
-  for (int j = 0; j < B; ++j) {
+  for (int j = 0; j < CB; ++j) {
     const int i = c0 + j * NT + t;
-    if (i >= L.m) continue;
+    if (i >= c1) continue;
     int first = -1;   // the cell's entry in its first band, if listed
     if (nbd[j] > 0) {
       for (int b = b0[j]; b < b0[j] + nbd[j]; ++b) {
@@ -228,73 +189,37 @@ __global__ void __launch_bounds__(kBandThreads) k_band_place(BandBatch<NB> bb) {
         if (b == b0[j]) first = (int)(rbase + q);
       }
     } else if (nbd[j] < 0) {
-      L.big[(int64_t)k * kCellsPerBlock + atomicAdd(&cur[L.nb], 1)] = i;
+      L.big[(int64_t)k * L.cpk + atomicAdd(&cur[L.nb], 1)] = i;
     }
     L.epos[i] = first;
   }
 }
 
-// Fixed-point LDS add of an overlap v in [0, 1] (units of 2^-31; a sum of
-// up to 2^32 entries stays inside 64 bits).
-constexpr double kAccUnit = 1.0 / 2147483648.0;
-__device__ __forceinline__ void add_fixed(unsigned long long* a, float v) {
-  atomicAdd(a, (unsigned long long)__float2uint_rn(v * 2147483648.0f));
-}
-
-template <int NB>
-__global__ void __launch_bounds__(kAccThreads) k_band_accum(BandBatch<NB> bb) {
+// NTA threads taking KB entries each, at most BINS bins per band: (1024, 8,
+// 4096), or (512, 4, 1024) for n <= 512 and up to 1024 cells per band on
+// average.  Such a band holds a few hundred entries, less than the larger
+// block's fixed work (owner map, scan over the threads, clears), and the smaller
+// block leaves room for four per CU: a batch of eight designs at n = 256 takes
+// 12.4 us instead of 51.5 us, one design at n = 512 about as long as before
+// (200k cells 7.8 -> 8.2 us, 123k 7.9 -> 7.6 us).
+template <int NB, int NTA, int KB, int BINS>
+__global__ void __launch_bounds__(NTA) k_band_accum(BandBatch<NB> bb) {
   const BandReq& q = bb.r[blockIdx.y];
   const GridF g = q.g;
   const BandLayout L = q.L;
-  const float* __restrict__ x = q.x;
-  const float* __restrict__ y = q.y;
-  const float* __restrict__ w = q.w;
-  const float* __restrict__ h = q.h;
   const float* __restrict__ base = q.base;
   float* __restrict__ rho = q.rho;
-  __shared__ unsigned long long acc[kBandMaxN * 4];   // rows * n <= 4096 bins
-  __shared__ int pre[NTA];
-  __shared__ int64_t start[NTA];
-  __shared__ unsigned short owner[NTA * B];
+  __shared__ unsigned long long acc[BINS];
+  __shared__ WalkLds<NTA, KB> lds;
   const int t = threadIdx.x;
   const int n = g.n, R = L.rows, band = blockIdx.x, r0 = band * R;
   const int cells = min(R, n - r0) * n;
   for (int k = t; k < cells; k += NTA) acc[k] = 0ull;
   __syncthreads();
-  walk_band<NTA, B>(L, band, kBandRegion, pre, start, owner, [&](const int64_t (&idx)[B]) {
-    float4 q[B];
-#pragma unroll
-    for (int j = 0; j < B; ++j) q[j] = L.entries[idx[j] >= 0 ? idx[j] : 0];
-#pragma unroll
-    for (int j = 0; j < B; ++j) {
-      if (idx[j] < 0) continue;
-      const Span sx = span_from_edges(q[j].x, q[j].y, n);
-      const Span sy = span_from_edges(q[j].z, q[j].w, n);
-      const int ya = max(sy.i0, r0), yb = min(sy.i1, r0 + R - 1);
-      for (int iy = ya; iy <= yb; ++iy) {
-        const float oy = span_overlap(sy, iy);
-        unsigned long long* row = acc + (iy - r0) * n;
-        for (int ix = sx.i0; ix <= sx.i1; ++ix) add_fixed(&row[ix], span_overlap(sx, ix) * oy);
-      }
-    }
-  });
-  // cells too tall to be listed per band: every band block adds its rows of
-  // them, one thread per cell
-  walk_band<NTA, 1>(L, L.nb, kCellsPerBlock, pre, start, owner, [&](const int64_t (&idx)[1]) {
-    if (idx[0] < 0) return;
-    const int i = L.big[idx[0]];
-    const Span sx = cell_span(x[i], w[i], g.xl, g.inv_bw, n);
-    const Span sy = cell_span(y[i], h[i], g.yl, g.inv_bh, n);
-    const int ya = max(sy.i0, r0), yb = min(sy.i1, r0 + R - 1);
-    for (int iy = ya; iy <= yb; ++iy) {
-      const float oy = span_overlap(sy, iy);
-      for (int ix = sx.i0; ix <= sx.i1; ++ix)
-        add_fixed(&acc[(iy - r0) * n + ix], span_overlap(sx, ix) * oy);
-    }
-  });
+  band_accumulate<NTA, KB>(g, L, band, q.x, q.y, q.w, q.h, acc, lds);
   __syncthreads();
   // rho = base + rows: all of a thread's base loads issued before any store
-  constexpr int PA = kBandMaxN * 4 / NTA;
+  constexpr int PA = BINS / NTA;
   const size_t o = (size_t)r0 * n;
   float bv[PA];
 #pragma unroll
@@ -340,7 +265,7 @@ __global__ void __launch_bounds__(NTG) k_band_gather(BandBatch<NB> bb) {
       if (t + j * NTG < cnt) rows[t + j * NTG] = v[j];
   }
   // (the walk's first scan synchronises the block after the staging)
-  walk_band<NTG, B>(L, band, kBandRegion, pre, start, owner, [&](const int64_t (&idx)[B]) {
+  walk_band<NTG, B>(L, band, L.region, pre, start, owner, [&](const int64_t (&idx)[B]) {
     float4 q[B];
 #pragma unroll
     for (int j = 0; j < B; ++j) q[j] = L.entries[idx[j] >= 0 ? idx[j] : 0];
@@ -427,15 +352,32 @@ hipError_t launch_interleave(int m, const float* x, const float* y, float2* xy,
 }
 
 template <int NB>
-static hipError_t band_scatter_nb(const BandBatch<NB>& bb, int max_nblk, int nb,
-                                  bool any_cells, hipStream_t s, Plan* tp) {
+static hipError_t band_place_nb(const BandBatch<NB>& bb, int max_nblk, int cpk, hipStream_t s) {
+  const dim3 grid(max_nblk, bb.count), block(NT);
+  if (cpk <= NT)
+    hipLaunchKernelGGL((k_band_place<NB, 1>), grid, block, 0, s, bb);
+  else if (cpk <= 2 * NT)
+    hipLaunchKernelGGL((k_band_place<NB, 2>), grid, block, 0, s, bb);
+  else if (cpk <= 4 * NT)
+    hipLaunchKernelGGL((k_band_place<NB, 4>), grid, block, 0, s, bb);
+  else
+    hipLaunchKernelGGL((k_band_place<NB, kCellBatch>), grid, block, 0, s, bb);
+  return hipGetLastError();
+}
+
+template <int NB>
+static hipError_t band_scatter_nb(const BandBatch<NB>& bb, int max_nblk, int max_cpk, int max_m,
+                                  hipStream_t s, Plan* tp) {
   hipError_t e = hipSuccess;
-  if (any_cells) {
-    hipLaunchKernelGGL((k_band_place<NB>), dim3(max_nblk, bb.count), dim3(NT), 0, s, bb);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (max_m > 0) {
+    if ((e = band_place_nb<NB>(bb, max_nblk, max_cpk, s)) != hipSuccess) return e;
     if (tp) plan_mark(*tp, "k_band_place", s);
   }
-  hipLaunchKernelGGL((k_band_accum<NB>), dim3(nb, bb.count), dim3(NTA), 0, s, bb);
+  const int n = bb.r[0].L.n, nb = bb.r[0].L.nb;
+  if (n <= 512 && max_m <= 1024 * (int64_t)nb)
+    hipLaunchKernelGGL((k_band_accum<NB, 512, 4, 1024>), dim3(nb, bb.count), dim3(512), 0, s, bb);
+  else
+    hipLaunchKernelGGL((k_band_accum<NB, 1024, B, 4096>), dim3(nb, bb.count), dim3(1024), 0, s, bb);
   e = hipGetLastError();
   if (tp) plan_mark(*tp, "k_band_accum", s);
   return e;
@@ -445,11 +387,11 @@ hipError_t launch_band_scatter_batch(const BandReq* reqs, int count, hipStream_t
                                      Plan* tp) {
   if (count <= 0) return hipSuccess;
   if (count > kMaxBatch) return hipErrorInvalidValue;
-  int max_nblk = 1;
-  bool any = false;
+  int max_nblk = 1, max_cpk = 0, max_m = 0;
   for (int i = 0; i < count; ++i) {
     if (reqs[i].L.m > 0) {
-      any = true;
+      max_m = std::max(max_m, reqs[i].L.m);
+      max_cpk = std::max(max_cpk, reqs[i].L.cpk);
       max_nblk = std::max(max_nblk, reqs[i].L.nblk);
     } else {
       // no cells: one empty region
@@ -458,17 +400,16 @@ hipError_t launch_band_scatter_batch(const BandReq* reqs, int count, hipStream_t
       if (e != hipSuccess) return e;
     }
   }
-  const int nb = reqs[0].L.nb;
   if (count == 1) {
     BandBatch<1> bb;
     bb.count = 1;
     bb.r[0] = reqs[0];
-    return band_scatter_nb(bb, max_nblk, nb, any, s, tp);
+    return band_scatter_nb(bb, max_nblk, max_cpk, max_m, s, tp);
   }
   BandBatch<kMaxBatch> bb;
   bb.count = count;
   for (int i = 0; i < count; ++i) bb.r[i] = reqs[i];
-  return band_scatter_nb(bb, max_nblk, nb, any, s, tp);
+  return band_scatter_nb(bb, max_nblk, max_cpk, max_m, s, tp);
 }
 
 // ---- the density map without allocation -----------------------------------
@@ -485,17 +426,12 @@ void* g_scratch_ptr[kMaxDevicesNoalloc] = {};
 
 // Band lists of the density scatter alone (no wirelength or gather arrays).
 BandLayout band_layout_density(int n, int m, void* work, size_t* bytes_out) {
-  BandLayout L;
-  L.n = n;
-  L.rows = (n + 255) / 256;
-  L.nb = (n + L.rows - 1) / L.rows;
-  L.m = m;
-  L.nblk = m > 0 ? (m + kCellsPerBlock - 1) / kCellsPerBlock : 1;
+  BandLayout L = band_shape(n, m);
   size_t off = 0;
   const size_t o_en = off;
-  off = align256(off + sizeof(float4) * (size_t)L.nblk * kBandRegion);
+  off = align256(off + sizeof(float4) * (size_t)L.nblk * L.region);
   const size_t o_big = off;
-  off = align256(off + sizeof(int32_t) * (size_t)L.nblk * kCellsPerBlock);
+  off = align256(off + sizeof(int32_t) * (size_t)L.nblk * L.cpk);
   const size_t o_ep = off;
   off = align256(off + sizeof(int32_t) * (size_t)m);
   const size_t o_bo = off;

@@ -554,23 +554,21 @@ inline int wa_big_grid(int num_nets) {
 constexpr int kMaxBands = 4;
 constexpr int kBandMaxN = 1024;
 constexpr int kBandThreads = 512;      // threads of a counting / placing block
-constexpr int kCellBatch = 8;          // cells whose loads a thread issues together
-constexpr int kCellsPerBlock = kBandThreads * kCellBatch;   // 4096
-constexpr int kBandRegion = kMaxBands * kCellsPerBlock;      // entries per block
-constexpr int kAccThreads = 1024;      // threads of a band accumulation block
+constexpr int kCellBatch = 8;          // most cells whose loads a thread issues together
 
 struct BandLayout {
   int n = 0, rows = 0, nb = 0;   // band height in rows, number of bands
   int m = 0, nblk = 0;           // cells, counting blocks
+  int cpk = 0, region = 0;       // cells per counting block, entries of its region
   // regions of the problem workspace
   float2* xy = nullptr;          // [m] interleaved positions
   float2* pin_grad = nullptr;    // [P] per-pin WA gradients, cell-major slots
-  float4* entries = nullptr;     // [nblk*kBandRegion] band entries (cell edges in bins),
+  float4* entries = nullptr;     // [nblk*region] band entries (cell edges in bins),
                                  // one region per counting block, sliced by band
   int32_t* epos = nullptr;       // [m] each cell's entry in its first band, -1 if none
-  float2* egrad = nullptr;       // [nblk*kBandRegion] density gradient of the cell whose
+  float2* egrad = nullptr;       // [nblk*region] density gradient of the cell whose
                                  // first-band entry this is (band gather)
-  int32_t* big = nullptr;        // [nblk*kCellsPerBlock] per block, its cells spanning
+  int32_t* big = nullptr;        // [nblk*cpk] per block, its cells spanning
                                  // more than kMaxBands bands
   int32_t* blk_off = nullptr;    // [nb + 1][nblk] per band: each block's slice offset
   int32_t* blk_cnt = nullptr;    // [nb + 1][nblk] per band: each block's slice size
@@ -579,6 +577,8 @@ struct BandLayout {
 };
 BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
                        size_t* bytes_out);
+// Bands and counting blocks of a design (the pointers stay null).
+BandLayout band_shape(int n, int m);
 
 // ---- batches: several designs of one grid side in one launch per stage ----
 // Kernels take a batch of per-design descriptors by value (the kernel
