@@ -833,7 +833,8 @@ int run_other(Plan& p, const EvalReq& r, int grad_mode, hipStream_t s) {
   if (e == hipSuccess)
     e = launch_eval_finalize(a.en_part, p.n_en, a.tau_part, p.n_tau, slots ? L.wa_part : nullptr,
                              slots ? (prob->num_nets + 255) / 256 : 0,
-                             slots ? wa_big_grid(prob->num_nets) : 0, &r.out4[0], &r.out4[1],
+                             slots && prob->num_nets > 0 ? wa_big_grid(prob->num_nets) : 0,
+                             &r.out4[0], &r.out4[1],
                              &r.out4[2], &r.out4[3], s);
   plan_mark(p, "k_eval_finalize", s);
   return dev_status(e);
