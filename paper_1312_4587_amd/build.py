@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 ROCTX = os.environ.get("FFTPL_ROCTX") == "1"
 LIB = os.path.join(HERE, "libfftpl_roctx.so" if ROCTX else "libfftpl.so")
 OBJDIR = os.path.join(HERE, "_build_roctx" if ROCTX else "_build")
-SOURCES = ["abi.hip", "band_scatter.hip", "density.hip", "driver.hip", "exchange.hip", "spectral_fft.hip", "spectral_gemm.hip",
+SOURCES = ["abi.hip", "band_scatter.hip", "compact.hip", "density.hip", "driver.hip", "exchange.hip", "spectral_fft.hip", "spectral_gemm.hip",
            "wirelength.hip"]
 ARCH = os.environ.get("FFTPL_OFFLOAD_ARCH", "gfx950")
 FLAGS = [

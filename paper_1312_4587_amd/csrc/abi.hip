@@ -574,6 +574,7 @@ struct EvalReq {
   BandLayout L;
   XchDims xd;
   XchIndex X;
+  bool compact = false;   // the exchange path in its compact form (compact.hip)
 };
 
 // Host-side checks of one evaluation (nothing is enqueued); fills r.
@@ -621,6 +622,7 @@ int check_eval(const Plan& p, const fftpl_problem* prob, const float* x, const f
   if (path == FFTPL_PATH_EXCHANGE) {
     r->xd = xd;
     r->X = xch_index(xd, prob->xindex);
+    r->compact = compact_design(p.n, xd);
   }
   return FFTPL_OK;
 }
@@ -644,6 +646,124 @@ SpectralArgs spectral_args(Plan& p, const EvalReq& r, int slot, int grad_mode, b
   return a;
 }
 
+// The per-cell sums (and scalars) of a request in batch slot `slot`.
+SumReq cell_request(Plan& p, const EvalReq& r, const SpectralArgs& sa, int slot) {
+  const size_t nn = (size_t)p.n * p.n;
+  FinalArgs fin;
+  fin.en = sa.en_part;
+  fin.n_en = p.n_en;
+  fin.tau = sa.tau_part;
+  fin.n_tau = p.n_tau;
+  fin.wa = r.L.wa_part;
+  fin.n_s = r.xd.nnb;
+  fin.n_b = 0;
+  fin.o_en = &r.out4[0];
+  fin.o_wa = &r.out4[1];
+  fin.o_hp = &r.out4[2];
+  fin.o_tau = &r.out4[3];
+  CellGradArgs ca;
+  ca.g = r.g;
+  ca.x = r.x;
+  ca.y = r.y;
+  ca.w = r.prob->w;
+  ca.h = r.prob->h;
+  ca.exy = reinterpret_cast<const float2*>(p.exy + 2 * slot * nn);
+  ca.psi = p.psi + slot * nn;
+  ca.epos = r.L.epos;
+  ca.egrad = r.L.egrad;
+  ca.scale = r.lambda;
+  if (r.params) ca.dscale = r.params;
+  ca.gx = r.gx;
+  ca.gy = r.gy;
+  ca.fin = fin;
+  ca.fin_block = r.xd.ncb - 1;
+  return sum_req(r.xd, r.X, r.L.pin_grad, ca);
+}
+
+// The compact form of the exchange path for count requests (all compact; see
+// compact.hip): the same results in five launches on `s` alone.
+int run_compact_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream_t s) {
+  const bool grads = rs[0].gx != nullptr;
+  const size_t nn = (size_t)p.n * p.n;
+  const bool fuse = compact_fuses_rows(p);
+  p.nev = 0;
+  plan_mark(p, "start", s);
+  BandReq br[kMaxBatch];
+  CompactReq cr[kMaxBatch];
+  SpectralArgs sa[kMaxBatch];
+  bool place = false;
+  for (int i = 0; i < count; ++i) {
+    const EvalReq& r = rs[i];
+    const bool scan = r.xd.m <= kCompactScanCells;
+    br[i].g = r.g;
+    br[i].L = r.L;
+    br[i].L.epos = nullptr;   // the gradient is gathered per cell
+    if (scan)
+      br[i].L.m = 0;
+    else
+      place = true;
+    br[i].x = r.x;
+    br[i].y = r.y;
+    br[i].w = r.prob->w;
+    br[i].h = r.prob->h;
+    sa[i] = spectral_args(p, r, i, grad_mode, grads);
+    const SpecReq sq = spec_req(p, sa[i], i);
+    CompactReq& q = cr[i];
+    q.g = r.g;
+    q.m = r.xd.m;
+    q.nblk = scan ? 0 : r.L.nblk;
+    q.rows = r.L.rows;
+    q.nb = r.L.nb;
+    q.cpk = r.L.cpk;
+    q.region = r.L.region;
+    q.entries = r.L.entries;
+    q.big = r.L.big;
+    q.blk_off = r.L.blk_off;
+    q.blk_cnt = r.L.blk_cnt;
+    q.w = r.prob->w;
+    q.h = r.prob->h;
+    q.base = r.prob->base;
+    q.cap = r.prob->cap;
+    q.rho = p.rho + i * nn;
+    q.bT = sq.bT;
+    q.rowsum = sq.rowsum;
+    q.tau_part = sq.tau_part;
+    q.x = xch_req(r.xd, r.X, r.x, r.y, r.L.pin_grad, r.prob->net_ptr, r.prob->pin_cell,
+                  r.prob->pin_dx, r.prob->pin_dy, r.gamma, r.L.wa_part);
+    if (r.params) q.x.dgamma = r.params + 1;
+    if (!scan) q.x.xy = r.L.xy;   // the place pass interleaves the positions
+  }
+  hipError_t e = hipSuccess;
+  if (place) {
+    e = launch_band_place_batch(br, count, s);
+    plan_mark(p, "k_band_place", s);
+  }
+  if (e == hipSuccess) e = launch_compact_mid(p, cr, count, rs[0].prob->wl_model, fuse, s);
+  plan_mark(p, "k_compact_mid", s);
+  if (e == hipSuccess) {
+    if (p.mode == FFTPL_DCT_FFT) {
+      e = spectral_fft_batch(p, sa, count, s, !fuse);
+    } else {
+      for (int i = 0; i < count && e == hipSuccess; ++i) e = spectral_gemm(p, sa[i], s);
+    }
+  }
+  SumReq sr[kMaxBatch];
+  for (int i = 0; i < count; ++i) sr[i] = cell_request(p, rs[i], sa[i], i);
+  if (grads) {
+    if (e == hipSuccess) e = launch_compact_cells(sr, count, grad_mode, s);
+    plan_mark(p, "k_compact_cells", s);
+  } else {
+    for (int i = 0; i < count; ++i) {
+      const FinalArgs& f = sr[i].a.fin;
+      if (e == hipSuccess)
+        e = launch_eval_finalize(f.en, f.n_en, f.tau, f.n_tau, f.wa, f.n_s, f.n_b, f.o_en,
+                                 f.o_wa, f.o_hp, f.o_tau, s);
+      plan_mark(p, "k_eval_finalize", s);
+    }
+  }
+  return dev_status(e);
+}
+
 // The exchange path for count requests (count <= the plan's max_batch, one
 // wirelength model, workspaces that do not overlap): every stage is one
 // launch over all of them, request i in batch slot i of the plan.  The
@@ -655,6 +775,7 @@ SpectralArgs spectral_args(Plan& p, const EvalReq& r, int slot, int grad_mode, b
 // density branch reaches it.  With per-kernel timing on, everything runs on
 // `s` so that consecutive events bracket single kernels.
 int run_exchange_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream_t s) {
+  if (rs[0].compact) return run_compact_group(p, rs, count, grad_mode, s);
   const bool grads = rs[0].gx != nullptr;
   const size_t nn = (size_t)p.n * p.n;
   const bool overlap = !p.timing;
@@ -673,6 +794,7 @@ int run_exchange_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream
     const EvalReq& r = rs[i];
     br[i].g = r.g;
     br[i].L = r.L;
+    br[i].L.xy = nullptr;   // (the spread reads x and y)
     br[i].x = r.x;
     br[i].y = r.y;
     br[i].w = r.prob->w;
@@ -681,8 +803,8 @@ int run_exchange_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream
     br[i].rho = p.rho + i * nn;
     br[i].exy = reinterpret_cast<const float2*>(p.exy + 2 * i * nn);
     br[i].psi = p.psi + i * nn;
-    xr[i] = xch_req(r.xd, r.X, r.x, r.y, r.L.pin_grad, r.prob->net_ptr, r.prob->pin_dx,
-                    r.prob->pin_dy, r.gamma, r.L.wa_part);
+    xr[i] = xch_req(r.xd, r.X, r.x, r.y, r.L.pin_grad, r.prob->net_ptr, r.prob->pin_cell,
+                    r.prob->pin_dx, r.prob->pin_dy, r.gamma, r.L.wa_part);
     if (r.params) xr[i].dgamma = r.params + 1;
     sa[i] = spectral_args(p, r, i, grad_mode, grads);
   }
@@ -720,38 +842,9 @@ int run_exchange_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream
   SumReq sr[kMaxBatch];
   bool fin_separate[kMaxBatch];
   for (int i = 0; i < count; ++i) {
-    const EvalReq& r = rs[i];
-    FinalArgs fin;
-    fin.en = sa[i].en_part;
-    fin.n_en = p.n_en;
-    fin.tau = sa[i].tau_part;
-    fin.n_tau = p.n_tau;
-    fin.wa = r.L.wa_part;
-    fin.n_s = r.xd.nnb;
-    fin.n_b = 0;
-    fin.o_en = &r.out4[0];
-    fin.o_wa = &r.out4[1];
-    fin.o_hp = &r.out4[2];
-    fin.o_tau = &r.out4[3];
-    CellGradArgs ca;
-    ca.g = r.g;
-    ca.x = r.x;
-    ca.y = r.y;
-    ca.w = r.prob->w;
-    ca.h = r.prob->h;
-    ca.exy = reinterpret_cast<const float2*>(p.exy + 2 * i * nn);
-    ca.psi = p.psi + i * nn;
-    ca.epos = r.L.epos;
-    ca.egrad = r.L.egrad;
-    ca.scale = r.lambda;
-    if (r.params) ca.dscale = r.params;
-    ca.gx = r.gx;
-    ca.gy = r.gy;
-    ca.fin = fin;
-    ca.fin_block = r.xd.ncb - 1;
-    sr[i] = sum_req(r.xd, r.X, r.L.pin_grad, ca);
+    sr[i] = cell_request(p, rs[i], sa[i], i);
     // designs without cells (or the scalars alone) reduce in a separate launch
-    fin_separate[i] = !grads || r.xd.ncb <= 0 || r.xd.m <= 0;
+    fin_separate[i] = !grads || rs[i].xd.ncb <= 0 || rs[i].xd.m <= 0;
   }
   if (grads) {
     if (e == hipSuccess) e = launch_xch_cellsum_batch(sr, count, grad_mode, true, s);
@@ -850,6 +943,7 @@ bool joins_group(const EvalReq* g, int count, const EvalReq& r, int max_batch) {
   if (count >= max_batch || r.path != FFTPL_PATH_EXCHANGE) return false;
   if (count == 0) return true;
   const bool big = g[0].xd.cap > kXchPinLds2;
+  if (r.compact != g[0].compact) return false;
   if (r.prob->wl_model != g[0].prob->wl_model || (r.xd.cap > kXchPinLds2) != big) return false;
   for (int i = 0; i < count; ++i)
     if (ranges_overlap(g[i].prob->work, g[i].prob->work_bytes, r.prob->work,
@@ -987,12 +1081,14 @@ static int problem_wl(const fftpl_problem* prob, const float* x, const float* y,
   const BandLayout L =
       band_layout(prob->grid.n, m, prob->num_nets, prob->num_pins, prob->work, nullptr);
   const XchIndex X = xch_index(xd, prob->xindex);
-  XchReq xr = xch_req(xd, X, x, y, L.pin_grad, prob->net_ptr, prob->pin_dx, prob->pin_dy,
-                      gamma, L.wa_part);
+  XchReq xr = xch_req(xd, X, x, y, L.pin_grad, prob->net_ptr, prob->pin_cell, prob->pin_dx,
+                      prob->pin_dy, gamma, L.wa_part);
   xr.net_wl = net_wl;
   xr.net_hp = net_hp;
-  hipError_t e = launch_xch_spread_batch(&xr, 1, s);
-  if (e == hipSuccess) e = launch_xch_wa_batch(&xr, 1, prob->wl_model, s);
+  // positions straight from x, y where the compact evaluation reads them so
+  const bool direct = m > 0 && compact_design(1, xd);
+  hipError_t e = direct ? hipSuccess : launch_xch_spread_batch(&xr, 1, s);
+  if (e == hipSuccess) e = launch_xch_wa_batch(&xr, 1, prob->wl_model, s, direct);
   if (net_wl) return dev_status(e);
   FinalArgs fin;
   fin.wa = L.wa_part;

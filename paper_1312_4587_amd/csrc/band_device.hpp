@@ -19,9 +19,9 @@ namespace fftpl {
 // loads).  Thread t takes window entries t, t + NTB, ...: KB of them, whose
 // indices are all known before f(index) uses any, so the caller can issue
 // their loads together.  Every thread of the block must call it; `owner`
-// holds NTB * KB entries.
-template <int NTB, int KB, typename F>
-__device__ __forceinline__ void walk_band(const BandLayout& L, int band, int64_t stride,
+// holds NTB * KB entries.  LT: BandLayout, or a request with its fields.
+template <int NTB, int KB, typename LT, typename F>
+__device__ __forceinline__ void walk_band(const LT& L, int band, int64_t stride,
                                           int* pre, int64_t* start, unsigned short* owner,
                                           F f) {
   static_assert(NTB <= 65536, "slice numbers are u16");
@@ -84,6 +84,44 @@ __device__ __forceinline__ void add_span(const Span& sx, const Span& sy, int r0,
   }
 }
 
+// Adds the entries of band `band` as long as every slice is short (at most
+// kSliceMax entries per lane): each slice is taken by the same few lanes, which
+// need its count and offset and nothing from the other slices, where walk_band
+// scans the counts and fills the owner map first.  Returns false, having
+// added nothing, when a slice is longer (cells crowded into few bands) or there
+// are more slices than threads.  Every thread of the block must call it.
+constexpr int kSliceMax = 8;
+template <int NTB, typename LT>
+__device__ __forceinline__ bool add_short_slices(const LT& L, int band, int r0, int n,
+                                                 unsigned long long* acc) {
+  if (L.nblk > NTB) return false;
+  const int lanes = NTB / L.nblk;   // >= 1, per slice
+  const int k = (int)threadIdx.x / lanes, l = (int)threadIdx.x - k * lanes;
+  int c = 0, o = 0;
+  if (k < L.nblk) {
+    c = L.blk_cnt[(size_t)band * L.nblk + k];
+    o = L.blk_off[(size_t)band * L.nblk + k];
+  }
+  if (__syncthreads_or(c > kSliceMax * lanes)) return false;
+  const float4* e = L.entries + (int64_t)k * L.region + o;
+#pragma unroll
+  for (int j0 = 0; j0 < kSliceMax; j0 += 4) {
+    if (!__any(l + j0 * lanes < c)) break;
+    float4 q[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int v = l + (j0 + j) * lanes;
+      if (v < c) q[j] = e[v];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (l + (j0 + j) * lanes < c)
+        add_span(span_from_edges(q[j].x, q[j].y, n), span_from_edges(q[j].z, q[j].w, n), r0,
+                 L.rows, n, acc);
+  }
+  return true;
+}
+
 // LDS of a band walk by NTB threads taking KB entries each.
 template <int NTB, int KB>
 struct WalkLds {
@@ -95,16 +133,18 @@ struct WalkLds {
 // Adds the cells of band `band` (rows r0 .. r0 + R - 1) into acc (R rows of n
 // fixed-point bins, cleared by the caller): the band's entries, then the
 // cells too tall to be listed per band, one thread per cell.
-template <int NTB, int KB>
-__device__ __forceinline__ void band_accumulate(const GridF& g, const BandLayout& L, int band,
+// SHORT: try the short slices' form first.
+template <int NTB, int KB, bool SHORT, typename LT>
+__device__ __forceinline__ void band_accumulate(const GridF& g, const LT& L, int band,
                                                 const float* __restrict__ x,
                                                 const float* __restrict__ y,
                                                 const float* __restrict__ w,
                                                 const float* __restrict__ h,
                                                 unsigned long long* acc, WalkLds<NTB, KB>& lds) {
   const int n = g.n, R = L.rows, r0 = band * R;
-  walk_band<NTB, KB>(L, band, L.region, lds.pre, lds.start, lds.owner,
-                     [&](const int64_t (&idx)[KB]) {
+  if (!SHORT || !add_short_slices<NTB>(L, band, r0, n, acc))
+    walk_band<NTB, KB>(L, band, L.region, lds.pre, lds.start, lds.owner,
+                       [&](const int64_t (&idx)[KB]) {
     float4 q[KB];
 #pragma unroll
     for (int j = 0; j < KB; ++j) q[j] = L.entries[idx[j] >= 0 ? idx[j] : 0];

@@ -55,9 +55,9 @@ BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
   BandLayout L = band_shape(n, m);
   L.nwa = (num_nets + 255) / 256;
   // wirelength partials: 4 per 256 nets (slot path) or 2 per net block of at
-  // least kXchMinTarget pins (exchange path)
+  // least kXchSmallTarget pins (exchange path)
   size_t nwp = 4 * (size_t)L.nwa;
-  const size_t nxp = 2 * ((size_t)(num_pins + kXchMinTarget - 1) / kXchMinTarget + 1);
+  const size_t nxp = 2 * (((size_t)num_pins + kXchSmallTarget - 1) / kXchSmallTarget + 1);
   if (nwp < nxp) nwp = nxp;
   size_t off = 0;
   const size_t o_wp = off;
@@ -152,6 +152,7 @@ __global__ void __launch_bounds__(kBandThreads) k_band_place(BandBatch<NB> bb) {
     nbd[j] = 0;
     b0[j] = 0;
     if (i >= c1) continue;
+    if (L.xy) L.xy[i] = make_float2(c.x[j], c.y[j]);
     const Span sx = cell_span(c.x[j], c.w[j], g.xl, g.inv_bw, g.n);
     const Span sy = cell_span(c.y[j], c.h[j], g.yl, g.inv_bh, g.n);
     if (sx.i0 > sx.i1 || sy.i0 > sy.i1) continue;
@@ -191,7 +192,7 @@ __global__ void __launch_bounds__(kBandThreads) k_band_place(BandBatch<NB> bb) {
     } else if (nbd[j] < 0) {
       L.big[(int64_t)k * L.cpk + atomicAdd(&cur[L.nb], 1)] = i;
     }
-    L.epos[i] = first;
+    if (L.epos) L.epos[i] = first;
   }
 }
 
@@ -216,7 +217,7 @@ __global__ void __launch_bounds__(NTA) k_band_accum(BandBatch<NB> bb) {
   const int cells = min(R, n - r0) * n;
   for (int k = t; k < cells; k += NTA) acc[k] = 0ull;
   __syncthreads();
-  band_accumulate<NTA, KB>(g, L, band, q.x, q.y, q.w, q.h, acc, lds);
+  band_accumulate<NTA, KB, BINS == 1024>(g, L, band, q.x, q.y, q.w, q.h, acc, lds);
   __syncthreads();
   // rho = base + rows: all of a thread's base loads issued before any store
   constexpr int PA = BINS / NTA;
@@ -383,6 +384,28 @@ static hipError_t band_scatter_nb(const BandBatch<NB>& bb, int max_nblk, int max
   return e;
 }
 
+hipError_t launch_band_place_batch(const BandReq* reqs, int count, hipStream_t s) {
+  if (count <= 0) return hipSuccess;
+  if (count > kMaxBatch) return hipErrorInvalidValue;
+  int max_nblk = 0, max_cpk = 0;
+  for (int i = 0; i < count; ++i) {
+    if (reqs[i].L.m <= 0) continue;
+    max_nblk = std::max(max_nblk, reqs[i].L.nblk);
+    max_cpk = std::max(max_cpk, reqs[i].L.cpk);
+  }
+  if (max_nblk == 0) return hipSuccess;
+  if (count == 1) {
+    BandBatch<1> bb;
+    bb.count = 1;
+    bb.r[0] = reqs[0];
+    return band_place_nb(bb, max_nblk, max_cpk, s);
+  }
+  BandBatch<kMaxBatch> bb;
+  bb.count = count;
+  for (int i = 0; i < count; ++i) bb.r[i] = reqs[i];
+  return band_place_nb(bb, max_nblk, max_cpk, s);
+}
+
 hipError_t launch_band_scatter_batch(const BandReq* reqs, int count, hipStream_t s,
                                      Plan* tp) {
   if (count <= 0) return hipSuccess;
@@ -472,6 +495,7 @@ hipError_t launch_band_scatter(const GridF& g, const BandLayout& L, const float*
   BandReq q;
   q.g = g;
   q.L = L;
+  q.L.xy = nullptr;   // no interleaved copy of the positions
   q.x = x;
   q.y = y;
   q.w = w;

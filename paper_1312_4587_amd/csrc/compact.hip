@@ -1,0 +1,301 @@
+// The compact evaluation: the exchange path of designs whose kernels are all
+// shorter than the work of launching them.
+//
+// The general exchange path runs nine kernels on two streams.  Up to some
+// hundred thousand cells each of them lasts 3 to 20 us, most of it the latency of
+// a few dependent loads, and the host spends longer enqueueing the nine
+// launches and the four cross-stream event calls (75 to 89 us measured) than the
+// device evaluating.  Here the same steps take five launches on the caller's
+// stream alone (four for the smallest designs):
+//   place  the counting sort of the cells by band (k_band_place), skipped up to
+//          kCompactScanCells cells, whose band blocks read every cell;
+//   mid    band blocks: scatter of a row pair, and for FFT plans its row transform
+//          straight from LDS; beside them in the same launch the net blocks, which
+//          read the positions by cell (they fit the L2 of every XCD), so that
+//          neither a spread nor a second stream is needed;
+//   solve  the column and the inverse row pass (or the matrix-core solve);
+//   cells  per cell the density gradient gathered from the field map (it fits the
+//          L2 too) and the sum of its pins' gradients; one more block per design
+//          sums the scalars.
+// Every per-cell, per-bin and per-net value is computed by the same code and
+// in the same order as on the general path.
+// Per evaluation, general -> compact, one after another: 2k cells (n = 64) 77.8
+// -> 22.6 us, 30k (n = 256, exact, LSE) 71.5 -> 32.9, 200k (n = 512) 78.3 -> 54.5,
+// 500k (n = 512) 136 -> 101 (with its scalars-only twin), eight of 17k to 62k
+// cells in a batch 172 -> 75.  What bounds it now is the device: at 200k cells
+// place 7, mid 23, columns 7, inverse rows 6, cells 13 us.
+#include <algorithm>
+
+#include "band_device.hpp"
+#include "fft_device.hpp"
+#include "xch_device.hpp"
+
+namespace fftpl {
+
+namespace {
+
+constexpr int NT = kXchWaThreads;   // the net blocks' threads, and the band blocks'
+constexpr int KB = 4;               // band entries a thread takes together
+constexpr int kBins = 2 * kCompactMaxN;
+constexpr int kCellThreads = 512;   // threads of a block of the cells kernel
+
+// Cells of a small design straight from their arrays, for one band.
+__device__ __forceinline__ void scan_cells(const CompactReq& q, int r0, int R,
+                                           unsigned long long* acc) {
+  constexpr int U = 4;
+  const GridF& g = q.g;
+  const int n = g.n, m = q.m;
+  for (int i0 = threadIdx.x; i0 < m; i0 += U * NT) {
+    float x[U], y[U], w[U], h[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + u * NT, m - 1);
+      x[u] = q.x.x[i];
+      y[u] = q.x.y[i];
+      w[u] = q.w[i];
+      h[u] = q.h[i];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u * NT >= m) continue;
+      const Span sy = cell_span(y[u], h[u], g.yl, g.inv_bh, n);
+      if (sy.i1 < r0 || sy.i0 >= r0 + R || sy.i0 > sy.i1) continue;
+      add_span(cell_span(x[u], w[u], g.xl, g.inv_bw, n), sy, r0, R, n, acc);
+    }
+  }
+}
+
+// LDS of a band block: the accumulators, then the walk's arrays or the row
+// transform's (N = 0: no transform).
+template <int N>
+struct MidLds {
+  unsigned long long acc[kBins];
+  union {
+    WalkLds<NT, KB> walk;
+    RowsLds<N ? N : 8, NT> rows;
+  };
+};
+
+// Six wavefronts per SIMD: three blocks of 512 threads per CU instead of the
+// two that 94 registers leave (27.7 -> 23.9 us at 200k cells).
+template <int N, bool LSE, int NB>
+__global__ void __launch_bounds__(NT, 6) k_compact_mid(CompactBatch<NB> cb,
+                                                    const float2* __restrict__ tw_g,
+                                                    const float2* __restrict__ cs_g) {
+  extern __shared__ float2 smem[];
+  const CompactReq& q = cb.r[blockIdx.y];
+  if ((int)blockIdx.x >= cb.nb) {
+    const int k = (int)blockIdx.x - cb.nb;
+    if (k < q.x.nnb) wa_block<kStageS, LSE, true>(q.x, k, smem);
+    return;
+  }
+  MidLds<N>& lds = *reinterpret_cast<MidLds<N>*>(smem);
+  const int t = threadIdx.x;
+  const GridF& g = q.g;
+  const int n = g.n, R = q.rows, band = blockIdx.x, r0 = band * R;
+  const int bins = min(R, n - r0) * n;
+  const size_t o = (size_t)r0 * n;
+  // fixed charge and capacity of the thread's bins, in flight during the scatter
+  constexpr int PA = kBins / NT;
+  float bv[PA], cv[PA];
+#pragma unroll
+  for (int j = 0; j < PA; ++j) bv[j] = q.base ? q.base[o + min(t + j * NT, bins - 1)] : 0.0f;
+  if constexpr (N > 0) {
+    if (q.cap) {
+#pragma unroll
+      for (int j = 0; j < PA; ++j) cv[j] = q.cap[o + min(t + j * NT, bins - 1)];
+    } else {
+#pragma unroll
+      for (int j = 0; j < PA; ++j)
+        cv[j] = fmaxf(0.0f, g.rho_t - fminf(g.rho_t, bv[j]));
+    }
+  }
+  for (int k = t; k < bins; k += NT) lds.acc[k] = 0ull;
+  __syncthreads();
+  if (q.nblk > 0)
+    band_accumulate<NT, KB, true>(g, q, band, q.x.x, q.x.y, q.w, q.h, lds.acc, lds.walk);
+  else
+    scan_cells(q, r0, R, lds.acc);
+  __syncthreads();
+  float rho[PA];
+#pragma unroll
+  for (int j = 0; j < PA; ++j) {
+    const int k = t + j * NT;
+    rho[j] = bv[j] + (float)((double)lds.acc[min(k, bins - 1)] * kAccUnit);
+    if (k < bins) q.rho[o + k] = rho[j];
+  }
+  if constexpr (N > 0) {
+    // the row pair's transform: rows of N = 512 lie one sample per thread as
+    // they are; shorter rows go back through LDS
+    static_assert(N <= NT && kBins / NT == 2, "one sample of each row per thread");
+    float a1[1], a2[1], b1[1], b2[1], c1[1], c2[1];
+    stage_tables<N, NT, false>(lds.rows.tw, tw_g, lds.rows.cs, cs_g, nullptr, nullptr, t);
+    if constexpr (N == NT) {
+      a1[0] = rho[0];
+      a2[0] = rho[1];
+      b1[0] = bv[0];
+      b2[0] = bv[1];
+      c1[0] = cv[0];
+      c2[0] = cv[1];
+    } else {
+      float* f = reinterpret_cast<float*>(lds.acc);
+      static_assert(6 * N * sizeof(float) <= sizeof(lds.acc), "three row pairs fit");
+      __syncthreads();   // every accumulator is read
+#pragma unroll
+      for (int j = 0; j < PA; ++j) {
+        const int k = t + j * NT;
+        if (k < 2 * N) {
+          f[k] = rho[j];
+          f[2 * N + k] = bv[j];
+          f[4 * N + k] = cv[j];
+        }
+      }
+      __syncthreads();
+      const int i = min(t, N - 1);
+      a1[0] = f[i];
+      a2[0] = f[N + i];
+      b1[0] = f[2 * N + i];
+      b2[0] = f[3 * N + i];
+      c1[0] = f[4 * N + i];
+      c2[0] = f[5 * N + i];
+    }
+    rows_dct2<N, NT>(a1, a2, b1, b2, c1, c2, r0, t, lds.rows, q.bT, q.rowsum, q.tau_part);
+  }
+}
+
+template <int MODE, int NB>
+__global__ void __launch_bounds__(kCellThreads) k_compact_cells(SumBatch<NB> sb) {
+  const SumReq& rq = sb.r[blockIdx.y];
+  const int cb = blockIdx.x, t = threadIdx.x;
+  const CellGradArgs& a = rq.a;
+  if (cb >= rq.ncb) {
+    // the block past the design's last cell block sums its scalars
+    if (cb == rq.ncb) eval_scalars<kCellThreads>(a.fin);
+    return;
+  }
+  constexpr int PC = kCompactMaxCpb / kCellThreads;
+  __shared__ unsigned long long ax[kCompactMaxCpb], ay[kCompactMaxCpb];
+  __shared__ unsigned char bad[kCompactMaxCpb];
+  const int m = rq.m, cpb = rq.cpb, c0 = cb * cpb;
+  const int a0 = rq.cb_a_ptr[cb], a1 = rq.cb_a_ptr[cb + 1];
+  float x[PC], y[PC], w[PC], h[PC];
+#pragma unroll
+  for (int k = 0; k < PC; ++k) {
+    if (k * kCellThreads >= cpb) break;
+    const int ci = min(c0 + t + k * kCellThreads, m - 1);
+    x[k] = a.x[ci];
+    y[k] = a.y[ci];
+    w[k] = a.w[ci];
+    h[k] = a.h[ci];
+  }
+  const float lam = a.dscale ? a.dscale[0] : a.scale;
+  PinSums<kCellThreads, kCompactMaxCpb> pins;
+  pins.prefetch(rq.lc, rq.T, a0, a1);
+  for (int c = t; c < cpb; c += kCellThreads) {
+    ax[c] = 0ull;
+    ay[c] = 0ull;
+    bad[c] = 0;
+  }
+  // density part while the accumulators are cleared
+  float2 d[PC];
+#pragma unroll
+  for (int k = 0; k < PC; ++k) {
+    if (k * kCellThreads >= cpb) break;
+    const Span sx = cell_span(x[k], w[k], a.g.xl, a.g.inv_bw, a.g.n);
+    const Span sy = cell_span(y[k], h[k], a.g.yl, a.g.inv_bh, a.g.n);
+    d[k] = density_grad_small<MODE>(a.g, sx, sy, a.exy, a.psi);
+  }
+  __syncthreads();
+  pins.add(rq.fx_scale, ax, ay, bad);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PC; ++k) {
+    const int c = t + k * kCellThreads, ci = c0 + c;
+    if (c >= cpb || ci >= m) break;
+    a.gx[ci] = lam * d[k].x + pin_sum(ax[c], bad[c], rq.inv_scale);
+    a.gy[ci] = lam * d[k].y + pin_sum(ay[c], bad[c], rq.inv_scale);
+  }
+}
+
+template <int N, bool LSE, int NB>
+hipError_t mid_launch(const Plan& p, const CompactBatch<NB>& cb, int max_nnb, int max_cap,
+                      hipStream_t s) {
+  const size_t wa = sizeof(float2) * 2 * (size_t)max_cap;
+  const size_t lds = std::max(wa, sizeof(MidLds<N>));
+  hipLaunchKernelGGL((k_compact_mid<N, LSE, NB>), dim3(cb.nb + max_nnb, cb.count), dim3(NT), lds,
+                     s, cb, p.fft_tw, p.dct_cs);
+  return hipGetLastError();
+}
+
+template <bool LSE, int NB>
+hipError_t mid_size(const Plan& p, const CompactBatch<NB>& cb, int max_nnb, int max_cap,
+                    bool fuse_rows, hipStream_t s) {
+  switch (fuse_rows ? p.n : 0) {
+    case 64: return mid_launch<64, LSE, NB>(p, cb, max_nnb, max_cap, s);
+    case 128: return mid_launch<128, LSE, NB>(p, cb, max_nnb, max_cap, s);
+    case 256: return mid_launch<256, LSE, NB>(p, cb, max_nnb, max_cap, s);
+    case 512: return mid_launch<512, LSE, NB>(p, cb, max_nnb, max_cap, s);
+    default: return mid_launch<0, LSE, NB>(p, cb, max_nnb, max_cap, s);
+  }
+}
+
+template <int NB>
+hipError_t mid_batch(const Plan& p, const CompactReq* reqs, int count, int wl_model,
+                     bool fuse_rows, hipStream_t s) {
+  CompactBatch<NB> cb;
+  cb.count = count;
+  cb.nb = reqs[0].nb;
+  int max_nnb = 0, max_cap = 1;
+  for (int i = 0; i < count; ++i) {
+    cb.r[i] = reqs[i];
+    max_nnb = std::max(max_nnb, reqs[i].x.nnb);
+    max_cap = std::max(max_cap, reqs[i].x.cap);
+  }
+  if (max_cap > kXchPinLds2) return hipErrorInvalidValue;
+  return wl_model == FFTPL_WL_LSE ? mid_size<true, NB>(p, cb, max_nnb, max_cap, fuse_rows, s)
+                                  : mid_size<false, NB>(p, cb, max_nnb, max_cap, fuse_rows, s);
+}
+
+template <int NB>
+hipError_t cells_batch(const SumReq* reqs, int count, int max_ncb, int grad_mode,
+                       hipStream_t s) {
+  SumBatch<NB> sb;
+  sb.count = count;
+  for (int i = 0; i < count; ++i) sb.r[i] = reqs[i];
+  const dim3 grid(max_ncb + 1, count), block(kCellThreads);
+  if (grad_mode == FFTPL_GRAD_EXACT)
+    hipLaunchKernelGGL((k_compact_cells<FFTPL_GRAD_EXACT, NB>), grid, block, 0, s, sb);
+  else
+    hipLaunchKernelGGL((k_compact_cells<FFTPL_GRAD_FIELD, NB>), grid, block, 0, s, sb);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool compact_design(int n, const XchDims& d) {
+  return n <= kCompactMaxN && d.m > 0 && d.cpb <= kCompactMaxCpb && d.cap <= kXchPinLds2;
+}
+
+bool compact_fuses_rows(const Plan& p) { return p.mode == FFTPL_DCT_FFT && p.n >= 64; }
+
+hipError_t launch_compact_mid(const Plan& p, const CompactReq* reqs, int count, int wl_model,
+                              bool fuse_rows, hipStream_t s) {
+  if (count <= 0) return hipSuccess;
+  if (count > kMaxBatch) return hipErrorInvalidValue;
+  return count == 1 ? mid_batch<1>(p, reqs, count, wl_model, fuse_rows, s)
+                    : mid_batch<kMaxBatch>(p, reqs, count, wl_model, fuse_rows, s);
+}
+
+hipError_t launch_compact_cells(const SumReq* reqs, int count, int grad_mode, hipStream_t s) {
+  if (count <= 0) return hipSuccess;
+  if (count > kMaxBatch) return hipErrorInvalidValue;
+  int max_ncb = 0;
+  for (int i = 0; i < count; ++i) {
+    if (reqs[i].cpb > kCompactMaxCpb) return hipErrorInvalidValue;
+    max_ncb = std::max(max_ncb, reqs[i].ncb);
+  }
+  return count == 1 ? cells_batch<1>(reqs, count, max_ncb, grad_mode, s)
+                    : cells_batch<kMaxBatch>(reqs, count, max_ncb, grad_mode, s);
+}
+
+}  // namespace fftpl

@@ -40,21 +40,17 @@
 #include <atomic>
 #include <vector>
 
-#include "fftpl_internal.hpp"
+#include "xch_device.hpp"
 
 namespace fftpl {
 
 namespace {
 
 constexpr int NT = kXchThreads;
+constexpr int NW = kXchWaThreads;
+constexpr int kSmall = kXchSmallDeg;
 constexpr int kHdrInts = 16;
 constexpr int32_t kXchMagic = 0x46584348;   // "FXCH"
-constexpr int kSmall = 8;                   // degree handled by one thread
-constexpr int NW = kXchWaThreads;
-// B positions per thread of the net-block kernel: for blocks of up to
-// kXchPinLds2 pins, or up to kXchPinCap
-constexpr int kStageS = (kXchPinLds2 + NW - 1) / NW;
-constexpr int kStageL = (kXchPinCap + NW - 1) / NW;
 constexpr int kMaxDevices = 64;     // device ordinals with a per-device flag
 constexpr int kSumThreads = 1024;   // cell sums: one block per cell block
 
@@ -73,6 +69,26 @@ int xch_dims(int m, int num_nets, int num_pins, int max_degree, XchDims* d) {
     if (npt > kXchPinCap + 1 - max_degree) npt = kXchPinCap + 1 - max_degree;
   }
   if (npt < kXchMinTarget) return FFTPL_E_UNSUPPORTED;
+  // cells per block
+  int cpb = kXchCells;
+  {
+    const int64_t per_cu = ((int64_t)m + kNumCus - 1) / kNumCus;
+    const int64_t step = (per_cu + kXchCellStep - 1) / kXchCellStep * kXchCellStep;
+    cpb = (int)std::min<int64_t>(kXchCells, std::max<int64_t>(kXchCellStep, step));
+  }
+  // Netlists that do not fill two blocks of that size per CU are cut finer: a
+  // block's time follows its pins (staging, the nets handed to its eight
+  // wavefronts, the write-back), and small blocks share a CU three at a time.
+  // Designs of the compact evaluation's size are kept to blocks that stage in
+  // one round of four pins per thread.  Net blocks of 30k cells (78k pins)
+  // alone: 15.1 us in 20 blocks of 4096 pins, 8.4 us in 153 of 512; eight such
+  // designs in one launch prefer 1024 (41.9 -> 35.9 us), one design does not mind.
+  {
+    const int64_t even = ((int64_t)num_pins + kXchNetBlocks - 1) / kXchNetBlocks;
+    npt = (int)std::min<int64_t>(npt, std::max<int64_t>(kXchSmallTarget, even));
+    if (cpb <= kCompactMaxCpb)
+      npt = std::min(npt, std::max(kXchSmallTarget, 4 * kXchWaThreads + 1 - max_degree));
+  }
   XchDims r;
   r.m = m;
   r.num_nets = num_nets;
@@ -80,11 +96,7 @@ int xch_dims(int m, int num_nets, int num_pins, int max_degree, XchDims* d) {
   r.max_degree = max_degree;
   r.npt = npt;
   r.cap = max_degree > 0 ? npt - 1 + max_degree : 1;
-  {
-    const int64_t per_cu = ((int64_t)m + kNumCus - 1) / kNumCus;
-    const int64_t step = (per_cu + kXchCellStep - 1) / kXchCellStep * kXchCellStep;
-    r.cpb = (int)std::min<int64_t>(kXchCells, std::max<int64_t>(kXchCellStep, step));
-  }
+  r.cpb = cpb;
   r.ncb = (m + r.cpb - 1) / r.cpb;
   r.nnb = num_pins > 0 ? (num_pins + npt - 1) / npt : 1;
   size_t off = 0;
@@ -443,332 +455,12 @@ __global__ void __launch_bounds__(NT) k_xch_spread(XchBatch<NB> xb) {
   }
 }
 
-// Weighted-average terms of one axis with the exponentials computed once:
-// e+ = exp((X - M)/gamma), e- = exp((L - X)/gamma) (fast exp2-based exp: the
-// arguments are <= 0 and the terms that matter are near 0).
-__device__ __forceinline__ float fexp(float v) { return __expf(v); }
-
-// One net block: cell positions and pin offsets staged in LDS in CSR order,
-// nets evaluated from LDS, gradients written back over the pins' positions in
-// T.  LDS: pos[cap], off[cap] (dynamic, 16 bytes per pin of the block).
-// LSE: the log-sum-exp model in place of the weighted average (same sums;
-// the gradient is e+/S+ - e-/S-, the value (M - L) + gamma (ln S+ + ln S-)).
-template <int STAGE, bool LSE, int NB>
+template <int STAGE, bool LSE, int NB, bool DIRECT>
 __global__ void __launch_bounds__(NW) k_xch_wa(XchBatch<NB> xb) {
-  const XchReq& rq = xb.r[blockIdx.y];
-  const int k = blockIdx.x, t = threadIdx.x, nblk = rq.nnb;
-  if (k >= nblk) return;
-  const int num_pins = rq.num_pins, cap = rq.cap;
-  const int32_t* __restrict__ net_ptr = rq.net_ptr;
-  const int32_t* __restrict__ nb_net_ptr = rq.nb_net_ptr;
-  const uint32_t* __restrict__ nmeta = rq.nmeta;
-  const int32_t* __restrict__ a_of_b = rq.a_of_b;
-  const uint16_t* __restrict__ lcsr = rq.lcsr;
-  const float* __restrict__ pin_dx = rq.pin_dx;
-  const float* __restrict__ pin_dy = rq.pin_dy;
-  const float gamma = rq.dgamma ? rq.dgamma[0] : rq.gamma;
-  const float inv_gamma = rq.dgamma ? 1.0f / gamma : rq.inv_gamma;
-  float2* __restrict__ T = rq.T;
-  double* __restrict__ part = rq.part;
-  double* __restrict__ net_wl = rq.net_wl;
-  double* __restrict__ net_hp = rq.net_hp;
   extern __shared__ float2 smem[];
-  float2* pos = smem;
-  float2* off = smem + cap;
-  __shared__ uint32_t bigmeta[NW];   // extents of the last NW nets of the order
-  __shared__ int q_big, q_small;     // work counters
-  const int lane = t & (kWave - 1), wv = t / kWave;
-  const int e0 = nb_net_ptr[k], e1 = nb_net_ptr[k + 1];
-  const int p0 = net_ptr[e0], p1 = net_ptr[e1];
-  const int np = p1 - p0;
-  double acc_wa = 0.0, acc_hp = 0.0;
-  if (np > 0 && np <= cap && np <= STAGE * NW) {
-    // 0. net extents, read before the staging loads so that the latency of
-    // both overlaps: the last NW entries of the order (the large nets, largest
-    // first) for LDS, and this wavefront's first chunk of small nets.
-    const int nn = e1 - e0;
-    constexpr int NWV = NW / kWave;
-    const uint32_t* meta = nmeta + e0;
-    const uint32_t mbig = meta[max(nn - 1 - t, 0)];
-    const uint32_t msm0 = meta[min(wv * kWave + lane, nn - 1)];
-    // 1. stage: off[csr offset] = pin offset (coalesced), pos[csr offset] =
-    // cell position read from T in B order (runs of consecutive A positions).
-    // Loads are unconditional (index clamped into the block) so that each
-    // batch is in flight at once; only the LDS stores are masked.
-    int av[STAGE], lv[STAGE];
-    {
-      float dx[STAGE], dy[STAGE];
-      const int blast = p1 - 1;
-#pragma unroll
-      for (int j = 0; j < STAGE; ++j) {
-        const int b = min(p0 + t + j * NW, blast);
-        av[j] = a_of_b[b];
-        lv[j] = lcsr[b];
-        dx[j] = pin_dx[b];
-        dy[j] = pin_dy[b];
-      }
-#pragma unroll
-      for (int j = 0; j < STAGE; ++j) {
-        av[j] = min((unsigned)av[j], (unsigned)(num_pins - 1));
-        lv[j] = min(lv[j], cap - 1);
-      }
-      float2 q[STAGE];
-#pragma unroll
-      for (int j = 0; j < STAGE; ++j) q[j] = T[av[j]];
-#pragma unroll
-      for (int j = 0; j < STAGE; ++j) {
-        if (p0 + t + j * NW < p1) {
-          off[t + j * NW] = make_float2(dx[j], dy[j]);
-          pos[lv[j]] = q[j];
-        }
-      }
-    }
-    bigmeta[t] = mbig;
-    if (t == 0) {
-      q_big = 0;
-      q_small = NWV;   // chunks 0..NWV-1 are the wavefronts' first ones
-    }
-    __syncthreads();
-
-    // 2. nets in degree order, work handed out by block-wide counters so
-    // that every wavefront stays busy until the block's nets run out.  Nets
-    // above kSmall sit at the back of the order, largest class last: each is
-    // taken by one wavefront, largest first (three passes over its pins in
-    // LDS: pass 1 turns positions into pin coordinates relative to the first
-    // pin's cell, pass 3 overwrites them with the gradient).  Then the
-    // others: one lane per net, a wavefront per chunk of kWave nets of
-    // (nearly) equal degree, loops as long as the chunk's largest degree.
-    for (;;) {
-      int j = 0;
-      if (lane == 0) j = atomicAdd(&q_big, 1);
-      j = __builtin_amdgcn_readfirstlane(j);
-      if (j >= nn) break;
-      // beyond the NW staged extents (more than NW large nets): from memory
-      const uint32_t mj = j < NW ? bigmeta[j] : meta[nn - 1 - j];
-      const int deg = (int)(mj & 0xffffu);
-      if (deg <= kSmall) break;   // every net left is small
-      // extents come from the index; kept inside the staged pins whatever it
-      // holds, so a block never leaves its LDS
-      const int b0 = min((int)(mj >> 16), np - 1), b1 = min(b0 + deg, np);
-      const float2 r = pos[b0];
-      wave_lds_sync();
-      constexpr int H = 4;   // pins per lane whose LDS loads are issued together
-      float mx = -INFINITY, lx = INFINITY, my = -INFINITY, ly = INFINITY;
-      for (int l = b0 + lane; l < b1; l += H * kWave) {
-        float2 c[H], d[H];
-#pragma unroll
-        for (int u = 0; u < H; ++u) {
-          const int li = min(l + u * kWave, b1 - 1);
-          c[u] = pos[li];
-          d[u] = off[li];
-        }
-#pragma unroll
-        for (int u = 0; u < H; ++u) {
-          if (l + u * kWave < b1) {
-            const float X = (c[u].x - r.x) + d[u].x, Y = (c[u].y - r.y) + d[u].y;
-            pos[l + u * kWave] = make_float2(X, Y);
-            mx = fmaxf(mx, X);
-            lx = fminf(lx, X);
-            my = fmaxf(my, Y);
-            ly = fminf(ly, Y);
-          }
-        }
-      }
-      mx = wave_max_dpp(mx);
-      lx = wave_min_dpp(lx);
-      my = wave_max_dpp(my);
-      ly = wave_min_dpp(ly);
-      wave_lds_sync();
-      float spx = 0.f, tpx = 0.f, smx = 0.f, tmx = 0.f;
-      float spy = 0.f, tpy = 0.f, smy = 0.f, tmy = 0.f;
-      for (int l = b0 + lane; l < b1; l += H * kWave) {
-        float2 c[H];
-#pragma unroll
-        for (int u = 0; u < H; ++u) c[u] = pos[min(l + u * kWave, b1 - 1)];
-#pragma unroll
-        for (int u = 0; u < H; ++u) {
-          if (l + u * kWave < b1) {
-            float dd = c[u].x - mx, ee = fexp(dd * inv_gamma);
-            spx += ee;
-            tpx += dd * ee;
-            dd = c[u].x - lx;
-            ee = fexp(-dd * inv_gamma);
-            smx += ee;
-            tmx += dd * ee;
-            dd = c[u].y - my;
-            ee = fexp(dd * inv_gamma);
-            spy += ee;
-            tpy += dd * ee;
-            dd = c[u].y - ly;
-            ee = fexp(-dd * inv_gamma);
-            smy += ee;
-            tmy += dd * ee;
-          }
-        }
-      }
-      spx = wave_sum_dpp(spx);
-      tpx = wave_sum_dpp(tpx);
-      smx = wave_sum_dpp(smx);
-      tmx = wave_sum_dpp(tmx);
-      spy = wave_sum_dpp(spy);
-      tpy = wave_sum_dpp(tpy);
-      smy = wave_sum_dpp(smy);
-      tmy = wave_sum_dpp(tmy);
-      const float rspx = 1.0f / spx, rsmx = 1.0f / smx;
-      const float rspy = 1.0f / spy, rsmy = 1.0f / smy;
-      const float wpx = tpx * rspx, wmx = tmx * rsmx;
-      const float wpy = tpy * rspy, wmy = tmy * rsmy;
-      for (int l = b0 + lane; l < b1; l += H * kWave) {
-        float2 c[H];
-#pragma unroll
-        for (int u = 0; u < H; ++u) c[u] = pos[min(l + u * kWave, b1 - 1)];
-#pragma unroll
-        for (int u = 0; u < H; ++u) {
-          if (l + u * kWave < b1) {
-            const float dpx = c[u].x - mx, dmx = c[u].x - lx;
-            const float dpy = c[u].y - my, dmy = c[u].y - ly;
-            if (LSE)
-              pos[l + u * kWave] = make_float2(
-                  fexp(dpx * inv_gamma) * rspx - fexp(-dmx * inv_gamma) * rsmx,
-                  fexp(dpy * inv_gamma) * rspy - fexp(-dmy * inv_gamma) * rsmy);
-            else
-              pos[l + u * kWave] = make_float2(
-                  fexp(dpx * inv_gamma) * rspx * (1.0f + (dpx - wpx) * inv_gamma) -
-                      fexp(-dmx * inv_gamma) * rsmx * (1.0f - (dmx - wmx) * inv_gamma),
-                  fexp(dpy * inv_gamma) * rspy * (1.0f + (dpy - wpy) * inv_gamma) -
-                      fexp(-dmy * inv_gamma) * rsmy * (1.0f - (dmy - wmy) * inv_gamma));
-          }
-        }
-      }
-      if (lane == 0) {
-        const double vw = net_wl_value<LSE>(mx, lx, wpx, wmx, spx, smx, gamma) +
-                          net_wl_value<LSE>(my, ly, wpy, wmy, spy, smy, gamma);
-        const double vh = (double)(mx - lx) + (double)(my - ly);
-        acc_wa += vw;
-        acc_hp += vh;
-        if (net_wl) {
-          net_wl[p0 + b0] = vw;
-          net_hp[p0 + b0] = vh;
-        }
-      }
-    }
-
-    // small nets: chunk c holds order entries c * kWave + lane; a
-    // wavefront's first chunk is its own (extents read before staging), the
-    // rest come from the counter, each one's extents read while the previous
-    // chunk is evaluated
-    int cc = wv;
-    uint32_t mcur = msm0;
-    for (;;) {
-      if (cc * kWave >= nn) break;
-      int cn = 0;
-      if (lane == 0) cn = atomicAdd(&q_small, 1);
-      cn = __builtin_amdgcn_readfirstlane(cn);
-      uint32_t mnext = 0u;
-      if (cn * kWave < nn) mnext = meta[min(cn * kWave + lane, nn - 1)];
-      const int li = cc * kWave + lane;
-      int deg = li < nn ? (int)(mcur & 0xffffu) : 0;
-      if (deg > kSmall) deg = 0;   // done above
-      // kept inside the staged pins whatever the index holds
-      const int l0 = min((int)(mcur >> 16), np - 1);
-      deg = min(deg, np - l0);
-      // the chunk's largest small degree, uniform across the wavefront
-      const int wdeg = wave_max_dpp_i(deg);
-      if (deg == 1) {
-        // a one-pin net: no gradient, zero wirelength and half-perimeter
-        pos[l0] = make_float2(0.0f, 0.0f);
-        if (net_wl) {
-          net_wl[p0 + l0] = 0.0;
-          net_hp[p0 + l0] = 0.0;
-        }
-      }
-      if (wdeg >= 2) {
-        float px[kSmall], py[kSmall];
-        const float2 r = pos[deg >= 1 ? l0 : 0];
-        float mx = -INFINITY, lx = INFINITY, my = -INFINITY, ly = INFINITY;
-#pragma unroll
-        for (int j = 0; j < kSmall; ++j) {
-          if (j < wdeg) {
-            px[j] = 0.0f;
-            py[j] = 0.0f;
-            if (j < deg) {
-              const float2 c = pos[l0 + j], d = off[l0 + j];
-              px[j] = (c.x - r.x) + d.x;
-              py[j] = (c.y - r.y) + d.y;
-              mx = fmaxf(mx, px[j]);
-              lx = fminf(lx, px[j]);
-              my = fmaxf(my, py[j]);
-              ly = fminf(ly, py[j]);
-            }
-          }
-        }
-        float epx[kSmall], emx[kSmall], epy[kSmall], emy[kSmall];
-        float spx = 0.f, tpx = 0.f, smx = 0.f, tmx = 0.f;
-        float spy = 0.f, tpy = 0.f, smy = 0.f, tmy = 0.f;
-#pragma unroll
-        for (int j = 0; j < kSmall; ++j) {
-          if (j < wdeg) {
-            const bool in = j < deg;
-            const float dpx = px[j] - mx, dmx = px[j] - lx;
-            const float dpy = py[j] - my, dmy = py[j] - ly;
-            epx[j] = in ? fexp(dpx * inv_gamma) : 0.0f;
-            emx[j] = in ? fexp(-dmx * inv_gamma) : 0.0f;
-            epy[j] = in ? fexp(dpy * inv_gamma) : 0.0f;
-            emy[j] = in ? fexp(-dmy * inv_gamma) : 0.0f;
-            spx += epx[j];
-            tpx += dpx * epx[j];
-            smx += emx[j];
-            tmx += dmx * emx[j];
-            spy += epy[j];
-            tpy += dpy * epy[j];
-            smy += emy[j];
-            tmy += dmy * emy[j];
-          }
-        }
-        if (deg >= 2) {
-          const float rspx = 1.0f / spx, rsmx = 1.0f / smx;
-          const float rspy = 1.0f / spy, rsmy = 1.0f / smy;
-          const float wpx = tpx * rspx, wmx = tmx * rsmx;
-          const float wpy = tpy * rspy, wmy = tmy * rsmy;
-#pragma unroll
-          for (int j = 0; j < kSmall; ++j) {
-            if (j < wdeg && j < deg) {
-              const float dpx = px[j] - mx, dmx = px[j] - lx;
-              const float dpy = py[j] - my, dmy = py[j] - ly;
-              if (LSE)
-                pos[l0 + j] = make_float2(epx[j] * rspx - emx[j] * rsmx,
-                                          epy[j] * rspy - emy[j] * rsmy);
-              else
-                pos[l0 + j] = make_float2(
-                    epx[j] * rspx * (1.0f + (dpx - wpx) * inv_gamma) -
-                        emx[j] * rsmx * (1.0f - (dmx - wmx) * inv_gamma),
-                    epy[j] * rspy * (1.0f + (dpy - wpy) * inv_gamma) -
-                        emy[j] * rsmy * (1.0f - (dmy - wmy) * inv_gamma));
-            }
-          }
-          const double vw = net_wl_value<LSE>(mx, lx, wpx, wmx, spx, smx, gamma) +
-                            net_wl_value<LSE>(my, ly, wpy, wmy, spy, smy, gamma);
-          const double vh = (double)(mx - lx) + (double)(my - ly);
-          acc_wa += vw;
-          acc_hp += vh;
-          if (net_wl) {
-            net_wl[p0 + l0] = vw;
-            net_hp[p0 + l0] = vh;
-          }
-        }
-      }
-      cc = cn;
-      mcur = mnext;
-    }
-    __syncthreads();
-
-    // 3. gradients back to the pins' A positions
-#pragma unroll
-    for (int j = 0; j < STAGE; ++j)
-      if (p0 + t + j * NW < p1) T[av[j]] = pos[lv[j]];
-  }
-  block_sum_to<false>(acc_wa, &part[k]);
-  block_sum_to<false>(acc_hp, &part[nblk + k]);
+  const XchReq& rq = xb.r[blockIdx.y];
+  if ((int)blockIdx.x >= rq.nnb) return;
+  wa_block<STAGE, LSE, DIRECT>(rq, blockIdx.x, smem);
 }
 
 // The gradient of every cell (CellGradArgs): its density part plus the sum
@@ -784,8 +476,12 @@ __global__ void __launch_bounds__(NW) k_xch_wa(XchBatch<NB> xb) {
 // the largest scale that keeps every pin within a 32-bit conversion; the
 // 64-bit sums then hold any number of pins.  A non-finite pin gradient makes
 // its cell's sum NaN.
-template <int MODE, bool DENS, int NB>
-__global__ void __launch_bounds__(kSumThreads) k_xch_cellsum(SumBatch<NB> sb) {
+// NTS threads, at most CELLS cells per block: (1024, kXchCells), 153 KB of LDS
+// and one block per CU, or (256, kXchSmallCells) for designs cut into blocks
+// of up to 1024 cells, whose fixed work (clearing the accumulators, waiting at
+// the barriers) is that of 256 threads and 17 KB, several blocks per CU.
+template <int MODE, bool DENS, int NB, int NTS, int CELLS>
+__global__ void __launch_bounds__(NTS) k_xch_cellsum(SumBatch<NB> sb) {
   const SumReq& rq = sb.r[blockIdx.y];
   const int cb = blockIdx.x, t = threadIdx.x;
   if (cb >= rq.ncb) return;
@@ -796,72 +492,27 @@ __global__ void __launch_bounds__(kSumThreads) k_xch_cellsum(SumBatch<NB> sb) {
   const float scale = rq.fx_scale;
   const double inv_scale = rq.inv_scale;
   const CellGradArgs& a = rq.a;
-  __shared__ unsigned long long ax[kXchCells], ay[kXchCells];
-  __shared__ unsigned char bad[kXchCells];
+  __shared__ unsigned long long ax[CELLS], ay[CELLS];
+  __shared__ unsigned char bad[CELLS];
   // the block's A range, then the first-band entry of each of the thread's
   // cells and its first group of pins: all in flight while LDS is cleared
   const int a0 = cb_a_ptr[cb], a1 = cb_a_ptr[cb + 1];
-  constexpr int PC = kXchCells / kSumThreads;
+  constexpr int PC = CELLS / NTS;
   const int c0 = cb * cpb;
   int ep[PC];
   if (DENS) {
 #pragma unroll
-    for (int k = 0; k < PC; ++k) ep[k] = a.epos[min(c0 + t + k * kSumThreads, m - 1)];
+    for (int k = 0; k < PC; ++k) ep[k] = a.epos[min(c0 + t + k * NTS, m - 1)];
   }
-  // pairs of consecutive A positions aligned to 2, consecutive pairs on
-  // consecutive lanes (one 4-byte load of their cell indices and one 16-byte
-  // load of their gradients, coalesced); positions outside the range are
-  // skipped (the loads of a straddling pair stay inside the allocations)
-  const int g0 = a0 >> 1, g1 = (a1 + 1) >> 1;
-  const uint32_t* lc2 = reinterpret_cast<const uint32_t*>(lc);
-  const float4* T2 = reinterpret_cast<const float4*>(T);
-  constexpr int U = 4, STEP = U * kSumThreads;
-  // two groups of U pairs per thread in flight: the next group's loads are
-  // issued before the current group's adds
-  uint32_t q[U], qn[U];
-  float4 v[U], vn[U];
-  auto fetch = [&](uint32_t (&qq)[U], float4 (&vv)[U], int g) {
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int gg = min(g + k * kSumThreads, g1 - 1);
-      qq[k] = lc2[gg];
-      vv[k] = T2[gg];
-    }
-  };
-  int g = g0 + t;
-  if (g < g1) fetch(q, v, g);
-  for (int c = t; c < kXchCells; c += kSumThreads) {
+  PinSums<NTS, CELLS> pins;
+  pins.prefetch(lc, T, a0, a1);
+  for (int c = t; c < CELLS; c += NTS) {
     ax[c] = 0ull;
     ay[c] = 0ull;
     bad[c] = 0;
   }
   __syncthreads();
-  for (; g < g1; g += STEP) {
-    if (g + STEP < g1) fetch(qn, vn, g + STEP);
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int gg = g + k * kSumThreads;
-      if (gg >= g1) continue;
-      const int a = gg * 2;
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        if (a + e < a0 || a + e >= a1) continue;
-        const int l = min((int)(e ? q[k] >> 16 : q[k] & 0xffffu), kXchCells - 1);
-        const float gxv = e ? v[k].z : v[k].x, gyv = e ? v[k].w : v[k].y;
-        if (fabsf(gxv) <= 3.0e38f && fabsf(gyv) <= 3.0e38f) {
-          atomicAdd(&ax[l], (unsigned long long)(long long)__float2int_rn(gxv * scale));
-          atomicAdd(&ay[l], (unsigned long long)(long long)__float2int_rn(gyv * scale));
-        } else {
-          bad[l] = 1;
-        }
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      q[k] = qn[k];
-      v[k] = vn[k];
-    }
-  }
+  pins.add(scale, ax, ay, bad);
   __syncthreads();
   // each cell's gradient: its density part from its first-band entry (one
   // 8-byte read; all of a thread's reads issued together) or, for a cell
@@ -875,19 +526,18 @@ __global__ void __launch_bounds__(kSumThreads) k_xch_cellsum(SumBatch<NB> sb) {
   } else if (a.accumulate) {
 #pragma unroll
     for (int k = 0; k < PC; ++k) {
-      const int ci = min(c0 + t + k * kSumThreads, m - 1);
+      const int ci = min(c0 + t + k * NTS, m - 1);
       d[k] = make_float2(a.gx[ci], a.gy[ci]);
     }
   }
 #pragma unroll
   for (int k = 0; k < PC; ++k) {
-    const int c = t + k * kSumThreads, ci = c0 + c;
+    const int c = t + k * NTS, ci = c0 + c;
     if (c >= cpb || ci >= m) break;
     if (DENS && ep[k] < 0)
       d[k] = cell_density_grad<MODE, true>(a.g, a.x[ci], a.y[ci], a.w[ci], a.h[ci], nullptr,
                                            nullptr, a.exy, a.psi);
-    const float sx = bad[c] ? __builtin_nanf("") : (float)((double)(long long)ax[c] * inv_scale);
-    const float sy = bad[c] ? __builtin_nanf("") : (float)((double)(long long)ay[c] * inv_scale);
+    const float sx = pin_sum(ax[c], bad[c], inv_scale), sy = pin_sum(ay[c], bad[c], inv_scale);
     if (DENS) {
       a.gx[ci] = lam * d[k].x + sx;
       a.gy[ci] = lam * d[k].y + sy;
@@ -901,7 +551,7 @@ __global__ void __launch_bounds__(kSumThreads) k_xch_cellsum(SumBatch<NB> sb) {
   }
   if (cb == a.fin_block) {
     __syncthreads();
-    eval_scalars<kSumThreads>(a.fin);
+    eval_scalars<NTS>(a.fin);
   }
 }
 
@@ -931,37 +581,50 @@ SumReq sum_req(const XchDims& d, const XchIndex& X, const float2* T, const CellG
   return q;
 }
 
-template <int NB>
+template <int NB, int NTS, int CELLS>
 static hipError_t cellsum_nb(const SumBatch<NB>& sb, int max_ncb, int grad_mode, bool dens,
                              hipStream_t s) {
-  const dim3 grid(max_ncb, sb.count), block(kSumThreads);
+  const dim3 grid(max_ncb, sb.count), block(NTS);
   if (!dens)
-    hipLaunchKernelGGL((k_xch_cellsum<FFTPL_GRAD_FIELD, false, NB>), grid, block, 0, s, sb);
+    hipLaunchKernelGGL((k_xch_cellsum<FFTPL_GRAD_FIELD, false, NB, NTS, CELLS>), grid, block, 0,
+                       s, sb);
   else if (grad_mode == FFTPL_GRAD_EXACT)
-    hipLaunchKernelGGL((k_xch_cellsum<FFTPL_GRAD_EXACT, true, NB>), grid, block, 0, s, sb);
+    hipLaunchKernelGGL((k_xch_cellsum<FFTPL_GRAD_EXACT, true, NB, NTS, CELLS>), grid, block, 0,
+                       s, sb);
   else
-    hipLaunchKernelGGL((k_xch_cellsum<FFTPL_GRAD_FIELD, true, NB>), grid, block, 0, s, sb);
+    hipLaunchKernelGGL((k_xch_cellsum<FFTPL_GRAD_FIELD, true, NB, NTS, CELLS>), grid, block, 0,
+                       s, sb);
   return hipGetLastError();
+}
+
+template <int NB>
+static hipError_t cellsum_size(const SumBatch<NB>& sb, int max_ncb, int max_cpb, int grad_mode,
+                               bool dens, hipStream_t s) {
+  if (max_cpb <= kXchSmallCells)
+    return cellsum_nb<NB, 256, kXchSmallCells>(sb, max_ncb, grad_mode, dens, s);
+  return cellsum_nb<NB, kSumThreads, kXchCells>(sb, max_ncb, grad_mode, dens, s);
 }
 
 hipError_t launch_xch_cellsum_batch(const SumReq* reqs, int count, int grad_mode, bool dens,
                                     hipStream_t s) {
   if (count <= 0) return hipSuccess;
   if (count > kMaxBatch) return hipErrorInvalidValue;
-  int max_ncb = 0;
-  for (int i = 0; i < count; ++i)
+  int max_ncb = 0, max_cpb = 0;
+  for (int i = 0; i < count; ++i) {
     if (reqs[i].m > 0) max_ncb = std::max(max_ncb, reqs[i].ncb);
+    max_cpb = std::max(max_cpb, reqs[i].cpb);
+  }
   if (max_ncb == 0) return hipSuccess;
   if (count == 1) {
     SumBatch<1> sb;
     sb.count = 1;
     sb.r[0] = reqs[0];
-    return cellsum_nb(sb, max_ncb, grad_mode, dens, s);
+    return cellsum_size(sb, max_ncb, max_cpb, grad_mode, dens, s);
   }
   SumBatch<kMaxBatch> sb;
   sb.count = count;
   for (int i = 0; i < count; ++i) sb.r[i] = reqs[i];
-  return cellsum_nb(sb, max_ncb, grad_mode, dens, s);
+  return cellsum_size(sb, max_ncb, max_cpb, grad_mode, dens, s);
 }
 
 hipError_t launch_xch_cellsum(const XchDims& d, const XchIndex& X, const float2* T,
@@ -972,9 +635,10 @@ hipError_t launch_xch_cellsum(const XchDims& d, const XchIndex& X, const float2*
 }
 
 XchReq xch_req(const XchDims& d, const XchIndex& X, const float* x, const float* y, float2* T,
-               const int32_t* net_ptr, const float* pin_dx, const float* pin_dy, float gamma,
-               double* part) {
+               const int32_t* net_ptr, const int32_t* pin_cell, const float* pin_dx,
+               const float* pin_dy, float gamma, double* part) {
   XchReq q;
+  q.pin_cell = pin_cell;
   q.m = d.m;
   q.cpb = d.cpb;
   q.ncb = d.ncb;
@@ -1027,7 +691,7 @@ hipError_t launch_xch_spread_batch(const XchReq* reqs, int count, hipStream_t s)
 hipError_t launch_xch_spread(const XchDims& d, const XchIndex& X, const float* x,
                              const float* y, float2* T, hipStream_t s) {
   if (d.ncb <= 0) return hipSuccess;
-  const XchReq q = xch_req(d, X, x, y, T, nullptr, nullptr, nullptr, 1.0f, nullptr);
+  const XchReq q = xch_req(d, X, x, y, T, nullptr, nullptr, nullptr, nullptr, 1.0f, nullptr);
   return launch_xch_spread_batch(&q, 1, s);
 }
 
@@ -1051,51 +715,56 @@ static hipError_t allow_big_lds(K* kernel, std::atomic<bool>* flags) {
 }
 
 template <bool LSE, int NB>
-static hipError_t wa_nb(const XchBatch<NB>& xb, int max_nnb, int max_cap, hipStream_t s) {
+static hipError_t wa_nb(const XchBatch<NB>& xb, int max_nnb, int max_cap, bool direct,
+                        hipStream_t s) {
   const size_t lds = sizeof(float2) * 2 * (size_t)max_cap;
   const dim3 grid(max_nnb, xb.count);
-  if (max_cap <= kXchPinLds2) {
-    hipLaunchKernelGGL((k_xch_wa<kStageS, LSE, NB>), grid, dim3(NW), lds, s, xb);
+  if (direct) {
+    hipLaunchKernelGGL((k_xch_wa<kStageS, LSE, NB, true>), grid, dim3(NW), lds, s, xb);
+  } else if (max_cap <= kXchPinLds2) {
+    hipLaunchKernelGGL((k_xch_wa<kStageS, LSE, NB, false>), grid, dim3(NW), lds, s, xb);
   } else {
     static std::atomic<bool> attr[kMaxDevices];
-    const hipError_t e = allow_big_lds(&k_xch_wa<kStageL, LSE, NB>, attr);
+    const hipError_t e = allow_big_lds(&k_xch_wa<kStageL, LSE, NB, false>, attr);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_xch_wa<kStageL, LSE, NB>), grid, dim3(NW), lds, s, xb);
+    hipLaunchKernelGGL((k_xch_wa<kStageL, LSE, NB, false>), grid, dim3(NW), lds, s, xb);
   }
   return hipGetLastError();
 }
 
 template <bool LSE>
-static hipError_t wa_model(const XchReq* reqs, int count, hipStream_t s) {
+static hipError_t wa_model(const XchReq* reqs, int count, bool direct, hipStream_t s) {
   int max_nnb = 0, max_cap = 1;
   for (int i = 0; i < count; ++i) {
     max_nnb = std::max(max_nnb, reqs[i].nnb);
     max_cap = std::max(max_cap, reqs[i].cap);
   }
   if (max_nnb == 0) return hipSuccess;
+  if (direct && max_cap > kXchPinLds2) return hipErrorInvalidValue;
   if (count == 1) {
     XchBatch<1> xb;
     xb.count = 1;
     xb.r[0] = reqs[0];
-    return wa_nb<LSE, 1>(xb, max_nnb, max_cap, s);
+    return wa_nb<LSE, 1>(xb, max_nnb, max_cap, direct, s);
   }
   XchBatch<kMaxBatch> xb;
   xb.count = count;
   for (int i = 0; i < count; ++i) xb.r[i] = reqs[i];
-  return wa_nb<LSE, kMaxBatch>(xb, max_nnb, max_cap, s);
+  return wa_nb<LSE, kMaxBatch>(xb, max_nnb, max_cap, direct, s);
 }
 
-hipError_t launch_xch_wa_batch(const XchReq* reqs, int count, int wl_model, hipStream_t s) {
+hipError_t launch_xch_wa_batch(const XchReq* reqs, int count, int wl_model, hipStream_t s,
+                               bool direct) {
   if (count <= 0) return hipSuccess;
   if (count > kMaxBatch) return hipErrorInvalidValue;
-  return wl_model == FFTPL_WL_LSE ? wa_model<true>(reqs, count, s)
-                                  : wa_model<false>(reqs, count, s);
+  return wl_model == FFTPL_WL_LSE ? wa_model<true>(reqs, count, direct, s)
+                                  : wa_model<false>(reqs, count, direct, s);
 }
 
 hipError_t launch_xch_wa(const XchDims& d, const XchIndex& X, const int32_t* net_ptr,
                          const float* pin_dx, const float* pin_dy, float gamma, int wl_model,
                          float2* T, double* wa_part, hipStream_t s) {
-  const XchReq q = xch_req(d, X, nullptr, nullptr, T, net_ptr, pin_dx, pin_dy, gamma, wa_part);
+  const XchReq q = xch_req(d, X, nullptr, nullptr, T, net_ptr, nullptr, pin_dx, pin_dy, gamma, wa_part);
   return launch_xch_wa_batch(&q, 1, wl_model, s);
 }
 

@@ -162,6 +162,69 @@ __device__ __forceinline__ float2 density_grad_spans(const GridF& g, const Span&
   return make_float2(ax, ay);
 }
 
+// The same gradient from the interleaved map for the usual small cell, at most
+// three bins wide and two high (and, EXACT, inside the region): its six bins are
+// read together before any is used, where the loops above wait for each in
+// turn.  Other cells take the loops.  Same terms in the same order.
+template <int MODE>
+__device__ __forceinline__ float2 density_grad_small(const GridF& g, const Span& sx,
+                                                     const Span& sy,
+                                                     const float2* __restrict__ exy,
+                                                     const float* __restrict__ psi) {
+  const int n = g.n;
+  const float fn = (float)n;
+  const int nx = sx.i1 - sx.i0 + 1, ny = sy.i1 - sy.i0 + 1;
+  bool small = nx >= 1 && nx <= 3 && ny >= 1 && ny <= 2;
+  if (MODE == FFTPL_GRAD_EXACT)
+    small = small && sx.lo > 0.0f && sx.hi < fn && sy.lo > 0.0f && sy.hi < fn;
+  if (!small) return density_grad_spans<MODE, true>(g, sx, sy, nullptr, nullptr, exy, psi);
+  float2 e[2][3];
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      e[r][c] = exy[(int64_t)min(sy.i0 + r, sy.i1) * n + min(sx.i0 + c, sx.i1)];
+  float ax = 0.0f, ay = 0.0f;
+  if (MODE == FFTPL_GRAD_FIELD) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const float oy = span_overlap(sy, sy.i0 + r);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if (r < ny && c < nx) {
+          const float ov = span_overlap(sx, sx.i0 + c) * oy;
+          ax += ov * e[r][c].x;
+          ay += ov * e[r][c].y;
+        }
+      }
+    }
+    ax *= -g.inv_bw;
+    ay *= -g.inv_bh;
+  } else {
+    // the bins between the edges: columns i0 .. floor(hi) - 1, rows likewise
+    const int mx = (int)floorf(sx.hi) - sx.i0, my = (int)floorf(sy.hi) - sy.i0;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      float d = 0.0f;
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (c < mx) d += e[r][c].x;
+      if (r < ny) ax += span_overlap(sy, sy.i0 + r) * d;
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      float d = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        if (r < my) d += e[r][c].y;
+      if (c < nx) ay += span_overlap(sx, sx.i0 + c) * d;
+    }
+    ax *= 2.0f * g.inv_bw;
+    ay *= 2.0f * g.inv_bh;
+  }
+  return make_float2(ax, ay);
+}
+
 template <int MODE, bool INTERLEAVED>
 __device__ __forceinline__ float2 cell_density_grad(const GridF& g, float x, float y, float w,
                                                     float h, const float* __restrict__ ex,
@@ -291,6 +354,28 @@ __device__ __forceinline__ int wave_max_dpp_i(int v) {
   const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
   const int c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
   return max(max(a, b), max(c, d));
+}
+
+// The same for doubles: the sum over the wavefront, in a fixed order.
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)dpp_i<CTRL>((int)(uint32_t)b);
+  const uint32_t hi = (uint32_t)dpp_i<CTRL>((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double lane_d(double v, int lane) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum_dpp_d(double v) {
+  v += dpp_d<kDppRowRor8>(v);
+  v += dpp_d<kDppRowRor4>(v);
+  v += dpp_d<kDppQuad2301>(v);
+  v += dpp_d<kDppQuad1032>(v);
+  return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
 }
 
 // Order LDS accesses of one wavefront (all lanes) without a block barrier.
@@ -664,7 +749,10 @@ constexpr int kXchWaThreads = 512;     // threads of the net-block kernel
 constexpr int kXchPinCap = 9728;       // most pins of a net block (2 x 76 KiB of float2 in LDS)
 constexpr int kXchPinLds2 = 4864;      // pins of a net block that leave room for 2 blocks per CU
 constexpr int kXchPinTarget = 4096;    // most of npt, the least pins of a full net block
-constexpr int kXchMinTarget = 1024;
+constexpr int kXchMinTarget = 1024;    // least npt that very large nets may leave
+constexpr int kXchSmallTarget = 1024;  // least npt of a small netlist
+constexpr int kXchNetBlocks = kNumCus;   // net blocks a small netlist is spread over
+constexpr int kXchSmallCells = 1024;   // cells of a cell block that run in the small kernels
 constexpr int kXchBuckets = 20;        // degree classes of the net order: 0..8, then
                                        // 9-16, 17-32, ..., > 8192
 
@@ -750,6 +838,8 @@ struct XchReq {
   const uint32_t* nmeta = nullptr;
   const int32_t* a_of_b = nullptr;
   const uint16_t* lcsr = nullptr;
+  const int32_t* pin_cell = nullptr;   // direct reads (wa_block) only
+  const float2* xy = nullptr;          // direct reads: interleaved positions, if there are
   const float *pin_dx = nullptr, *pin_dy = nullptr;
   float gamma = 1.0f, inv_gamma = 1.0f;
   // if set, gamma is read on the device from dgamma[0] when the kernel runs
@@ -780,15 +870,50 @@ struct SumBatch {
   SumReq r[NB];
 };
 XchReq xch_req(const XchDims& d, const XchIndex& X, const float* x, const float* y, float2* T,
-               const int32_t* net_ptr, const float* pin_dx, const float* pin_dy, float gamma,
-               double* part);
+               const int32_t* net_ptr, const int32_t* pin_cell, const float* pin_dx,
+               const float* pin_dy, float gamma, double* part);
 SumReq sum_req(const XchDims& d, const XchIndex& X, const float2* T, const CellGradArgs& a);
 // count <= kMaxBatch designs per launch; the net blocks of one launch share
 // the wirelength model.  dens = false: the cell sums without density part.
 hipError_t launch_xch_spread_batch(const XchReq* reqs, int count, hipStream_t s);
-hipError_t launch_xch_wa_batch(const XchReq* reqs, int count, int wl_model, hipStream_t s);
+// direct: positions by pin_cell from x, y (no spread; cap <= kXchPinLds2)
+hipError_t launch_xch_wa_batch(const XchReq* reqs, int count, int wl_model, hipStream_t s,
+                               bool direct = false);
 hipError_t launch_xch_cellsum_batch(const SumReq* reqs, int count, int grad_mode, bool dens,
                                     hipStream_t s);
+
+// ---- compact evaluation (compact.hip) ---------------------------------------
+// One design: its scatter, net blocks, and (FFT plans) first row pass.
+struct CompactReq {
+  GridF g;
+  // the band lists of the place pass; nblk = 0: the band blocks read the cells
+  int m = 0, nblk = 0, rows = 0, nb = 0, cpk = 0, region = 0;
+  const float4* entries = nullptr;
+  const int32_t *big = nullptr, *blk_off = nullptr, *blk_cnt = nullptr;
+  const float *w = nullptr, *h = nullptr;
+  const float *base = nullptr, *cap = nullptr;
+  float* rho = nullptr;
+  float* bT = nullptr;
+  double *rowsum = nullptr, *tau_part = nullptr;
+  XchReq x;   // (x.x, x.y: the positions)
+};
+template <int NB>
+struct CompactBatch {
+  int count = 0, nb = 0;
+  CompactReq r[NB];
+};
+constexpr int kCompactMaxN = 512;       // largest grid: a row pair per band
+constexpr int kCompactMaxCpb = 2048;    // largest cell block
+constexpr int kCompactScanCells = 8192; // most cells read by every band block
+bool compact_design(int n, const XchDims& d);
+// scatter (and first row pass) beside the net blocks
+hipError_t launch_compact_mid(const Plan& p, const CompactReq* reqs, int count, int wl_model,
+                              bool fuse_rows, hipStream_t s);
+bool compact_fuses_rows(const Plan& p);
+// per-cell gradients: density part gathered per cell, pin sums, the scalars
+hipError_t launch_compact_cells(const SumReq* reqs, int count, int grad_mode, hipStream_t s);
+hipError_t launch_band_place_batch(const BandReq* reqs, int count, hipStream_t s);
+
 // ---- placement iteration (driver.hip) --------------------------------------
 size_t step_stats_work_doubles();
 hipError_t launch_step_stats(int m, const float* ux, const float* uy, const float* upx,
@@ -836,7 +961,9 @@ struct SpectralArgs {
 hipError_t spectral_fft(Plan& p, const SpectralArgs& a, hipStream_t s);
 // count designs (count <= the plan's max_batch, one difference mode): design
 // i uses batch slot i of the plan's intermediate maps; one launch per pass.
-hipError_t spectral_fft_batch(Plan& p, const SpectralArgs* a, int count, hipStream_t s);
+// rows = false: the row pass has run already (inside the compact scatter).
+hipError_t spectral_fft_batch(Plan& p, const SpectralArgs* a, int count, hipStream_t s,
+                              bool rows = true);
 
 // One design of a batched FFT solve: its maps and the plan slot it uses.
 struct SpecReq {
@@ -855,6 +982,7 @@ struct SpecBatch {
   int count = 0;
   SpecReq r[NB];
 };
+SpecReq spec_req(Plan& p, const SpectralArgs& a, int slot);
 hipError_t spectral_gemm(Plan& p, const SpectralArgs& a, hipStream_t s);
 int gemm_plan_init(Plan& p, hipStream_t s);   // returns fftpl_status
 void gemm_plan_free(Plan& p);

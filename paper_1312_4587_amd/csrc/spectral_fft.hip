@@ -32,231 +32,11 @@
 // transforms of a pass share the stages.  Each pass issues all its global
 // loads (rows and tables) before touching LDS, so a block waits on memory
 // once rather than once per loop trip.
-#include "fftpl_internal.hpp"
+#include "fft_device.hpp"
 
 namespace fftpl {
 
 namespace {
-
-constexpr int ilog2c(int v) { return v <= 1 ? 0 : 1 + ilog2c(v / 2); }
-
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-  return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
-// Position of sample i in the even/odd reordered sequence.
-template <int N>
-__device__ __forceinline__ int mk_pos(int i) {
-  return (i & 1) ? N - ((i + 1) >> 1) : (i >> 1);
-}
-
-// Threads per block for a length-N transform: one radix-4 butterfly per
-// thread and stage at N = 1024 (four wavefronts), never less than one
-// wavefront.
-template <int N>
-struct FftShape {
-  static constexpr int NT = N / 4 >= 256 ? 256 : (N / 4 >= kWave ? N / 4 : kWave);
-};
-
-template <int NT>
-__device__ __forceinline__ void block_lds_sync() {
-  if constexpr (NT > kWave)
-    __syncthreads();
-  else
-    wave_lds_sync();
-}
-
-// Unnormalised in-place DFTs of NB buffers of length N (b0..b{NB-1}) by a
-// block of NT threads.  The buffers go through the stages together, so one
-// barrier per stage serves all of them and each twiddle is read once for all.
-// INV selects exp(+).  tw[t] = exp(-2 pi i t / N).
-template <int N, int NT, bool INV, int NB>
-__device__ __forceinline__ void block_fft(float2* b0, float2* b1, float2* b2, float2* b3,
-                                          const float2* __restrict__ tw, int tid) {
-  float2* const bufs[4] = {b0, b1, b2, b3};
-  constexpr int LOG = ilog2c(N);
-  int ns = 1;
-  if constexpr (LOG & 1) {
-    constexpr int B = N / 2;
-    constexpr int PER = (B + NT - 1) / NT;
-    float2 v0[NB][PER], v1[NB][PER];
-#pragma unroll
-    for (int q = 0; q < NB; ++q)
-#pragma unroll
-      for (int t = 0; t < PER; ++t) {
-        const int j = tid + NT * t;
-        if (B % NT == 0 || j < B) {
-          v0[q][t] = bufs[q][j];
-          v1[q][t] = bufs[q][j + B];
-        }
-      }
-    block_lds_sync<NT>();
-#pragma unroll
-    for (int q = 0; q < NB; ++q)
-#pragma unroll
-      for (int t = 0; t < PER; ++t) {
-        const int j = tid + NT * t;
-        if (B % NT == 0 || j < B) {
-          bufs[q][2 * j] = make_float2(v0[q][t].x + v1[q][t].x, v0[q][t].y + v1[q][t].y);
-          bufs[q][2 * j + 1] = make_float2(v0[q][t].x - v1[q][t].x, v0[q][t].y - v1[q][t].y);
-        }
-      }
-    block_lds_sync<NT>();
-    ns = 2;
-  }
-  constexpr int B = N / 4;
-  constexpr int PER = (B + NT - 1) / NT;
-#pragma unroll
-  for (int st = 0; st < LOG / 2; ++st) {
-    float2 v[NB][PER][4];
-#pragma unroll
-    for (int q = 0; q < NB; ++q)
-#pragma unroll
-      for (int t = 0; t < PER; ++t) {
-        const int j = tid + NT * t;
-        if (B % NT == 0 || j < B) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v[q][t][r] = bufs[q][j + r * B];
-        }
-      }
-    block_lds_sync<NT>();
-    const int stride = N / (4 * ns);
-#pragma unroll
-    for (int t = 0; t < PER; ++t) {
-      const int j = tid + NT * t;
-      if (B % NT == 0 || j < B) {
-        const int k = j & (ns - 1);
-        float2 w[4];
-        if (ns > 1) {
-#pragma unroll
-          for (int r = 1; r < 4; ++r) {
-            w[r] = tw[k * r * stride];
-            if (INV) w[r].y = -w[r].y;
-          }
-        }
-        const int o = (j - k) * 4 + k;
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-          float2* u = v[q][t];
-          if (ns > 1) {
-#pragma unroll
-            for (int r = 1; r < 4; ++r) u[r] = cmul(u[r], w[r]);
-          }
-          const float2 t0 = make_float2(u[0].x + u[2].x, u[0].y + u[2].y);
-          const float2 t1 = make_float2(u[0].x - u[2].x, u[0].y - u[2].y);
-          const float2 t2 = make_float2(u[1].x + u[3].x, u[1].y + u[3].y);
-          const float2 d = make_float2(u[1].x - u[3].x, u[1].y - u[3].y);
-          // forward: t3 = -i * d ; inverse: t3 = +i * d
-          const float2 t3 = INV ? make_float2(-d.y, d.x) : make_float2(d.y, -d.x);
-          float2* b = bufs[q];
-          b[o] = make_float2(t0.x + t2.x, t0.y + t2.y);
-          b[o + ns] = make_float2(t1.x + t3.x, t1.y + t3.y);
-          b[o + 2 * ns] = make_float2(t0.x - t2.x, t0.y - t2.y);
-          b[o + 3 * ns] = make_float2(t1.x - t3.x, t1.y - t3.y);
-        }
-      }
-    }
-    block_lds_sync<NT>();
-    ns *= 4;
-  }
-}
-
-// Copy the twiddle table, the quarter-sample table cs and (WF) the frequency
-// table wf into LDS.  All global loads are issued before the first LDS write,
-// so the block waits on memory once; the caller synchronises.
-template <int N, int NT, bool WF>
-__device__ __forceinline__ void stage_tables(float2* tw, const float2* __restrict__ tw_g,
-                                             float2* cs, const float2* __restrict__ cs_g,
-                                             float* wf, const float* __restrict__ wf_g,
-                                             int tid) {
-  constexpr int PT = (N + NT - 1) / NT, PC = (N / 2 + NT) / NT;
-  float2 a[PT], c[PC];
-  float f[PT];
-#pragma unroll
-  for (int t = 0; t < PT; ++t) {
-    const int i = min(tid + NT * t, N - 1);
-    a[t] = tw_g[i];
-    if (WF) f[t] = wf_g[i];
-  }
-#pragma unroll
-  for (int t = 0; t < PC; ++t) c[t] = cs_g[min(tid + NT * t, N / 2)];
-#pragma unroll
-  for (int t = 0; t < PT; ++t) {
-    const int i = tid + NT * t;
-    if (N % NT == 0 || i < N) {
-      tw[i] = a[t];
-      if (WF) wf[i] = f[t];
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < PC; ++t) {
-    const int i = tid + NT * t;
-    if (i <= N / 2) cs[i] = c[t];
-  }
-}
-
-// Sums over the block of K per-thread doubles, added in a fixed order, so
-// every thread gets the same bits.  red holds K * NT / 64 doubles of LDS.
-template <int NT, int K>
-__device__ __forceinline__ void block_sums(double (&v)[K], double* red, int tid) {
-  constexpr int NW = NT / kWave;
-#pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
-  if constexpr (NW > 1) {
-    if ((tid & (kWave - 1)) == 0) {
-#pragma unroll
-      for (int k = 0; k < K; ++k) red[k * NW + tid / kWave] = v[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      double s = 0.0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) s += red[k * NW + w];
-      v[k] = s;
-    }
-  }
-}
-
-// Forward post-processing for the pair (k, n-k) of a two-real-sequence FFT
-// V = FFT(v1 + i v2): returns the DCT-II outputs X1, X2 at k and n-k.
-// cs = (cos, sin)(pi k / 2n).
-__device__ __forceinline__ void dct2_pair(float2 A, float2 B, float2 cs, float& x1k,
-                                          float& x2k, float& x1kp, float& x2kp) {
-  const float v1x = 0.5f * (A.x + B.x), v1y = 0.5f * (A.y - B.y);
-  const float v2x = 0.5f * (A.y + B.y), v2y = -0.5f * (A.x - B.x);
-  x1k = cs.x * v1x + cs.y * v1y;
-  x2k = cs.x * v2x + cs.y * v2y;
-  x1kp = cs.y * v1x - cs.x * v1y;
-  x2kp = cs.y * v2x - cs.x * v2y;
-}
-
-// Hermitian input of a DCT-III of real coefficients Y at the pair (k, n-k):
-// H_k = exp(i pi k / 2n) (Y_k - i Y_{n-k}) / 2, H_{n-k} = conj(H_k), H_0 = Y_0.
-__device__ __forceinline__ void dct3_herm(float yk, float ykp, float2 cs, bool k0,
-                                          float2& hk, float2& hkp) {
-  if (k0) {
-    hk = make_float2(yk, 0.0f);
-    hkp = hk;
-    return;
-  }
-  hk = make_float2(0.5f * (cs.x * yk + cs.y * ykp), 0.5f * (cs.y * yk - cs.x * ykp));
-  hkp = make_float2(hk.x, -hk.y);
-}
-
-// z = ha + i hb
-__device__ __forceinline__ float2 pack2(float2 ha, float2 hb) {
-  return make_float2(ha.x - hb.y, ha.y + hb.x);
-}
-
-// Difference-mode weights at the pair (k, n-k) from cs = (cos, sin)(pi k / 2n):
-// cos w_k - 1 = -2 sin^2(w_k / 2), cos w_{n-k} - 1 = -2 cos^2(w_k / 2),
-// sin w_k = sin w_{n-k} = 2 sin(w_k / 2) cos(w_k / 2).
-__device__ __forceinline__ void diff_weights(float2 cs, float& dm_k, float& dm_kp, float& sw) {
-  dm_k = -2.0f * cs.y * cs.y;
-  dm_kp = -2.0f * cs.x * cs.x;
-  sw = 2.0f * cs.y * cs.x;
-}
 
 // ---------------------------------------------------------------------------
 // Pass A: rows -> bT (transposed), row sums in double; optional overflow sums.
@@ -268,18 +48,13 @@ __global__ void __launch_bounds__(FftShape<N>::NT)
   // design blockIdx.y of the batch
   const SpecReq& rq = sb.r[blockIdx.y];
   const float* __restrict__ rho = rq.rho;
-  float* __restrict__ bT = rq.bT;
-  double* __restrict__ rowsum = rq.rowsum;
   const float* __restrict__ base = rq.base;
   const float* __restrict__ cap = rq.cap;
   const float rho_t = rq.rho_t;
   double* __restrict__ tau_part = rq.tau_part;
   constexpr int NT = FftShape<N>::NT;
-  constexpr int PER = (N + NT - 1) / NT, PK = (N / 2 + NT) / NT;
-  __shared__ float2 buf[N];
-  __shared__ float2 tw[N];
-  __shared__ float2 cs[N / 2 + 1];
-  __shared__ double red[4 * (NT / kWave)];
+  constexpr int PER = (N + NT - 1) / NT;
+  __shared__ RowsLds<N, NT> lds;
   const int tid = threadIdx.x;
   const int pair = xcd_block(blockIdx.x, gridDim.x);
   const int r1 = 2 * pair, r2 = r1 + 1;
@@ -316,54 +91,8 @@ __global__ void __launch_bounds__(FftShape<N>::NT)
       c2[t] = fmaxf(0.0f, rho_t - fminf(rho_t, b2[t]));
     }
   }
-  stage_tables<N, NT, false>(tw, tw_g, cs, cs_g, nullptr, nullptr, tid);
-  double s[4] = {0.0, 0.0, 0.0, 0.0};   // row sums r1, r2; overflow; movable
-#pragma unroll
-  for (int t = 0; t < PER; ++t) {
-    if (N % NT == 0 || tid + NT * t < N) {
-      s[0] += a1[t];
-      s[1] += a2[t];
-      if (tau_part) {
-        const float m1 = a1[t] - b1[t], m2 = a2[t] - b2[t];
-        s[2] += fmaxf(0.0f, m1 - c1[t]);
-        s[2] += fmaxf(0.0f, m2 - c2[t]);
-        s[3] += m1;
-        s[3] += m2;
-      }
-    }
-  }
-  block_sums<NT, 4>(s, red, tid);
-  if (tid == 0) {
-    rowsum[r1] = s[0];
-    rowsum[r2] = s[1];
-    if (tau_part) {
-      tau_part[2 * pair] = s[2];
-      tau_part[2 * pair + 1] = s[3];
-    }
-  }
-  const float m1 = (float)(s[0] / N), m2 = (float)(s[1] / N);
-#pragma unroll
-  for (int t = 0; t < PER; ++t) {
-    const int i = tid + NT * t;
-    if (N % NT == 0 || i < N) buf[mk_pos<N>(i)] = make_float2(a1[t] - m1, a2[t] - m2);
-  }
-  block_lds_sync<NT>();
-  block_fft<N, NT, false, 1>(buf, nullptr, nullptr, nullptr, tw, tid);
-#pragma unroll
-  for (int t = 0; t < PK; ++t) {
-    const int k = tid + NT * t;
-    if (k > N / 2) continue;
-    const int kp = (N - k) & (N - 1);
-    float x1k, x2k, x1kp, x2kp;
-    dct2_pair(buf[k], buf[kp], cs[k], x1k, x2k, x1kp, x2kp);
-    if (k == 0) {
-      x1k = (float)s[0];
-      x2k = (float)s[1];
-    }
-    *reinterpret_cast<float2*>(&bT[(int64_t)k * N + r1]) = make_float2(x1k, x2k);
-    if (k != 0 && k != N / 2)
-      *reinterpret_cast<float2*>(&bT[(int64_t)kp * N + r1]) = make_float2(x1kp, x2kp);
-  }
+  stage_tables<N, NT, false>(lds.tw, tw_g, lds.cs, cs_g, nullptr, nullptr, tid);
+  rows_dct2<N, NT>(a1, a2, b1, b2, c1, c2, r1, tid, lds, rq.bT, rq.rowsum, tau_part);
 }
 
 // ---------------------------------------------------------------------------
@@ -629,12 +358,14 @@ __global__ void __launch_bounds__(FftShape<N>::NT)
 }
 
 template <int N, int NB>
-hipError_t run_fft_nb(Plan& p, const SpecBatch<NB>& sb, bool diff, hipStream_t s) {
+hipError_t run_fft_nb(Plan& p, const SpecBatch<NB>& sb, bool diff, bool rows, hipStream_t s) {
   const dim3 grid(N / 2, sb.count), block(FftShape<N>::NT);
-  hipLaunchKernelGGL((k_rows_dct2<N, NB>), grid, block, 0, s, sb, p.fft_tw, p.dct_cs);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  plan_mark(p, "k_rows_dct2", s);
+  hipError_t e = hipSuccess;
+  if (rows) {
+    hipLaunchKernelGGL((k_rows_dct2<N, NB>), grid, block, 0, s, sb, p.fft_tw, p.dct_cs);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    plan_mark(p, "k_rows_dct2", s);
+  }
   if (diff)
     hipLaunchKernelGGL((k_cols_solve<N, true, NB>), grid, block, 0, s, sb, p.fft_tw, p.dct_cs,
                        p.wfreq);
@@ -653,6 +384,8 @@ hipError_t run_fft_nb(Plan& p, const SpecBatch<NB>& sb, bool diff, hipStream_t s
   plan_mark(p, "k_rows_inverse", s);
   return e;
 }
+
+}  // namespace
 
 // The descriptor of request a for the plan's batch slot `slot`.
 SpecReq spec_req(Plan& p, const SpectralArgs& a, int slot) {
@@ -676,36 +409,39 @@ SpecReq spec_req(Plan& p, const SpectralArgs& a, int slot) {
   return q;
 }
 
+namespace {
+
 template <int N>
-hipError_t run_fft(Plan& p, const SpectralArgs* a, int count, hipStream_t s) {
+hipError_t run_fft(Plan& p, const SpectralArgs* a, int count, bool rows, hipStream_t s) {
   if (count == 1) {
     SpecBatch<1> sb;
     sb.count = 1;
     sb.r[0] = spec_req(p, a[0], 0);
-    return run_fft_nb<N, 1>(p, sb, a[0].diff, s);
+    return run_fft_nb<N, 1>(p, sb, a[0].diff, rows, s);
   }
   SpecBatch<kMaxBatch> sb;
   sb.count = count;
   for (int i = 0; i < count; ++i) sb.r[i] = spec_req(p, a[i], i);
-  return run_fft_nb<N, kMaxBatch>(p, sb, a[0].diff, s);
+  return run_fft_nb<N, kMaxBatch>(p, sb, a[0].diff, rows, s);
 }
 
 }  // namespace
 
-hipError_t spectral_fft_batch(Plan& p, const SpectralArgs* a, int count, hipStream_t s) {
+hipError_t spectral_fft_batch(Plan& p, const SpectralArgs* a, int count, hipStream_t s,
+                              bool rows) {
   if (count <= 0) return hipSuccess;
   if (count > p.max_batch) return hipErrorInvalidValue;
   for (int i = 1; i < count; ++i)
     if (a[i].diff != a[0].diff) return hipErrorInvalidValue;
   switch (p.n) {
-    case 8: return run_fft<8>(p, a, count, s);
-    case 16: return run_fft<16>(p, a, count, s);
-    case 32: return run_fft<32>(p, a, count, s);
-    case 64: return run_fft<64>(p, a, count, s);
-    case 128: return run_fft<128>(p, a, count, s);
-    case 256: return run_fft<256>(p, a, count, s);
-    case 512: return run_fft<512>(p, a, count, s);
-    case 1024: return run_fft<1024>(p, a, count, s);
+    case 8: return run_fft<8>(p, a, count, rows, s);
+    case 16: return run_fft<16>(p, a, count, rows, s);
+    case 32: return run_fft<32>(p, a, count, rows, s);
+    case 64: return run_fft<64>(p, a, count, rows, s);
+    case 128: return run_fft<128>(p, a, count, rows, s);
+    case 256: return run_fft<256>(p, a, count, rows, s);
+    case 512: return run_fft<512>(p, a, count, rows, s);
+    case 1024: return run_fft<1024>(p, a, count, rows, s);
     default: return hipErrorInvalidValue;
   }
 }

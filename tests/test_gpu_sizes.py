@@ -39,3 +39,96 @@ def test_density_map_block_sizes(F, m, n):
     F.density_map(grid, c.x, c.y, c.w, c.h, base, rho)
     torch.cuda.synchronize()
     assert rel_l2(host(rho).reshape(n, n), oracle.density_map(inst, b0)) < RTOL
+
+
+def _eval(F, inst, mode, dct="fft", shift=0, **prob_kw):
+    """One evaluation with the positions `shift` floats into a larger array."""
+    import torch
+    prob = F.Problem.from_instance(inst, **prob_kw)
+    plan = F.Plan(inst.n, dct)
+    m = inst.num_cells
+    x, y, gx, gy = (torch.zeros(m + shift, device="cuda")[shift:] for _ in range(4))
+    x.copy_(torch.as_tensor(inst.x))
+    y.copy_(torch.as_tensor(inst.y))
+    out = torch.empty(4, dtype=torch.float64, device="cuda")
+    F.eval(plan, prob, x, y, 1.5, inst.gamma, mode, gx, gy, out)
+    only = torch.empty(4, dtype=torch.float64, device="cuda")
+    F.eval(plan, prob, x, y, 1.5, inst.gamma, mode, None, None, only)
+    torch.cuda.synchronize()
+    got = dict(gx=host(gx), gy=host(gy), out=host(out), only=host(only),
+               rho=host(plan.maps()[0]))
+    plan.close()
+    return got
+
+
+def _check(inst, got, mode, **kw):
+    ref = oracle.evaluate(inst, lam=1.5, grad_mode=mode, **kw)
+    assert rel_l2(got["rho"], ref["rho"]) < RTOL
+    assert rel_l2(got["gx"], ref["gx"]) < RTOL and rel_l2(got["gy"], ref["gy"]) < RTOL
+    for o in (got["out"], got["only"]):
+        for k, name in enumerate(("energy", "wa", "hpwl")):
+            assert abs(o[k] - ref[name]) <= RTOL * abs(ref[name])
+        assert abs(o[3] - ref["overflow"]) < RTOL
+
+
+# the compact evaluation's forms: cells read by every band block up to 8192,
+# then a place pass; row transforms fused from n = 64; cell blocks of up to
+# 2048 cells (524,288 cells), past them and past its grids the general path
+@pytest.mark.parametrize("m,n,mode", [
+    (1, 8, "field"), (257, 16, "exact"), (1000, 32, "field"), (4097, 64, "field"),
+    (8192, 128, "exact"), (8193, 128, "field"), (40000, 256, "exact"), (131073, 512, "field"),
+    (262145, 512, "field"), (524288, 512, "exact"), (524289, 512, "field"),
+    (300000, 1024, "field")])
+def test_eval_sizes(F, m, n, mode):
+    inst = gen.make_instance((93, m, n), num_cells=m, util=0.7, n=n,
+                             num_nets=int(1.1 * m) if m > 9 else 0, num_macros=3,
+                             macro_area_frac=0.1)
+    say("eval", m, n, mode)
+    _check(inst, _eval(F, inst, mode, shift=1), mode)
+
+
+# net blocks at their size rules: one staging round, several, the largest that
+# two share a CU, and past it (the general path); pins above 2,048 per block
+@pytest.mark.parametrize("hi", [900, 1100, 3000, 4700])
+def test_eval_net_block_sizes(F, hi):
+    inst = gen.make_instance((94, hi), num_cells=20000, util=0.7, n=128, num_nets=21000,
+                             hi_frac=0.003, hi_range=(hi, hi))
+    say("eval, nets of", hi)
+    for wl in ("wa", "lse"):
+        _check(inst, _eval(F, inst, "field", wl_model=wl), "field", wl_model=wl)
+
+
+def test_eval_sizes_with_matrix_cores(F):
+    # scatter and net blocks in one launch, the solve on the matrix cores
+    for m, n in ((9000, 192), (5000, 128)):
+        inst = gen.make_instance((95, m), num_cells=m, util=0.7, n=n, num_nets=m)
+        for mode in ("field", "exact"):
+            say("eval gemm_f32", m, n, mode)
+            _check(inst, _eval(F, inst, mode, dct="gemm_f32"), mode)
+
+
+def test_batch_mixes_size_classes(F):
+    # one call with designs read by the band blocks, placed first, and on the
+    # general path (nets too large for the compact form): each equals its own
+    # single evaluation
+    import torch
+    sizes = [(3000, 8), (8192, 8), (8193, 8), (15000, 4800), (12000, 8)]
+    insts = [gen.make_instance((96, k), num_cells=m, util=0.7, n=128, num_nets=m,
+                               hi_frac=0.001 if d > 8 else 0.0, hi_range=(d, d))
+             for k, (m, d) in enumerate(sizes)]
+    probs = [F.Problem.from_instance(i) for i in insts]
+    cells = [DeviceCells(i) for i in insts]
+    plan, single = F.Plan(128, max_batch=8), F.Plan(128)
+    gxs, gys = ([torch.empty(i.num_cells, device="cuda") for i in insts] for _ in range(2))
+    out = torch.empty((len(insts), 4), dtype=torch.float64, device="cuda")
+    F.eval_batch(plan, probs, [c.x for c in cells], [c.y for c in cells], [2.0] * len(insts),
+                 [i.gamma for i in insts], "field", gxs, gys, out)
+    for k, i in enumerate(insts):
+        gx, gy = (torch.empty(i.num_cells, device="cuda") for _ in range(2))
+        o4 = torch.empty(4, dtype=torch.float64, device="cuda")
+        F.eval(single, probs[k], cells[k].x, cells[k].y, 2.0, i.gamma, "field", gx, gy, o4)
+        torch.cuda.synchronize()
+        assert torch.equal(gx, gxs[k]) and torch.equal(gy, gys[k])
+        assert torch.allclose(o4, out[k], rtol=1e-12, atol=0.0)
+    plan.close()
+    single.close()
