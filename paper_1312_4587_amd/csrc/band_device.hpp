@@ -7,6 +7,96 @@
 
 namespace fftpl {
 
+template <int CB>
+struct CellBatch {
+  float x[CB], y[CB], w[CB], h[CB];
+};
+
+template <int CB>
+__device__ __forceinline__ void load_batch(CellBatch<CB>& c, int base, int m,
+                                           const float* __restrict__ x,
+                                           const float* __restrict__ y,
+                                           const float* __restrict__ w,
+                                           const float* __restrict__ h) {
+  // unconditional (index clamped, m >= 1) so the whole batch is in flight
+#pragma unroll
+  for (int j = 0; j < CB; ++j) {
+    const int i = min(base + j * kBandThreads + (int)threadIdx.x, m - 1);
+    c.x[j] = x[i];
+    c.y[j] = y[i];
+    c.w[j] = w[i];
+    c.h[j] = h[i];
+  }
+}
+
+// Counting block k of the scatter: sorts its cells' edges by band into its own
+// region.  LT: BandLayout, or a request with its fields.
+template <int CB, typename LT>
+__device__ __forceinline__ void place_block(const GridF& g, const LT& L, int k,
+                                            const float* __restrict__ x,
+                                            const float* __restrict__ y,
+                                            const float* __restrict__ w,
+                                            const float* __restrict__ h) {
+  constexpr int NT = kBandThreads;
+  const int t = threadIdx.x;
+  __shared__ int hist[257], cur[257];   // the bands, then the tall cells
+  for (int b = t; b <= L.nb; b += NT) hist[b] = 0;
+  __syncthreads();
+  const int c0 = k * L.cpk, c1 = min(L.m, c0 + L.cpk);   // one batch of cells per thread
+  CellBatch<CB> c;
+  load_batch(c, c0, L.m, x, y, w, h);
+  float4 e[CB];
+  int b0[CB], nbd[CB];   // first band, bands listed (0: none, -1: tall)
+#pragma unroll
+  for (int j = 0; j < CB; ++j) {
+    const int i = c0 + j * NT + t;
+    nbd[j] = 0;
+    b0[j] = 0;
+    if (i >= c1) continue;
+    if (L.xy) L.xy[i] = make_float2(c.x[j], c.y[j]);
+    const Span sx = cell_span(c.x[j], c.w[j], g.xl, g.inv_bw, g.n);
+    const Span sy = cell_span(c.y[j], c.h[j], g.yl, g.inv_bh, g.n);
+    if (sx.i0 > sx.i1 || sy.i0 > sy.i1) continue;
+    b0[j] = sy.i0 / L.rows;
+    const int b1 = sy.i1 / L.rows;
+    e[j] = make_float4(sx.lo, sx.hi, sy.lo, sy.hi);
+    if (b1 - b0[j] >= kMaxBands) {
+      nbd[j] = -1;
+      atomicAdd(&hist[L.nb], 1);
+    } else {
+      nbd[j] = b1 - b0[j] + 1;
+      for (int b = b0[j]; b <= b1; ++b) atomicAdd(&hist[b], 1);
+    }
+  }
+  __syncthreads();
+  int tot;
+  const int ex = block_exclusive_scan<NT>(t < L.nb ? hist[t] : 0, &tot);
+  if (t <= L.nb) {
+    const int off = t < L.nb ? ex : 0;   // the tall cells have a list of their own
+    L.blk_off[(size_t)t * L.nblk + k] = off;
+    L.blk_cnt[(size_t)t * L.nblk + k] = hist[t];
+    cur[t] = off;
+  }
+  __syncthreads();
+  const int64_t rbase = (int64_t)k * L.region;
+#pragma unroll
+  for (int j = 0; j < CB; ++j) {
+    const int i = c0 + j * NT + t;
+    if (i >= c1) continue;
+    int first = -1;   // the cell's entry in its first band, if listed
+    if (nbd[j] > 0) {
+      for (int b = b0[j]; b < b0[j] + nbd[j]; ++b) {
+        const int q = atomicAdd(&cur[b], 1);
+        L.entries[rbase + q] = e[j];
+        if (b == b0[j]) first = (int)(rbase + q);
+      }
+    } else if (nbd[j] < 0) {
+      L.big[(int64_t)k * L.cpk + atomicAdd(&cur[L.nb], 1)] = i;
+    }
+    if (L.epos) L.epos[i] = first;
+  }
+}
+
 // The entries of band `band` (band = nb: the tall cells) lie in one slice per
 // region: slice k holds blk_cnt[band][k] entries from index
 // k * stride + blk_off[band][k].  A block of NTB threads walks them in chunks
@@ -74,7 +164,7 @@ __device__ __forceinline__ void add_fixed(unsigned long long* a, float v) {
 }
 
 // The overlaps of one cell with rows r0 .. r0 + R - 1.
-__device__ __forceinline__ void add_span(const Span& sx, const Span& sy, int r0, int R, int n,
+__device__ __forceinline__ void add_span_rows(const Span& sx, const Span& sy, int r0, int R, int n,
                                          unsigned long long* acc) {
   const int ya = max(sy.i0, r0), yb = min(sy.i1, r0 + R - 1);
   for (int iy = ya; iy <= yb; ++iy) {
@@ -116,7 +206,7 @@ __device__ __forceinline__ bool add_short_slices(const LT& L, int band, int r0, 
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (l + (j0 + j) * lanes < c)
-        add_span(span_from_edges(q[j].x, q[j].y, n), span_from_edges(q[j].z, q[j].w, n), r0,
+        add_span_rows(span_from_edges(q[j].x, q[j].y, n), span_from_edges(q[j].z, q[j].w, n), r0,
                  L.rows, n, acc);
   }
   return true;
@@ -153,15 +243,95 @@ __device__ __forceinline__ void band_accumulate(const GridF& g, const LT& L, int
       if (idx[j] < 0) continue;
       const Span sx = span_from_edges(q[j].x, q[j].y, n);
       const Span sy = span_from_edges(q[j].z, q[j].w, n);
-      add_span(sx, sy, r0, R, n, acc);
+      add_span_rows(sx, sy, r0, R, n, acc);
     }
   });
   walk_band<NTB, 1>(L, L.nb, L.cpk, lds.pre, lds.start, lds.owner, [&](const int64_t (&idx)[1]) {
     if (idx[0] < 0) return;
     const int i = L.big[idx[0]];
-    add_span(cell_span(x[i], w[i], g.xl, g.inv_bw, n), cell_span(y[i], h[i], g.yl, g.inv_bh, n),
+    add_span_rows(cell_span(x[i], w[i], g.xl, g.inv_bw, n), cell_span(y[i], h[i], g.yl, g.inv_bh, n),
              r0, R, n, acc);
   });
+}
+
+// The same; the usual cell, at most three bins wide in at most two of the
+// band's rows, takes straight-line code (the same products in the same order).
+__device__ __forceinline__ void add_span(const Span& sx, const Span& sy, int r0, int R, int n,
+                                         unsigned long long* acc) {
+  const int ya = max(sy.i0, r0), yb = min(sy.i1, r0 + R - 1);
+  const int nx = sx.i1 - sx.i0 + 1, ny = yb - ya + 1;
+  if (nx <= 0 || ny <= 0) return;
+  if (nx <= 3 && ny <= 2) {
+    const float o0 = span_overlap(sx, sx.i0), o1 = span_overlap(sx, sx.i0 + 1),
+                o2 = span_overlap(sx, sx.i0 + 2);
+    unsigned long long* row = acc + (ya - r0) * n + sx.i0;
+    float oy = span_overlap(sy, ya);
+    add_fixed(row, o0 * oy);
+    if (nx > 1) add_fixed(row + 1, o1 * oy);
+    if (nx > 2) add_fixed(row + 2, o2 * oy);
+    if (ny > 1) {
+      oy = span_overlap(sy, ya + 1);
+      row += n;
+      add_fixed(row, o0 * oy);
+      if (nx > 1) add_fixed(row + 1, o1 * oy);
+      if (nx > 2) add_fixed(row + 2, o2 * oy);
+    }
+    return;
+  }
+  add_span_rows(sx, sy, r0, R, n, acc);
+}
+
+// LDS of a band block of NTB threads that reads a small design's cells itself:
+// the cells that meet the band go to a list, which all threads drain together.
+// Few cells meet a band (90 of 2000 at n = 64); handled where they are found,
+// each would hold up its wavefront alone.  k_compact_mid at 2k cells 9.4 ->
+// 7.7 us.
+template <int NTB, int CAP>
+struct ScanLds {
+  float4 list[CAP];
+  int count;
+};
+
+// Adds a small design's cells straight from their arrays (no entries).
+template <int NTB, int CAP, typename LT>
+__device__ __forceinline__ void band_scan(const GridF& g, const LT& L, int band,
+                                          const float* __restrict__ x,
+                                          const float* __restrict__ y,
+                                          const float* __restrict__ w,
+                                          const float* __restrict__ h, unsigned long long* acc,
+                                          ScanLds<NTB, CAP>& lds) {
+  constexpr int U = CAP / NTB;
+  const int n = g.n, R = L.rows, r0 = band * R, t = threadIdx.x, m = L.m;
+#pragma unroll 1
+  for (int i0 = 0; i0 < m; i0 += CAP) {
+    float cx[U], cy[U], cw[U], ch[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + t + u * NTB, m - 1);
+      cx[u] = x[i];
+      cy[u] = y[i];
+      cw[u] = w[i];
+      ch[u] = h[i];
+    }
+    if (t == 0) lds.count = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + t + u * NTB >= m) continue;
+      const Span sy = cell_span(cy[u], ch[u], g.yl, g.inv_bh, n);
+      if (sy.i1 < r0 || sy.i0 >= r0 + R || sy.i0 > sy.i1) continue;
+      const Span sx = cell_span(cx[u], cw[u], g.xl, g.inv_bw, n);
+      lds.list[atomicAdd(&lds.count, 1)] = make_float4(sx.lo, sx.hi, sy.lo, sy.hi);
+    }
+    __syncthreads();
+    const int count = lds.count;
+#pragma unroll 1
+    for (int i = t; i < count; i += NTB) {
+      const float4 q = lds.list[i];
+      add_span(span_from_edges(q.x, q.y, n), span_from_edges(q.z, q.w, n), r0, R, n, acc);
+    }
+    __syncthreads();
+  }
 }
 
 }  // namespace fftpl

@@ -100,28 +100,6 @@ namespace {
 constexpr int NT = kBandThreads;
 constexpr int B = kCellBatch;   // entries a thread of a band walk takes together
 
-template <int CB>
-struct CellBatch {
-  float x[CB], y[CB], w[CB], h[CB];
-};
-
-template <int CB>
-__device__ __forceinline__ void load_batch(CellBatch<CB>& c, int base, int m,
-                                           const float* __restrict__ x,
-                                           const float* __restrict__ y,
-                                           const float* __restrict__ w,
-                                           const float* __restrict__ h) {
-  // unconditional (index clamped, m >= 1) so the whole batch is in flight
-#pragma unroll
-  for (int j = 0; j < CB; ++j) {
-    const int i = min(base + j * NT + (int)threadIdx.x, m - 1);
-    c.x[j] = x[i];
-    c.y[j] = y[i];
-    c.w[j] = w[i];
-    c.h[j] = h[i];
-  }
-}
-
 }  // namespace
 
 // CB: the most cells per thread among the batch's designs (a design with fewer
@@ -130,70 +108,8 @@ template <int NB, int CB>
 __global__ void __launch_bounds__(kBandThreads) k_band_place(BandBatch<NB> bb) {
   // design blockIdx.y of the batch; blocks past its count of cell blocks idle
   const BandReq& q = bb.r[blockIdx.y];
-  const GridF g = q.g;
-  const BandLayout L = q.L;
-  const int t = threadIdx.x, k = blockIdx.x;
-  if (L.m <= 0 || k >= L.nblk) return;
-  const float* __restrict__ x = q.x;
-  const float* __restrict__ y = q.y;
-  const float* __restrict__ w = q.w;
-  const float* __restrict__ h = q.h;
-  __shared__ int hist[257], cur[257];   // the bands, then the tall cells
-  for (int b = t; b <= L.nb; b += NT) hist[b] = 0;
-  __syncthreads();
-  const int c0 = k * L.cpk, c1 = min(L.m, c0 + L.cpk);   // one batch of cells per thread
-  CellBatch<CB> c;
-  load_batch(c, c0, L.m, x, y, w, h);
-  float4 e[CB];
-  int b0[CB], nbd[CB];   // first band, bands listed (0: none, -1: tall)
-#pragma unroll
-  for (int j = 0; j < CB; ++j) {
-    const int i = c0 + j * NT + t;
-    nbd[j] = 0;
-    b0[j] = 0;
-    if (i >= c1) continue;
-    if (L.xy) L.xy[i] = make_float2(c.x[j], c.y[j]);
-    const Span sx = cell_span(c.x[j], c.w[j], g.xl, g.inv_bw, g.n);
-    const Span sy = cell_span(c.y[j], c.h[j], g.yl, g.inv_bh, g.n);
-    if (sx.i0 > sx.i1 || sy.i0 > sy.i1) continue;
-    b0[j] = sy.i0 / L.rows;
-    const int b1 = sy.i1 / L.rows;
-    e[j] = make_float4(sx.lo, sx.hi, sy.lo, sy.hi);
-    if (b1 - b0[j] >= kMaxBands) {
-      nbd[j] = -1;
-      atomicAdd(&hist[L.nb], 1);
-    } else {
-      nbd[j] = b1 - b0[j] + 1;
-      for (int b = b0[j]; b <= b1; ++b) atomicAdd(&hist[b], 1);
-    }
-  }
-  __syncthreads();
-  int tot;
-  const int ex = block_exclusive_scan<NT>(t < L.nb ? hist[t] : 0, &tot);
-  if (t <= L.nb) {
-    const int off = t < L.nb ? ex : 0;   // the tall cells have a list of their own
-    L.blk_off[(size_t)t * L.nblk + k] = off;
-    L.blk_cnt[(size_t)t * L.nblk + k] = hist[t];
-    cur[t] = off;
-  }
-  __syncthreads();
-  const int64_t rbase = (int64_t)k * L.region;
-#pragma unroll
-  for (int j = 0; j < CB; ++j) {
-    const int i = c0 + j * NT + t;
-    if (i >= c1) continue;
-    int first = -1;   // the cell's entry in its first band, if listed
-    if (nbd[j] > 0) {
-      for (int b = b0[j]; b < b0[j] + nbd[j]; ++b) {
-        const int q = atomicAdd(&cur[b], 1);
-        L.entries[rbase + q] = e[j];
-        if (b == b0[j]) first = (int)(rbase + q);
-      }
-    } else if (nbd[j] < 0) {
-      L.big[(int64_t)k * L.cpk + atomicAdd(&cur[L.nb], 1)] = i;
-    }
-    if (L.epos) L.epos[i] = first;
-  }
+  if (q.L.m <= 0 || (int)blockIdx.x >= q.L.nblk) return;
+  place_block<CB>(q.g, q.L, blockIdx.x, q.x, q.y, q.w, q.h);
 }
 
 // NTA threads taking KB entries each, at most BINS bins per band: (1024, 8,

@@ -36,42 +36,17 @@ namespace {
 
 constexpr int NT = kXchWaThreads;   // the net blocks' threads, and the band blocks'
 constexpr int KB = 4;               // band entries a thread takes together
+constexpr int kList = 4 * NT;       // cells of a scanning band block's list
 constexpr int kBins = 2 * kCompactMaxN;
-constexpr int kCellThreads = 512;   // threads of a block of the cells kernel
 
-// Cells of a small design straight from their arrays, for one band.
-__device__ __forceinline__ void scan_cells(const CompactReq& q, int r0, int R,
-                                           unsigned long long* acc) {
-  constexpr int U = 4;
-  const GridF& g = q.g;
-  const int n = g.n, m = q.m;
-  for (int i0 = threadIdx.x; i0 < m; i0 += U * NT) {
-    float x[U], y[U], w[U], h[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = min(i0 + u * NT, m - 1);
-      x[u] = q.x.x[i];
-      y[u] = q.x.y[i];
-      w[u] = q.w[i];
-      h[u] = q.h[i];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (i0 + u * NT >= m) continue;
-      const Span sy = cell_span(y[u], h[u], g.yl, g.inv_bh, n);
-      if (sy.i1 < r0 || sy.i0 >= r0 + R || sy.i0 > sy.i1) continue;
-      add_span(cell_span(x[u], w[u], g.xl, g.inv_bw, n), sy, r0, R, n, acc);
-    }
-  }
-}
-
-// LDS of a band block: the accumulators, then the walk's arrays or the row
-// transform's (N = 0: no transform).
+// LDS of a band block: the accumulators, then the scatter's arrays or the
+// row transform's (N = 0: no transform).
 template <int N>
 struct MidLds {
   unsigned long long acc[kBins];
   union {
     WalkLds<NT, KB> walk;
+    ScanLds<NT, kList> scan;
     RowsLds<N ? N : 8, NT> rows;
   };
 };
@@ -115,7 +90,7 @@ __global__ void __launch_bounds__(NT, 6) k_compact_mid(CompactBatch<NB> cb,
   if (q.nblk > 0)
     band_accumulate<NT, KB, true>(g, q, band, q.x.x, q.x.y, q.w, q.h, lds.acc, lds.walk);
   else
-    scan_cells(q, r0, R, lds.acc);
+    band_scan<NT, kList>(g, q, band, q.x.x, q.x.y, q.w, q.h, lds.acc, lds.scan);
   __syncthreads();
   float rho[PA];
 #pragma unroll
@@ -163,35 +138,39 @@ __global__ void __launch_bounds__(NT, 6) k_compact_mid(CompactBatch<NB> cb,
   }
 }
 
-template <int MODE, int NB>
-__global__ void __launch_bounds__(kCellThreads) k_compact_cells(SumBatch<NB> sb) {
+// TC threads, PC cells per thread: (256, 1), (512, 1), (512, 2) or (512, 4), the smallest
+// that holds a cell block.  A block of one cell per thread is a short chain of
+// loads, and its registers and LDS leave room for several blocks per CU (eight
+// designs of up to 62k cells 22.3 -> 17.1 us).
+template <int MODE, int NB, int TC, int PC>
+__global__ void __launch_bounds__(TC) k_compact_cells(SumBatch<NB> sb) {
   const SumReq& rq = sb.r[blockIdx.y];
   const int cb = blockIdx.x, t = threadIdx.x;
   const CellGradArgs& a = rq.a;
   if (cb >= rq.ncb) {
     // the block past the design's last cell block sums its scalars
-    if (cb == rq.ncb) eval_scalars<kCellThreads>(a.fin);
+    if (cb == rq.ncb) eval_scalars<TC>(a.fin);
     return;
   }
-  constexpr int PC = kCompactMaxCpb / kCellThreads;
-  __shared__ unsigned long long ax[kCompactMaxCpb], ay[kCompactMaxCpb];
-  __shared__ unsigned char bad[kCompactMaxCpb];
+  constexpr int CELLS = TC * PC;
+  __shared__ unsigned long long ax[CELLS], ay[CELLS];
+  __shared__ unsigned char bad[CELLS];
   const int m = rq.m, cpb = rq.cpb, c0 = cb * cpb;
   const int a0 = rq.cb_a_ptr[cb], a1 = rq.cb_a_ptr[cb + 1];
   float x[PC], y[PC], w[PC], h[PC];
 #pragma unroll
   for (int k = 0; k < PC; ++k) {
-    if (k * kCellThreads >= cpb) break;
-    const int ci = min(c0 + t + k * kCellThreads, m - 1);
+    if (k * TC >= cpb) break;
+    const int ci = min(c0 + t + k * TC, m - 1);
     x[k] = a.x[ci];
     y[k] = a.y[ci];
     w[k] = a.w[ci];
     h[k] = a.h[ci];
   }
   const float lam = a.dscale ? a.dscale[0] : a.scale;
-  PinSums<kCellThreads, kCompactMaxCpb> pins;
+  PinSums<TC, CELLS> pins;
   pins.prefetch(rq.lc, rq.T, a0, a1);
-  for (int c = t; c < cpb; c += kCellThreads) {
+  for (int c = t; c < cpb; c += TC) {
     ax[c] = 0ull;
     ay[c] = 0ull;
     bad[c] = 0;
@@ -200,7 +179,7 @@ __global__ void __launch_bounds__(kCellThreads) k_compact_cells(SumBatch<NB> sb)
   float2 d[PC];
 #pragma unroll
   for (int k = 0; k < PC; ++k) {
-    if (k * kCellThreads >= cpb) break;
+    if (k * TC >= cpb) break;
     const Span sx = cell_span(x[k], w[k], a.g.xl, a.g.inv_bw, a.g.n);
     const Span sy = cell_span(y[k], h[k], a.g.yl, a.g.inv_bh, a.g.n);
     d[k] = density_grad_small<MODE>(a.g, sx, sy, a.exy, a.psi);
@@ -210,7 +189,7 @@ __global__ void __launch_bounds__(kCellThreads) k_compact_cells(SumBatch<NB> sb)
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < PC; ++k) {
-    const int c = t + k * kCellThreads, ci = c0 + c;
+    const int c = t + k * TC, ci = c0 + c;
     if (c >= cpb || ci >= m) break;
     a.gx[ci] = lam * d[k].x + pin_sum(ax[c], bad[c], rq.inv_scale);
     a.gy[ci] = lam * d[k].y + pin_sum(ay[c], bad[c], rq.inv_scale);
@@ -219,9 +198,11 @@ __global__ void __launch_bounds__(kCellThreads) k_compact_cells(SumBatch<NB> sb)
 
 template <int N, bool LSE, int NB>
 hipError_t mid_launch(const Plan& p, const CompactBatch<NB>& cb, int max_nnb, int max_cap,
-                      hipStream_t s) {
-  const size_t wa = sizeof(float2) * 2 * (size_t)max_cap;
-  const size_t lds = std::max(wa, sizeof(MidLds<N>));
+                      bool scan, hipStream_t s) {
+  using L = MidLds<N>;
+  size_t lds = sizeof(L::acc) + std::max(sizeof(L::walk), sizeof(L::rows));
+  if (scan) lds = sizeof(L);
+  lds = std::max(lds, sizeof(float2) * 2 * (size_t)max_cap);
   hipLaunchKernelGGL((k_compact_mid<N, LSE, NB>), dim3(cb.nb + max_nnb, cb.count), dim3(NT), lds,
                      s, cb, p.fft_tw, p.dct_cs);
   return hipGetLastError();
@@ -229,13 +210,13 @@ hipError_t mid_launch(const Plan& p, const CompactBatch<NB>& cb, int max_nnb, in
 
 template <bool LSE, int NB>
 hipError_t mid_size(const Plan& p, const CompactBatch<NB>& cb, int max_nnb, int max_cap,
-                    bool fuse_rows, hipStream_t s) {
+                    bool scan, bool fuse_rows, hipStream_t s) {
   switch (fuse_rows ? p.n : 0) {
-    case 64: return mid_launch<64, LSE, NB>(p, cb, max_nnb, max_cap, s);
-    case 128: return mid_launch<128, LSE, NB>(p, cb, max_nnb, max_cap, s);
-    case 256: return mid_launch<256, LSE, NB>(p, cb, max_nnb, max_cap, s);
-    case 512: return mid_launch<512, LSE, NB>(p, cb, max_nnb, max_cap, s);
-    default: return mid_launch<0, LSE, NB>(p, cb, max_nnb, max_cap, s);
+    case 64: return mid_launch<64, LSE, NB>(p, cb, max_nnb, max_cap, scan, s);
+    case 128: return mid_launch<128, LSE, NB>(p, cb, max_nnb, max_cap, scan, s);
+    case 256: return mid_launch<256, LSE, NB>(p, cb, max_nnb, max_cap, scan, s);
+    case 512: return mid_launch<512, LSE, NB>(p, cb, max_nnb, max_cap, scan, s);
+    default: return mid_launch<0, LSE, NB>(p, cb, max_nnb, max_cap, scan, s);
   }
 }
 
@@ -246,28 +227,44 @@ hipError_t mid_batch(const Plan& p, const CompactReq* reqs, int count, int wl_mo
   cb.count = count;
   cb.nb = reqs[0].nb;
   int max_nnb = 0, max_cap = 1;
+  bool scan = false;
   for (int i = 0; i < count; ++i) {
     cb.r[i] = reqs[i];
     max_nnb = std::max(max_nnb, reqs[i].x.nnb);
     max_cap = std::max(max_cap, reqs[i].x.cap);
+    scan = scan || reqs[i].nblk == 0;
   }
   if (max_cap > kXchPinLds2) return hipErrorInvalidValue;
-  return wl_model == FFTPL_WL_LSE ? mid_size<true, NB>(p, cb, max_nnb, max_cap, fuse_rows, s)
-                                  : mid_size<false, NB>(p, cb, max_nnb, max_cap, fuse_rows, s);
+  return wl_model == FFTPL_WL_LSE
+             ? mid_size<true, NB>(p, cb, max_nnb, max_cap, scan, fuse_rows, s)
+             : mid_size<false, NB>(p, cb, max_nnb, max_cap, scan, fuse_rows, s);
+}
+
+template <int NB, int TC, int PC>
+hipError_t cells_launch(const SumBatch<NB>& sb, int max_ncb, int grad_mode, hipStream_t s) {
+  const dim3 grid(max_ncb + 1, sb.count), block(TC);
+  if (grad_mode == FFTPL_GRAD_EXACT)
+    hipLaunchKernelGGL((k_compact_cells<FFTPL_GRAD_EXACT, NB, TC, PC>), grid, block, 0, s, sb);
+  else
+    hipLaunchKernelGGL((k_compact_cells<FFTPL_GRAD_FIELD, NB, TC, PC>), grid, block, 0, s, sb);
+  return hipGetLastError();
 }
 
 template <int NB>
-hipError_t cells_batch(const SumReq* reqs, int count, int max_ncb, int grad_mode,
-                       hipStream_t s) {
+hipError_t cells_batch(const SumReq* reqs, int count, int grad_mode, hipStream_t s) {
   SumBatch<NB> sb;
   sb.count = count;
-  for (int i = 0; i < count; ++i) sb.r[i] = reqs[i];
-  const dim3 grid(max_ncb + 1, count), block(kCellThreads);
-  if (grad_mode == FFTPL_GRAD_EXACT)
-    hipLaunchKernelGGL((k_compact_cells<FFTPL_GRAD_EXACT, NB>), grid, block, 0, s, sb);
-  else
-    hipLaunchKernelGGL((k_compact_cells<FFTPL_GRAD_FIELD, NB>), grid, block, 0, s, sb);
-  return hipGetLastError();
+  int max_ncb = 0, max_cpb = 0;
+  for (int i = 0; i < count; ++i) {
+    sb.r[i] = reqs[i];
+    max_ncb = std::max(max_ncb, reqs[i].ncb);
+    max_cpb = std::max(max_cpb, reqs[i].cpb);
+  }
+  if (max_cpb > kCompactMaxCpb) return hipErrorInvalidValue;
+  if (max_cpb <= 256) return cells_launch<NB, 256, 1>(sb, max_ncb, grad_mode, s);
+  if (max_cpb <= 512) return cells_launch<NB, 512, 1>(sb, max_ncb, grad_mode, s);
+  if (max_cpb <= 1024) return cells_launch<NB, 512, 2>(sb, max_ncb, grad_mode, s);
+  return cells_launch<NB, 512, kCompactMaxCpb / 512>(sb, max_ncb, grad_mode, s);
 }
 
 }  // namespace
@@ -289,13 +286,8 @@ hipError_t launch_compact_mid(const Plan& p, const CompactReq* reqs, int count, 
 hipError_t launch_compact_cells(const SumReq* reqs, int count, int grad_mode, hipStream_t s) {
   if (count <= 0) return hipSuccess;
   if (count > kMaxBatch) return hipErrorInvalidValue;
-  int max_ncb = 0;
-  for (int i = 0; i < count; ++i) {
-    if (reqs[i].cpb > kCompactMaxCpb) return hipErrorInvalidValue;
-    max_ncb = std::max(max_ncb, reqs[i].ncb);
-  }
-  return count == 1 ? cells_batch<1>(reqs, count, max_ncb, grad_mode, s)
-                    : cells_batch<kMaxBatch>(reqs, count, max_ncb, grad_mode, s);
+  return count == 1 ? cells_batch<1>(reqs, count, grad_mode, s)
+                    : cells_batch<kMaxBatch>(reqs, count, grad_mode, s);
 }
 
 }  // namespace fftpl

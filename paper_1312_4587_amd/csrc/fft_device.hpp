@@ -170,7 +170,7 @@ template <int NT, int K>
 __device__ __forceinline__ void block_sums(double (&v)[K], double* red, int tid) {
   constexpr int NW = NT / kWave;
 #pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
+  for (int k = 0; k < K; ++k) v[k] = wave_sum_dpp_d(v[k]);
   if constexpr (NW > 1) {
     if ((tid & (kWave - 1)) == 0) {
 #pragma unroll
