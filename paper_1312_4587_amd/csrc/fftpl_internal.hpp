@@ -538,7 +538,7 @@ hipError_t launch_wa(int num_nets, const int32_t* net_ptr, const int32_t* pin_ce
 // gradients added to per-cell 64-bit fixed-point accumulators, then written
 // (accumulate = 0) or added to gx, gy; wa_out / hp_out (if set) get the
 // totals from per-block partials summed in a fixed order.  work: at least
-// wa_fixed_work_bytes(num_cells, num_nets) bytes, 8-byte aligned.
+// wa_fixed_work_bytes(num_cells, num_nets) bytes, 16-byte aligned.
 size_t wa_fixed_work_bytes(int num_cells, int num_nets);
 hipError_t launch_wa_fixed(int num_nets, const int32_t* net_ptr, const int32_t* pin_cell,
                            const float* pin_dx, const float* pin_dy, int num_cells,

@@ -20,7 +20,9 @@
 //   FIXED:  64-bit integer atomics of the gradients in fixed point (units of
 //           2^-32, exact for every component of magnitude >= 2^-9) into
 //           per-cell accumulators, converted once per cell: the sums do not
-//           depend on the order of the adds (the stateless calls);
+//           depend on the order of the adds (the stateless calls, k_wa_fixed).
+//           A cell's two accumulators are neighbours and neighbouring lanes add to
+//           them in one instruction, so a pin costs one cache-line operation;
 //   SLOTS:  each pin's (gx, gy) is stored at its slot in a cell-major copy of
 //           the pins (one random 8-byte write per pin); the cell pass then sums
 //           contiguous slots.  Positions come interleaved as float2 so the
@@ -47,9 +49,8 @@ struct PinIO {
   float* gx;
   float* gy;
   float2* pin_grad;
-  unsigned long long* fx = nullptr;   // FIXED: per-cell sums (2^-32 units)
-  unsigned long long* fy = nullptr;
-  unsigned int* bad = nullptr;        // FIXED: a non-finite (or absurd) pin gradient
+  unsigned long long* acc = nullptr;   // FIXED: per-cell sums (2^-32 units), x and y in turn
+  unsigned int* bad = nullptr;         // FIXED: a non-finite (or absurd) pin gradient
   __device__ __forceinline__ float2 pos(int c) const {
     if (IO == kIoSlots) return xy[c];
     return make_float2(x[c], y[c]);
@@ -57,94 +58,52 @@ struct PinIO {
   __device__ __forceinline__ void put(int p, int c, float vx, float vy) const {
     if (IO == kIoSlots) {
       pin_grad[slot[p]] = make_float2(vx, vy);
-    } else if (IO == kIoFixed) {
-      if (fabsf(vx) <= kFixLimit && fabsf(vy) <= kFixLimit) {
-        atomicAdd(&fx[c], (unsigned long long)__float2ll_rn(vx * kFixScale));
-        atomicAdd(&fy[c], (unsigned long long)__float2ll_rn(vy * kFixScale));
-      } else {
-        atomicOr(&bad[c], 1u);
-      }
     } else {
       unsafeAtomicAdd(&gx[c], vx);
       unsafeAtomicAdd(&gy[c], vy);
     }
   }
+  // FIXED: one axis of a pin
+  __device__ __forceinline__ void put_axis(int c, int axis, float v) const {
+    if (fabsf(v) <= kFixLimit)
+      atomicAdd(&acc[2 * (size_t)c + axis], (unsigned long long)__float2ll_rn(v * kFixScale));
+    else
+      atomicOr(&bad[c], 1u);
+  }
+  // A wavefront's pins at once (p < p1: the lane has one); every lane must call it.
+  __device__ __forceinline__ void put_wave(int p, int p1, int c, float vx, float vy) const {
+    if (IO == kIoFixed) {
+      // two rounds of 32 pins, a lane pair per pin
+      const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int src = (lane >> 1) + 32 * r;
+        const int cs = __shfl(c, src, kWave);
+        const float ax = __shfl(vx, src, kWave), ay = __shfl(vy, src, kWave);
+        if (p - lane + src < p1) put_axis(cs, lane & 1, lane & 1 ? ay : ax);
+      }
+    } else if (p < p1) {
+      put(p, c, vx, vy);
+    }
+  }
 };
 
-// PART 0: nets of degree <= kSmallDeg; 1: larger nets.  LSE: the log-sum-exp
-// model instead of the weighted average (same sums, pin_wl_grad / net_wl_value).
-template <int IO, int PART, bool LSE>
-__global__ void __launch_bounds__(256)
-    k_wa(int num_nets, const int32_t* __restrict__ net_ptr,
-         const int32_t* __restrict__ pin_cell, const float* __restrict__ pin_dx,
-         const float* __restrict__ pin_dy, PinIO<IO> io, float gamma, float inv_gamma,
-         double* __restrict__ wa_out, double* __restrict__ hp_out,
-         double* __restrict__ part) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = threadIdx.x & (kWave - 1);
-  int p0 = 0, p1 = 0;
-  if (PART == 0 && e < num_nets) {
-    p0 = net_ptr[e];
-    p1 = net_ptr[e + 1];
-  }
-  const int deg = p1 - p0;
-  double acc_wa = 0.0, acc_hp = 0.0;
-
-  if (PART == 0 && deg >= 2 && deg <= kSmallDeg) {
-    int cell[kSmallDeg];
-    float px[kSmallDeg], py[kSmallDeg];
-    // all loads first (independent), positions relative to the first pin's cell
-#pragma unroll
-    for (int k = 0; k < kSmallDeg; ++k)
-      if (k < deg) cell[k] = pin_cell[p0 + k];
-    float2 q[kSmallDeg];
-#pragma unroll
-    for (int k = 0; k < kSmallDeg; ++k)
-      if (k < deg) q[k] = io.pos(cell[k]);
-    float mx = -INFINITY, lx = INFINITY, my = -INFINITY, ly = INFINITY;
-#pragma unroll
-    for (int k = 0; k < kSmallDeg; ++k) {
-      if (k < deg) {
-        px[k] = (q[k].x - q[0].x) + pin_dx[p0 + k];
-        py[k] = (q[k].y - q[0].y) + pin_dy[p0 + k];
-        mx = fmaxf(mx, px[k]);
-        lx = fminf(lx, px[k]);
-        my = fmaxf(my, py[k]);
-        ly = fminf(ly, py[k]);
-      }
-    }
-    AxisSums sx = {0.f, 0.f, 0.f, 0.f}, sy = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < kSmallDeg; ++k) {
-      if (k < deg) {
-        axis_accum(sx, px[k], mx, lx, inv_gamma);
-        axis_accum(sy, py[k], my, ly, inv_gamma);
-      }
-    }
-    const float wpx = sx.tp / sx.sp, wmx = sx.tm / sx.sm;
-    const float wpy = sy.tp / sy.sp, wmy = sy.tm / sy.sm;
-    const float rspx = 1.0f / sx.sp, rsmx = 1.0f / sx.sm;
-    const float rspy = 1.0f / sy.sp, rsmy = 1.0f / sy.sm;
-#pragma unroll
-    for (int k = 0; k < kSmallDeg; ++k) {
-      if (k < deg) {
-        io.put(p0 + k, cell[k], pin_wl_grad<LSE>(px[k], mx, lx, wpx, wmx, rspx, rsmx, inv_gamma),
-               pin_wl_grad<LSE>(py[k], my, ly, wpy, wmy, rspy, rsmy, inv_gamma));
-      }
-    }
-    acc_wa = net_wl_value<LSE>(mx, lx, wpx, wmx, sx.sp, sx.sm, gamma) +
-             net_wl_value<LSE>(my, ly, wpy, wmy, sy.sp, sy.sm, gamma);
-    acc_hp = (double)(mx - lx) + (double)(my - ly);
-  } else if (IO == kIoSlots && PART == 0 && deg == 1) {
-    io.put(p0, 0, 0.0f, 0.0f);   // a one-pin net has no wirelength: its slot holds zero
-  }
-
+// Nets above kSmallDeg by block blk of a grid of nblk blocks; adds their totals.
+template <int IO, bool LSE>
+__device__ __forceinline__ void wa_big_nets(int blk, int nblk, int num_nets,
+                                            const int32_t* __restrict__ net_ptr,
+                                            const int32_t* __restrict__ pin_cell,
+                                            const float* __restrict__ pin_dx,
+                                            const float* __restrict__ pin_dy,
+                                            const PinIO<IO>& io, float gamma, float inv_gamma,
+                                            double& acc_wa, double& acc_hp) {
   // Larger nets: the whole wavefront cooperates on each in turn.  This part
   // runs on a persistent grid (every wavefront walks chunks of kWave nets), so
   // a few slow nets do not hold back the dispatch of thousands of blocks.
-  const int wid = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const int nwaves = gridDim.x * blockDim.x / kWave;
-  const int nchunks = PART == 1 ? (num_nets + kWave - 1) / kWave : 0;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wid = (blk * blockDim.x + threadIdx.x) / kWave;
+  const int nwaves = nblk * blockDim.x / kWave;
+  const int nchunks = (num_nets + kWave - 1) / kWave;
   for (int ch = wid; ch < nchunks; ch += nwaves) {
   const int ec = ch * kWave + lane;
   int c0 = 0, c1 = 0;
@@ -211,10 +170,11 @@ __global__ void __launch_bounds__(256)
       const float rspy = 1.0f / sy.sp, rsmy = 1.0f / sy.sm;
 #pragma unroll
       for (int j = 0; j < kBigRegs; ++j) {
+        if (b0 + kWave * j >= b1) break;
         const int p = b0 + lane + kWave * j;
-        if (p < b1)
-          io.put(p, cj[j], pin_wl_grad<LSE>(q[j].x, mx, lx, wpx, wmx, rspx, rsmx, inv_gamma),
-                 pin_wl_grad<LSE>(q[j].y, my, ly, wpy, wmy, rspy, rsmy, inv_gamma));
+        io.put_wave(p, b1, cj[j],
+                    pin_wl_grad<LSE>(q[j].x, mx, lx, wpx, wmx, rspx, rsmx, inv_gamma),
+                    pin_wl_grad<LSE>(q[j].y, my, ly, wpy, wmy, rspy, rsmy, inv_gamma));
       }
       if (lane == src) {
         acc_wa += net_wl_value<LSE>(mx, lx, wpx, wmx, sx.sp, sx.sm, gamma) +
@@ -256,12 +216,13 @@ __global__ void __launch_bounds__(256)
     const float wpy = sy.tp / sy.sp, wmy = sy.tm / sy.sm;
     const float rspx = 1.0f / sx.sp, rsmx = 1.0f / sx.sm;
     const float rspy = 1.0f / sy.sp, rsmy = 1.0f / sy.sm;
-    for (int p = b0 + lane; p < b1; p += kWave) {
-      const int c = pin_cell[p];
+    for (int p0 = b0; p0 < b1; p0 += kWave) {
+      const int p = p0 + lane, pc = min(p, b1 - 1);
+      const int c = pin_cell[pc];
       const float2 q = io.pos(c);
-      const float X = (q.x - r.x) + pin_dx[p], Y = (q.y - r.y) + pin_dy[p];
-      io.put(p, c, pin_wl_grad<LSE>(X, mx, lx, wpx, wmx, rspx, rsmx, inv_gamma),
-             pin_wl_grad<LSE>(Y, my, ly, wpy, wmy, rspy, rsmy, inv_gamma));
+      const float X = (q.x - r.x) + pin_dx[pc], Y = (q.y - r.y) + pin_dy[pc];
+      io.put_wave(p, b1, c, pin_wl_grad<LSE>(X, mx, lx, wpx, wmx, rspx, rsmx, inv_gamma),
+                  pin_wl_grad<LSE>(Y, my, ly, wpy, wmy, rspy, rsmy, inv_gamma));
     }
     if (lane == src) {
       acc_wa += net_wl_value<LSE>(mx, lx, wpx, wmx, sx.sp, sx.sm, gamma) +
@@ -270,6 +231,78 @@ __global__ void __launch_bounds__(256)
     }
   }
   }
+}
+
+// PART 0: nets of degree <= kSmallDeg; 1: larger nets.  LSE: the log-sum-exp
+// model instead of the weighted average (same sums, pin_wl_grad / net_wl_value).
+template <int IO, int PART, bool LSE>
+__global__ void __launch_bounds__(256)
+    k_wa(int num_nets, const int32_t* __restrict__ net_ptr,
+         const int32_t* __restrict__ pin_cell, const float* __restrict__ pin_dx,
+         const float* __restrict__ pin_dy, PinIO<IO> io, float gamma, float inv_gamma,
+         double* __restrict__ wa_out, double* __restrict__ hp_out,
+         double* __restrict__ part) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  int p0 = 0, p1 = 0;
+  if (PART == 0 && e < num_nets) {
+    p0 = net_ptr[e];
+    p1 = net_ptr[e + 1];
+  }
+  const int deg = p1 - p0;
+  double acc_wa = 0.0, acc_hp = 0.0;
+
+  if (PART == 0 && deg >= 2 && deg <= kSmallDeg) {
+    int cell[kSmallDeg];
+    float px[kSmallDeg], py[kSmallDeg];
+    // all loads first (independent), positions relative to the first pin's cell
+#pragma unroll
+    for (int k = 0; k < kSmallDeg; ++k)
+      if (k < deg) cell[k] = pin_cell[p0 + k];
+    float2 q[kSmallDeg];
+#pragma unroll
+    for (int k = 0; k < kSmallDeg; ++k)
+      if (k < deg) q[k] = io.pos(cell[k]);
+    float mx = -INFINITY, lx = INFINITY, my = -INFINITY, ly = INFINITY;
+#pragma unroll
+    for (int k = 0; k < kSmallDeg; ++k) {
+      if (k < deg) {
+        px[k] = (q[k].x - q[0].x) + pin_dx[p0 + k];
+        py[k] = (q[k].y - q[0].y) + pin_dy[p0 + k];
+        mx = fmaxf(mx, px[k]);
+        lx = fminf(lx, px[k]);
+        my = fmaxf(my, py[k]);
+        ly = fminf(ly, py[k]);
+      }
+    }
+    AxisSums sx = {0.f, 0.f, 0.f, 0.f}, sy = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < kSmallDeg; ++k) {
+      if (k < deg) {
+        axis_accum(sx, px[k], mx, lx, inv_gamma);
+        axis_accum(sy, py[k], my, ly, inv_gamma);
+      }
+    }
+    const float wpx = sx.tp / sx.sp, wmx = sx.tm / sx.sm;
+    const float wpy = sy.tp / sy.sp, wmy = sy.tm / sy.sm;
+    const float rspx = 1.0f / sx.sp, rsmx = 1.0f / sx.sm;
+    const float rspy = 1.0f / sy.sp, rsmy = 1.0f / sy.sm;
+#pragma unroll
+    for (int k = 0; k < kSmallDeg; ++k) {
+      if (k < deg) {
+        io.put(p0 + k, cell[k], pin_wl_grad<LSE>(px[k], mx, lx, wpx, wmx, rspx, rsmx, inv_gamma),
+               pin_wl_grad<LSE>(py[k], my, ly, wpy, wmy, rspy, rsmy, inv_gamma));
+      }
+    }
+    acc_wa = net_wl_value<LSE>(mx, lx, wpx, wmx, sx.sp, sx.sm, gamma) +
+             net_wl_value<LSE>(my, ly, wpy, wmy, sy.sp, sy.sm, gamma);
+    acc_hp = (double)(mx - lx) + (double)(my - ly);
+  } else if (IO == kIoSlots && PART == 0 && deg == 1) {
+    io.put(p0, 0, 0.0f, 0.0f);   // a one-pin net has no wirelength: its slot holds zero
+  }
+
+  if (PART == 1)
+    wa_big_nets<IO, LSE>(blockIdx.x, gridDim.x, num_nets, net_ptr, pin_cell, pin_dx, pin_dy, io,
+                         gamma, inv_gamma, acc_wa, acc_hp);
   if (part) {
     // per-block partials: part[b] = W~, part[gridDim.x + b] = HPWL
     block_sum_to<false>(acc_wa, &part[blockIdx.x]);
@@ -278,6 +311,82 @@ __global__ void __launch_bounds__(256)
     if (wa_out) block_atomic_add(acc_wa, wa_out);
     if (hp_out) block_atomic_add(acc_hp, hp_out);
   }
+}
+
+// The stateless gradient (kIoFixed) in one launch: nbig persistent blocks for the
+// nets above kSmallDeg, dispatched first, and beside them a lane pair per smaller
+// net, one lane per axis.  Bound by the atomics: with a cell's two sums in
+// separate arrays and two instructions per pin they retired at 27 G/s, 63 us of
+// the 117 us that the five kernels of a call took at 200k cells, 854k pins.  As
+// neighbours added to in one instruction they cost one cache-line operation per
+// pin: k_wa_fixed 51 us, the call 123 -> 69 us; at 2.1M cells, 12.4M pins 1213 ->
+// 653 us.
+template <bool LSE>
+__global__ void __launch_bounds__(256)
+    k_wa_fixed(int num_nets, const int32_t* __restrict__ net_ptr,
+               const int32_t* __restrict__ pin_cell, const float* __restrict__ pin_dx,
+               const float* __restrict__ pin_dy, PinIO<kIoFixed> io, float gamma,
+               float inv_gamma, int nbig, double* __restrict__ part_small,
+               double* __restrict__ part_big) {
+  double acc_wa = 0.0, acc_hp = 0.0;
+  if ((int)blockIdx.x < nbig) {
+    wa_big_nets<kIoFixed, LSE>(blockIdx.x, nbig, num_nets, net_ptr, pin_cell, pin_dx, pin_dy, io,
+                               gamma, inv_gamma, acc_wa, acc_hp);
+  } else {
+    const int e = ((int)blockIdx.x - nbig) * 128 + ((int)threadIdx.x >> 1);
+    const int axis = threadIdx.x & 1;
+    int p0 = 0, p1 = 0;
+    if (e < num_nets) {
+      p0 = net_ptr[e];
+      p1 = net_ptr[e + 1];
+    }
+    const int deg = p1 - p0;
+    if (deg >= 2 && deg <= kSmallDeg) {
+      const float* __restrict__ xs = axis ? io.y : io.x;
+      const float* __restrict__ ds = axis ? pin_dy : pin_dx;
+      int cell[kSmallDeg];
+      float q[kSmallDeg], px[kSmallDeg];
+      // all loads first (independent), positions relative to the first pin's cell
+#pragma unroll
+      for (int k = 0; k < kSmallDeg; ++k)
+        if (k < deg) {
+          cell[k] = pin_cell[p0 + k];
+          px[k] = ds[p0 + k];
+        }
+#pragma unroll
+      for (int k = 0; k < kSmallDeg; ++k)
+        if (k < deg) q[k] = xs[cell[k]];
+      float mx = -INFINITY, lx = INFINITY;
+#pragma unroll
+      for (int k = 0; k < kSmallDeg; ++k) {
+        if (k < deg) {
+          px[k] = (q[k] - q[0]) + px[k];
+          mx = fmaxf(mx, px[k]);
+          lx = fminf(lx, px[k]);
+        }
+      }
+      AxisSums sx = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < kSmallDeg; ++k)
+        if (k < deg) axis_accum(sx, px[k], mx, lx, inv_gamma);
+      const float wp = sx.tp / sx.sp, wm = sx.tm / sx.sm;
+      const float rsp = 1.0f / sx.sp, rsm = 1.0f / sx.sm;
+#pragma unroll
+      for (int k = 0; k < kSmallDeg; ++k)
+        if (k < deg)
+          io.put_axis(cell[k], axis,
+                      pin_wl_grad<LSE>(px[k], mx, lx, wp, wm, rsp, rsm, inv_gamma));
+      acc_wa = net_wl_value<LSE>(mx, lx, wp, wm, sx.sp, sx.sm, gamma);
+      acc_hp = (double)(mx - lx);
+    }
+  }
+  // per-block partials: W~ of all blocks of the kind, then HPWL
+  const bool big = (int)blockIdx.x < nbig;
+  const int b = big ? (int)blockIdx.x : (int)blockIdx.x - nbig;
+  const int nb = big ? nbig : (int)gridDim.x - nbig;
+  double* part = big ? part_big : part_small;
+  block_sum_to<false>(acc_wa, &part[b]);
+  block_sum_to<false>(acc_hp, &part[nb + b]);
 }
 
 template <int IO, bool LSE>
@@ -313,23 +422,31 @@ hipError_t launch_wa(int num_nets, const int32_t* net_ptr, const int32_t* pin_ce
 }
 
 // Per cell: the fixed-point sums back to float (NaN for a cell that had a
-// non-finite pin gradient), written or added to gx, gy.
-__global__ void __launch_bounds__(256)
-    k_fix_cells(int m, const unsigned long long* __restrict__ fx,
-                const unsigned long long* __restrict__ fy, const unsigned int* __restrict__ bad,
-                int accumulate, float* __restrict__ gx, float* __restrict__ gy) {
-  constexpr double unit = 1.0 / 4294967296.0;
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < m; c += gridDim.x * blockDim.x) {
-    const bool b = bad[c] != 0u;
-    const float vx = b ? __builtin_nanf("") : (float)((double)(long long)fx[c] * unit);
-    const float vy = b ? __builtin_nanf("") : (float)((double)(long long)fy[c] * unit);
-    gx[c] = accumulate ? gx[c] + vx : vx;
-    gy[c] = accumulate ? gy[c] + vy : vy;
+// non-finite pin gradient), written or added to gx, gy; the last block sums
+// the totals from the per-block partials in a fixed order instead.
+constexpr int kFixThreads = 256;
+__global__ void __launch_bounds__(kFixThreads)
+    k_fix_cells(int m, const ulonglong2* __restrict__ acc, const unsigned int* __restrict__ bad,
+                int accumulate, float* __restrict__ gx, float* __restrict__ gy, FinalArgs fin) {
+  if (blockIdx.x + 1 == gridDim.x) {
+    if (fin.o_wa || fin.o_hp) eval_scalars<kFixThreads>(fin);
+    return;
   }
+  constexpr double unit = 1.0 / 4294967296.0;
+  const int c = blockIdx.x * kFixThreads + threadIdx.x;
+  if (c >= m) return;
+  const bool b = bad[c] != 0u;
+  const ulonglong2 a = acc[c];
+  const float vx = b ? __builtin_nanf("") : (float)((double)(long long)a.x * unit);
+  const float vy = b ? __builtin_nanf("") : (float)((double)(long long)a.y * unit);
+  gx[c] = accumulate ? gx[c] + vx : vx;
+  gy[c] = accumulate ? gy[c] + vy : vy;
 }
 
+static inline int wa_small_grid(int num_nets) { return (num_nets + 127) / 128; }
+
 size_t wa_fixed_work_bytes(int num_cells, int num_nets) {
-  const size_t parts = 2 * ((size_t)(num_nets + 255) / 256 + (size_t)wa_big_grid(num_nets));
+  const size_t parts = 2 * ((size_t)wa_small_grid(num_nets) + (size_t)wa_big_grid(num_nets));
   return 16 * (size_t)num_cells + 4 * (size_t)num_cells + 8 * parts + 256;
 }
 
@@ -338,36 +455,35 @@ hipError_t launch_wa_fixed(int num_nets, const int32_t* net_ptr, const int32_t* 
                            const float* x, const float* y, float gamma, int wl_model,
                            int accumulate, float* gx, float* gy, double* wa_out,
                            double* hp_out, void* work, hipStream_t s) {
-  // work: fx, fy [m] (u64), W~/HPWL partials, bad [m] (u32), cleared first
+  // work: the cells' (x, y) sums (u64), bad [m] (u32), both cleared first, then
+  // the W~ / HPWL partials [small blocks, big blocks], all written
   char* w = static_cast<char*>(work);
-  unsigned long long* fx = reinterpret_cast<unsigned long long*>(w);
-  unsigned long long* fy = fx + num_cells;
-  double* part = reinterpret_cast<double*>(fy + num_cells);
-  const int nblk = (num_nets + 255) / 256, nbig = wa_big_grid(num_nets);
-  unsigned int* bad = reinterpret_cast<unsigned int*>(part + 2 * ((size_t)nblk + nbig));
-  const int64_t words = (16 * (int64_t)num_cells + 4 * (int64_t)num_cells) / 4 +
-                        4 * ((int64_t)nblk + nbig);
-  hipError_t e = launch_zero_i32(reinterpret_cast<int32_t*>(work), words, s);
+  unsigned long long* acc = reinterpret_cast<unsigned long long*>(w);
+  unsigned int* bad = reinterpret_cast<unsigned int*>(w + 16 * (size_t)num_cells);
+  const int nsmall = wa_small_grid(num_nets), nbig = wa_big_grid(num_nets);
+  double* part = reinterpret_cast<double*>(w + (20 * (size_t)num_cells + 7) / 8 * 8);
+  hipError_t e = launch_zero_i32(reinterpret_cast<int32_t*>(w), 5 * (int64_t)num_cells, s);
   if (e != hipSuccess) return e;
-  PinIO<kIoFixed> io{x, y, nullptr, nullptr, nullptr, nullptr, nullptr, fx, fy, bad};
-  e = wl_model == FFTPL_WL_LSE
-          ? launch_wa_parts<kIoFixed, true>(num_nets, net_ptr, pin_cell, pin_dx, pin_dy, io,
-                                            gamma, nullptr, nullptr, part, s, nullptr)
-          : launch_wa_parts<kIoFixed, false>(num_nets, net_ptr, pin_cell, pin_dx, pin_dy, io,
-                                             gamma, nullptr, nullptr, part, s, nullptr);
-  if (e != hipSuccess) return e;
-  if (num_cells > 0) {
-    int blocks = (num_cells + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_fix_cells, dim3(blocks), dim3(256), 0, s, num_cells, fx, fy, bad,
-                       accumulate, gx, gy);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  // the totals from the per-block partials in a fixed order
-  if (wa_out || hp_out)
-    e = launch_eval_finalize(nullptr, 0, nullptr, 0, part, nblk, nbig, nullptr, wa_out, hp_out,
-                             nullptr, s);
-  return e;
+  PinIO<kIoFixed> io{x, y, nullptr, nullptr, nullptr, nullptr, nullptr, acc, bad};
+  double* part_big = part + 2 * (size_t)nsmall;
+  const dim3 grid(nbig + nsmall), block(256);
+  if (wl_model == FFTPL_WL_LSE)
+    hipLaunchKernelGGL((k_wa_fixed<true>), grid, block, 0, s, num_nets, net_ptr, pin_cell, pin_dx,
+                       pin_dy, io, gamma, 1.0f / gamma, nbig, part, part_big);
+  else
+    hipLaunchKernelGGL((k_wa_fixed<false>), grid, block, 0, s, num_nets, net_ptr, pin_cell,
+                       pin_dx, pin_dy, io, gamma, 1.0f / gamma, nbig, part, part_big);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  FinalArgs fin;
+  fin.wa = part;
+  fin.n_s = nsmall;
+  fin.n_b = nbig;
+  fin.o_wa = wa_out;
+  fin.o_hp = hp_out;
+  hipLaunchKernelGGL(k_fix_cells, dim3((num_cells + kFixThreads - 1) / kFixThreads + 1),
+                     dim3(kFixThreads), 0, s, num_cells,
+                     reinterpret_cast<const ulonglong2*>(acc), bad, accumulate, gx, gy, fin);
+  return hipGetLastError();
 }
 
 hipError_t launch_wa_pins(int num_nets, const int32_t* net_ptr, const int32_t* pin_cell,
@@ -480,7 +596,9 @@ __global__ void k_pin_slots(int num_pins, const int32_t* __restrict__ pin_cell,
 
 hipError_t launch_zero_i32(int32_t* a, int64_t count, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_zero_i32, dim3(256), dim3(256), 0, s, a, (int)count);
+  const int64_t blocks = (count + 1023) / 1024;
+  hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, s,
+                     a, (int)count);
   return hipGetLastError();
 }
 

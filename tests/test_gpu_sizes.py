@@ -1,13 +1,15 @@
 """The size rules of the launches: designs at the edges where the blocks of a
 kernel change their size, against the FP64 oracle (relative L2 <= 1e-5, the
 bar of every float32 result here)."""
+import dataclasses
+
 import numpy as np
 import pytest
 
 import gen
 import oracle
 from _helpers import rel_l2
-from gpu_common import RTOL, DeviceCells, host, lib_or_build, say
+from gpu_common import RTOL, DeviceCells, dev, host, lib_or_build, say
 
 pytestmark = pytest.mark.gpu
 
@@ -132,3 +134,49 @@ def test_batch_mixes_size_classes(F):
         assert torch.allclose(o4, out[k], rtol=1e-12, atol=0.0)
     plan.close()
     single.close()
+
+
+# the stateless wirelength gradient: lane pairs up to degree 8, a wavefront from
+# 9 (registers up to 1,024 pins, several passes past them), one launch for both;
+# net and cell counts around its blocks; accumulating, the totals left out, and a
+# non-finite position, which makes its nets' cells NaN and no other cell
+@pytest.mark.parametrize("m,degs", [(1, [1, 1]), (70, [8] * 127 + [9]), (127, [2] * 129),
+                                    (300, [64, 65, 0, 1, 63, 2, 3]),
+                                    (3000, [1024, 1025, 2, 2100, 8, 9] + [5] * 300)])
+def test_stateless_wirelength_sizes(F, m, degs):
+    import torch
+    base = gen.make_instance((97, m), num_cells=m, util=0.7, n=16, num_nets=0)
+    rng = np.random.default_rng(97)
+    cells = np.concatenate([rng.choice(m, size=d, replace=False) for d in degs]).astype(np.int32)
+    inst = dataclasses.replace(
+        base, net_ptr=np.concatenate([[0], np.cumsum(degs)]).astype(np.int32), pin_cell=cells,
+        pin_dx=(rng.random(len(cells)) - 0.5).astype(np.float32),
+        pin_dy=(rng.random(len(cells)) - 0.5).astype(np.float32))
+    c = DeviceCells(inst)
+    net = (dev(inst.net_ptr), dev(inst.pin_cell), dev(inst.pin_dx), dev(inst.pin_dy))
+    for call, ref in ((F.wa_grad, oracle.wa_wirelength), (F.lse_grad, oracle.lse_wirelength)):
+        gx, gy = (torch.full((m,), 3.0, device="cuda") for _ in range(2))
+        wl, hp = (torch.zeros(1, dtype=torch.float64, device="cuda") for _ in range(2))
+        say("stateless", m, len(degs), call.__name__)
+        call(*net, c.x, c.y, inst.gamma, 0, gx, gy, wl, hp)
+        W0, rx, ry = ref(inst)
+        scale = max(1.0, np.linalg.norm(rx), np.linalg.norm(ry))
+        assert np.linalg.norm(host(gx) - rx) < RTOL * scale
+        assert np.linalg.norm(host(gy) - ry) < RTOL * scale
+        assert abs(float(wl) - W0) <= RTOL * max(abs(W0), inst.gamma)
+        assert abs(float(hp) - oracle.hpwl(inst)) <= RTOL * oracle.hpwl(inst)
+        ax, ay = gx.clone(), gy.clone()
+        call(*net, c.x, c.y, inst.gamma, 1, ax, ay)
+        torch.cuda.synchronize()
+        assert torch.equal(ax, gx + gx) and torch.equal(ay, gy + gy)
+    bad = int(cells[-1])
+    x = c.x.clone()
+    x[bad] = float("nan")
+    F.wa_grad(*net, x, c.y, inst.gamma, 0, ax, ay)
+    deg = np.diff(inst.net_ptr)
+    net_of = np.repeat(np.arange(len(deg)), deg)
+    hit = np.zeros(m, bool)
+    for e in np.unique(net_of[cells == bad]):
+        if deg[e] >= 2:
+            hit[cells[net_of == e]] = True
+    assert np.array_equal(np.isnan(host(ax)), hit)
