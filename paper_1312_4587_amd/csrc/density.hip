@@ -146,6 +146,10 @@ hipError_t launch_init_eval(double* out4, int32_t* counters, int ncount, hipStre
 // ---------------------------------------------------------------------------
 // PINS: 0 density gradient only; 1 plus the sum of the cell's contiguous pin
 // slots (cell_ptr, pin_grad).
+// Random reads of the maps bound it: a cell touches one or two 128-byte lines of
+// a map row for 24 bytes of it.  density_grad_small and density_grad_maps
+// read a cell's bins of one row in one or two loads; 2.1M cells at n = 1024 in
+// random order: EXACT 59.9 -> 24.7 us, FIELD 77.3 -> 72.5 us.
 constexpr int kGatherThreads = 256;
 
 template <int MODE, bool INTERLEAVED, int PINS>
@@ -162,8 +166,10 @@ __global__ void __launch_bounds__(kGatherThreads)
     // the cell's own loads go out together, before the map reads that
     // depend on them
     const float xi = x[i], yi = y[i], wi = w[i], hi = h[i];
-    const float2 d =
-        cell_density_grad<MODE, INTERLEAVED>(g, xi, yi, wi, hi, ex, ey, exy, psi);
+    const Span sx = cell_span(xi, wi, g.xl, g.inv_bw, g.n);
+    const Span sy = cell_span(yi, hi, g.yl, g.inv_bh, g.n);
+    const float2 d = INTERLEAVED ? density_grad_small<MODE>(g, sx, sy, exy, psi)
+                                 : density_grad_maps<MODE>(g, sx, sy, ex, ey, psi);
     float ax = scale * d.x, ay = scale * d.y;
     if (PINS == 1) {
       // the cell's wirelength gradient: its pins' slots are contiguous
@@ -180,6 +186,61 @@ __global__ void __launch_bounds__(kGatherThreads)
     } else {
       gx[i] = ax;
       gy[i] = ay;
+    }
+  }
+}
+
+// FIELD from two maps that together are larger than an XCD's L2 (4 MB).  The two
+// are read one after the other: a block keeps its cells in LDS (each lane its
+// own), gathers Ex for all of them and then Ey, and as the blocks of the grid
+// run in step, most of the chip works on one map at a time.  Cells and results
+// pass the caches by (non-temporal).  m = 2.1M, n = 1024, random order: 72.5 ->
+// 62.8 us (L2 misses bound both); m = 1M: 41.4 -> 33.4; n = 2048: 155 -> 142.
+// Blocks of four or five cells per lane drift apart and measured the same at
+// 2.1M; one launch half per map (cells read twice) 54 us, but 24.9 in place of
+// 19.0 us when the cells are ordered by position.
+// Smaller maps (n = 512: 2 MB both) stay in the L2 together, 27.5 us in one pass
+// against 34.8 in two; fewer cells than the chip has lanes (8 blocks of 256 on
+// each of 256 compute units) are one cell per lane in flight at once, and gain
+// nothing (n = 1024: 20.9 against 19.7 us at 262k, 18.1 against 23.9 at 123k; at
+// 524k 26.3 against 23.5).
+constexpr int kGatherPhaseCells = 2;
+constexpr int kTwoMapsMinN = 1024;
+constexpr int kTwoMapsMinCells = 524288;
+
+__global__ void __launch_bounds__(kGatherThreads, 8)
+    k_gather_two_maps(GridF g, int m, const float* __restrict__ x,
+                      const float* __restrict__ y, const float* __restrict__ w,
+                      const float* __restrict__ h, const float* __restrict__ ex,
+                      const float* __restrict__ ey, float scale, int accumulate,
+                      float* __restrict__ gx, float* __restrict__ gy) {
+  __shared__ float4 cell[kGatherPhaseCells][kGatherThreads];
+  const int n = g.n, t = threadIdx.x;
+  const int64_t i0 = (int64_t)blockIdx.x * kGatherThreads + t;
+  const int64_t step = (int64_t)gridDim.x * kGatherThreads;
+#pragma unroll
+  for (int c = 0; c < kGatherPhaseCells; ++c) {
+    const int64_t i = min(i0 + c * step, (int64_t)m - 1);
+    cell[c][t] = make_float4(__builtin_nontemporal_load(x + i), __builtin_nontemporal_load(y + i),
+                             __builtin_nontemporal_load(w + i), __builtin_nontemporal_load(h + i));
+  }
+#pragma unroll 1
+  for (int p = 0; p < 2; ++p) {
+    const float* __restrict__ e = p ? ey : ex;
+    float* __restrict__ out = p ? gy : gx;
+    const float inv = p ? g.inv_bh : g.inv_bw;
+#pragma unroll 1
+    for (int c = 0; c < kGatherPhaseCells; ++c) {
+      const int64_t i = i0 + c * step;
+      if (i >= m) break;
+      const float4 q = cell[c][t];
+      const Span sx = cell_span(q.x, q.z, g.xl, g.inv_bw, n);
+      const Span sy = cell_span(q.y, q.w, g.yl, g.inv_bh, n);
+      const float a = scale * (-inv * span_map_sum(n, sx, sy, e));
+      if (accumulate)
+        out[i] += a;
+      else
+        __builtin_nontemporal_store(a, out + i);
     }
   }
 }
@@ -202,6 +263,10 @@ hipError_t launch_gather(const GridF& g, int m, const float* x, const float* y,
   } else if (exy) {
     hipLaunchKernelGGL((k_gather<FFTPL_GRAD_FIELD, true, 0>), grid, block, 0, s, g, m, x, y,
                        w, h, ex, ey, e2, psi, scale, accumulate, nullptr, nullptr, gx, gy);
+  } else if (g.n >= kTwoMapsMinN && m >= kTwoMapsMinCells) {
+    const int per = kGatherThreads * kGatherPhaseCells;
+    hipLaunchKernelGGL(k_gather_two_maps, dim3((unsigned)((m + (int64_t)per - 1) / per)), block,
+                       0, s, g, m, x, y, w, h, ex, ey, scale, accumulate, gx, gy);
   } else {
     hipLaunchKernelGGL((k_gather<FFTPL_GRAD_FIELD, false, 0>), grid, block, 0, s, g, m, x, y,
                        w, h, ex, ey, e2, psi, scale, accumulate, nullptr, nullptr, gx, gy);

@@ -162,10 +162,14 @@ __device__ __forceinline__ float2 density_grad_spans(const GridF& g, const Span&
   return make_float2(ax, ay);
 }
 
+// Vectors of map bins, as aligned as the bins themselves (rows start anywhere).
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f4b __attribute__((ext_vector_type(4), aligned(8)));
+
 // The same gradient from the interleaved map for the usual small cell, at most
-// three bins wide and two high (and, EXACT, inside the region): its six bins are
-// read together before any is used, where the loops above wait for each in
-// turn.  Other cells take the loops.  Same terms in the same order.
+// three bins wide and two high (and, EXACT, inside the region): its bins are
+// read together, two to a load, before any is used, where the loops above wait
+// for each in turn.  Other cells take the loops.  Same terms in the same order.
 template <int MODE>
 __device__ __forceinline__ float2 density_grad_small(const GridF& g, const Span& sx,
                                                      const Span& sy,
@@ -174,16 +178,19 @@ __device__ __forceinline__ float2 density_grad_small(const GridF& g, const Span&
   const int n = g.n;
   const float fn = (float)n;
   const int nx = sx.i1 - sx.i0 + 1, ny = sy.i1 - sy.i0 + 1;
-  bool small = nx >= 1 && nx <= 3 && ny >= 1 && ny <= 2;
+  bool small = nx >= 1 && nx <= 3 && ny >= 1 && ny <= 2 && sx.i0 <= n - 2;
   if (MODE == FFTPL_GRAD_EXACT)
     small = small && sx.lo > 0.0f && sx.hi < fn && sy.lo > 0.0f && sy.hi < fn;
   if (!small) return density_grad_spans<MODE, true>(g, sx, sy, nullptr, nullptr, exy, psi);
   float2 e[2][3];
 #pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-      e[r][c] = exy[(int64_t)min(sy.i0 + r, sy.i1) * n + min(sx.i0 + c, sx.i1)];
+  for (int r = 0; r < 2; ++r) {
+    const float2* row = exy + (int64_t)min(sy.i0 + r, sy.i1) * n + sx.i0;
+    const f4b v = *reinterpret_cast<const f4b*>(row);   // bins i0 and i0 + 1 < n
+    e[r][0] = make_float2(v.x, v.y);
+    e[r][1] = make_float2(v.z, v.w);
+    e[r][2] = nx > 2 ? row[2] : e[r][1];
+  }
   float ax = 0.0f, ay = 0.0f;
   if (MODE == FFTPL_GRAD_FIELD) {
 #pragma unroll
@@ -217,6 +224,106 @@ __device__ __forceinline__ float2 density_grad_small(const GridF& g, const Span&
 #pragma unroll
       for (int r = 0; r < 2; ++r)
         if (r < my) d += e[r][c].y;
+      if (c < nx) ay += span_overlap(sx, sx.i0 + c) * d;
+    }
+    ax *= 2.0f * g.inv_bw;
+    ay *= 2.0f * g.inv_bh;
+  }
+  return make_float2(ax, ay);
+}
+
+// The sum of ov(i, b) * e_b over a span, of one map.  The usual small cell's
+// bins are read four of a row to a load.
+__device__ __forceinline__ float span_map_sum(int n, const Span& sx, const Span& sy,
+                                              const float* __restrict__ e) {
+  const int nx = sx.i1 - sx.i0 + 1, ny = sy.i1 - sy.i0 + 1;
+  float s = 0.0f;
+  if (nx >= 1 && nx <= 3 && ny >= 1 && ny <= 2 && sx.i0 <= n - 4) {
+    const int64_t o = (int64_t)sy.i0 * n + sx.i0;
+    f4u v[2];
+    v[0] = *reinterpret_cast<const f4u*>(e + o);
+    v[1] = v[0];
+    if (ny > 1) v[1] = *reinterpret_cast<const f4u*>(e + o + n);
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const float oy = span_overlap(sy, sy.i0 + r);
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (r < ny && c < nx) s += span_overlap(sx, sx.i0 + c) * oy * v[r][c];
+    }
+  } else {
+    for (int iy = sy.i0; iy <= sy.i1; ++iy) {
+      const float oy = span_overlap(sy, iy);
+      for (int ix = sx.i0; ix <= sx.i1; ++ix)
+        s += span_overlap(sx, ix) * oy * e[(int64_t)iy * n + ix];
+    }
+  }
+  return s;
+}
+
+// The same from separate maps (ex, ey; EXACT: psi): four bins of a row to a load.
+// A wavefront's cells lie anywhere, so every load looks up 64 lines, and the
+// number of loads is what a gather costs.
+template <int MODE>
+__device__ __forceinline__ float2 density_grad_maps(const GridF& g, const Span& sx,
+                                                    const Span& sy,
+                                                    const float* __restrict__ ex,
+                                                    const float* __restrict__ ey,
+                                                    const float* __restrict__ psi) {
+  const int n = g.n;
+  const float fn = (float)n;
+  const int nx = sx.i1 - sx.i0 + 1, ny = sy.i1 - sy.i0 + 1;
+  bool small = nx >= 1 && nx <= 3 && ny >= 1 && ny <= 2 && sx.i0 <= n - 4;
+  if (MODE == FFTPL_GRAD_EXACT)
+    // edges inside the region, and the bins of the right edges among those read
+    small = small && sx.lo > 0.0f && sx.hi < fn && sy.lo > 0.0f && sy.hi < fn &&
+            (int)floorf(sx.hi) <= sx.i0 + 3 && (int)floorf(sy.hi) <= sy.i0 + 1;
+  if (!small) return density_grad_spans<MODE, false>(g, sx, sy, ex, ey, nullptr, psi);
+  const int64_t o = (int64_t)sy.i0 * n + sx.i0;
+  float ax = 0.0f, ay = 0.0f;
+  if (MODE == FFTPL_GRAD_FIELD) {
+    f4u vx[2], vy[2];
+    vx[0] = *reinterpret_cast<const f4u*>(ex + o);
+    vy[0] = *reinterpret_cast<const f4u*>(ey + o);
+    vx[1] = vx[0];
+    vy[1] = vy[0];
+    if (ny > 1) {
+      vx[1] = *reinterpret_cast<const f4u*>(ex + o + n);
+      vy[1] = *reinterpret_cast<const f4u*>(ey + o + n);
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const float oy = span_overlap(sy, sy.i0 + r);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if (r < ny && c < nx) {
+          const float ov = span_overlap(sx, sx.i0 + c) * oy;
+          ax += ov * vx[r][c];
+          ay += ov * vy[r][c];
+        }
+      }
+    }
+    ax *= -g.inv_bw;
+    ay *= -g.inv_bh;
+  } else {
+    const int cr = (int)floorf(sx.hi) - sx.i0, rr = (int)floorf(sy.hi) - sy.i0;
+    f4u v[2];
+    v[0] = *reinterpret_cast<const f4u*>(psi + o);
+    v[1] = v[0];
+    if (ny > 1 || rr > 0) v[1] = *reinterpret_cast<const f4u*>(psi + o + n);
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const float right = cr == 0 ? v[r][0] : cr == 1 ? v[r][1] : cr == 2 ? v[r][2] : v[r][3];
+      float d = 0.0f;
+      d += right;
+      d -= v[r][0];
+      if (r < ny) ax += span_overlap(sy, sy.i0 + r) * d;
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      float d = 0.0f;
+      d += rr > 0 ? v[1][c] : v[0][c];
+      d -= v[0][c];
       if (c < nx) ay += span_overlap(sx, sx.i0 + c) * d;
     }
     ax *= 2.0f * g.inv_bw;

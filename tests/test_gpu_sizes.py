@@ -180,3 +180,38 @@ def test_stateless_wirelength_sizes(F, m, degs):
         if deg[e] >= 2:
             hit[cells[net_of == e]] = True
     assert np.array_equal(np.isnan(host(ax)), hit)
+
+
+# the standalone gather's fast forms (a row's bins in one load: up to three bins
+# wide and two high, away from the last columns) and its loops, grids too narrow
+# for the wide loads, and one map after the other from 524288 cells at n >= 1024
+@pytest.mark.parametrize("mode", ["field", "exact"])
+@pytest.mark.parametrize("m,n", [(1, 1), (300, 3), (300, 4), (2000, 37), (524287, 1024),
+                                 (524288, 1024), (524545, 1030)])
+def test_field_gather_sizes(F, mode, m, n):
+    import torch
+    inst = gen.make_instance((94, m, n), num_cells=m, util=0.7, n=n, num_nets=0)
+    rng = np.random.default_rng((95, m, n))
+    # unit bins and dyadic edges, so that float32 and the oracle see the same bins:
+    # edges on and off bin edges, cells over and past the border, up to six bins
+    w, h = (rng.integers(1, 75, m) / 32 for _ in range(2))
+    x, y = (rng.integers(0, 64 * n, m) / 64 for _ in range(2))
+    k = min(m, 4000)
+    w[:k], h[:k] = rng.integers(1, 6, k), rng.integers(1, 6, k)
+    x[:k] = rng.integers(-1, n + 2, k) + 0.5 * rng.integers(0, 2, k)
+    y[:k] = rng.integers(-1, n + 2, k) + 0.5 * rng.integers(0, 2, k)
+    x, y, w, h = (np.asarray(a, np.float32) for a in (x, y, w, h))
+    inst = dataclasses.replace(inst, x=x, y=y, w=w, h=h, xl=0.0, yl=0.0, bin_w=1.0, bin_h=1.0)
+    ex, ey, psi = (rng.standard_normal((n, n)).astype(np.float32) for _ in range(3))
+    c = DeviceCells(inst)
+    gx, gy = torch.full((m,), 7.0, device="cuda"), torch.full((m,), -3.0, device="cuda")
+    say("gather", mode, m, n)
+    for accumulate in (0, 1):
+        F.field_gather(F.Grid.of(inst), c.x, c.y, c.w, c.h, dev(ex.ravel()), dev(ey.ravel()),
+                       dev(psi.ravel()), mode, 0.5, accumulate, gx, gy)
+    torch.cuda.synchronize()
+    if mode == "field":
+        rx, ry = oracle.field_gradient(inst, ex.astype(np.float64), ey.astype(np.float64))
+    else:
+        rx, ry = oracle.exact_gradient(inst, psi.astype(np.float64))
+    assert rel_l2(host(gx), rx) < RTOL and rel_l2(host(gy), ry) < RTOL
