@@ -129,7 +129,7 @@ __global__ void __launch_bounds__(NTA) k_band_accum(BandBatch<NB> bb) {
   __shared__ unsigned long long acc[BINS];
   __shared__ WalkLds<NTA, KB> lds;
   const int t = threadIdx.x;
-  const int n = g.n, R = L.rows, band = blockIdx.x, r0 = band * R;
+  const int n = g.n, R = L.rows, band = xcd_order(blockIdx.x, gridDim.x), r0 = band * R;
   const int cells = min(R, n - r0) * n;
   for (int k = t; k < cells; k += NTA) acc[k] = 0ull;
   __syncthreads();
@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(NTG) k_band_gather(BandBatch<NB> bb) {
   __shared__ int64_t start[NTG];
   __shared__ unsigned short owner[NTG * B];
   const int t = threadIdx.x;
-  const int n = g.n, R = L.rows, band = blockIdx.x;
+  const int n = g.n, R = L.rows, band = xcd_order(blockIdx.x, gridDim.x);
   const int r0 = band * R, nr = min(R + 1, n - r0);
   if (MODE == FFTPL_GRAD_FIELD) {
     // all of a thread's loads issued before its LDS stores

@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(NT, 6) k_compact_mid(CompactBatch<NB> cb,
   MidLds<N>& lds = *reinterpret_cast<MidLds<N>*>(smem);
   const int t = threadIdx.x;
   const GridF& g = q.g;
-  const int n = g.n, R = q.rows, band = blockIdx.x, r0 = band * R;
+  const int n = g.n, R = q.rows, band = xcd_order(blockIdx.x, cb.nb), r0 = band * R;
   const int bins = min(R, n - r0) * n;
   const size_t o = (size_t)r0 * n;
   // fixed charge and capacity of the thread's bins, in flight during the scatter

@@ -393,8 +393,8 @@ int xch_build(const XchDims& d, const int32_t* net_ptr, const int32_t* pin_cell,
 // ---------------------------------------------------------------------------
 namespace {
 
-// T[a] = (x, y) of pin a's cell, over part blockIdx.x % kXchSpreadSplit of
-// the A range of cell block blockIdx.x / kXchSpreadSplit.
+// T[a] = (x, y) of pin a's cell, over part b % kXchSpreadSplit of the A range of
+// cell block b / kXchSpreadSplit, b = xcd_order of the block.
 template <int NB>
 __global__ void __launch_bounds__(NT) k_xch_spread(XchBatch<NB> xb) {
   // design blockIdx.y of the batch; blocks past its cell blocks idle
@@ -407,7 +407,8 @@ __global__ void __launch_bounds__(NT) k_xch_spread(XchBatch<NB> xb) {
   const float* __restrict__ y = rq.y;
   float2* __restrict__ T = rq.T;
   __shared__ float2 win[kXchCells];
-  const int cb = blockIdx.x / kXchSpreadSplit, part = blockIdx.x % kXchSpreadSplit;
+  const int sb = xcd_order(blockIdx.x, rq.ncb * kXchSpreadSplit);
+  const int cb = sb / kXchSpreadSplit, part = sb % kXchSpreadSplit;
   const int t = threadIdx.x;
   const int c0 = cb * cpb;
   const int nc = min(cpb, m - c0);
@@ -464,7 +465,7 @@ __global__ void __launch_bounds__(NW) k_xch_wa(XchBatch<NB> xb) {
   extern __shared__ float2 smem[];
   const XchReq& rq = xb.r[blockIdx.y];
   if ((int)blockIdx.x >= rq.nnb) return;
-  wa_block<STAGE, LSE, DIRECT>(rq, blockIdx.x, smem);
+  wa_block<STAGE, LSE, DIRECT>(rq, xcd_order(blockIdx.x, rq.nnb), smem);
 }
 
 // The gradient of every cell (CellGradArgs): its density part plus the sum
