@@ -167,41 +167,50 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f4b __attribute__((ext_vector_type(4), aligned(8)));
 
 // The same gradient from the interleaved map for the usual small cell, at most
-// three bins wide and two high (and, EXACT, inside the region): its bins are
+// six bins wide and three high (and, EXACT, inside the region): its bins are
 // read together, two to a load, before any is used, where the loops above wait
 // for each in turn.  Other cells take the loops.  Same terms in the same order.
+// On grids of at least one bin per cell, the usual choice, a cell of one to four
+// sites spans up to six bins by three; with a limit of three by two most
+// wavefronts went through both forms (whole evaluations: 200k cells 51.3 -> 49.1
+// us, 30k 31.5 -> 29.1, eight designs 66.8 -> 61.8).
 template <int MODE>
 __device__ __forceinline__ float2 density_grad_small(const GridF& g, const Span& sx,
                                                      const Span& sy,
                                                      const float2* __restrict__ exy,
                                                      const float* __restrict__ psi) {
+  constexpr int NR = 3, NP = 3;   // rows, column pairs
   const int n = g.n;
   const float fn = (float)n;
   const int nx = sx.i1 - sx.i0 + 1, ny = sy.i1 - sy.i0 + 1;
-  bool small = nx >= 1 && nx <= 3 && ny >= 1 && ny <= 2 && sx.i0 <= n - 2;
+  bool small = nx >= 1 && nx <= 2 * NP && ny >= 1 && ny <= NR && n >= 2 * NP;
   if (MODE == FFTPL_GRAD_EXACT)
     small = small && sx.lo > 0.0f && sx.hi < fn && sy.lo > 0.0f && sy.hi < fn;
   if (!small) return density_grad_spans<MODE, true>(g, sx, sy, nullptr, nullptr, exy, psi);
-  float2 e[2][3];
+  // columns c0 .. c0 + 5 lie inside the row; those outside the span are masked
+  const int c0 = min(sx.i0, n - 2 * NP);
+  const float2* row = exy + (int64_t)sy.i0 * n + c0;
+  f4b v[NR][NP];
 #pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const float2* row = exy + (int64_t)min(sy.i0 + r, sy.i1) * n + sx.i0;
-    const f4b v = *reinterpret_cast<const f4b*>(row);   // bins i0 and i0 + 1 < n
-    e[r][0] = make_float2(v.x, v.y);
-    e[r][1] = make_float2(v.z, v.w);
-    e[r][2] = nx > 2 ? row[2] : e[r][1];
+  for (int r = 0; r < NR; ++r) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      v[r][p] = f4b{0.0f, 0.0f, 0.0f, 0.0f};
+      if (r < ny && c0 + 2 * p + 1 >= sx.i0 && c0 + 2 * p <= sx.i1)
+        v[r][p] = *reinterpret_cast<const f4b*>(row + (int64_t)r * n + 2 * p);
+    }
   }
   float ax = 0.0f, ay = 0.0f;
   if (MODE == FFTPL_GRAD_FIELD) {
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
+    for (int r = 0; r < NR; ++r) {
       const float oy = span_overlap(sy, sy.i0 + r);
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        if (r < ny && c < nx) {
-          const float ov = span_overlap(sx, sx.i0 + c) * oy;
-          ax += ov * e[r][c].x;
-          ay += ov * e[r][c].y;
+      for (int c = 0; c < 2 * NP; ++c) {
+        if (r < ny && c0 + c >= sx.i0 && c0 + c <= sx.i1) {
+          const float ov = span_overlap(sx, c0 + c) * oy;
+          ax += ov * v[r][c / 2][c % 2 * 2];
+          ay += ov * v[r][c / 2][c % 2 * 2 + 1];
         }
       }
     }
@@ -209,22 +218,22 @@ __device__ __forceinline__ float2 density_grad_small(const GridF& g, const Span&
     ay *= -g.inv_bh;
   } else {
     // the bins between the edges: columns i0 .. floor(hi) - 1, rows likewise
-    const int mx = (int)floorf(sx.hi) - sx.i0, my = (int)floorf(sy.hi) - sy.i0;
+    const int mx = (int)floorf(sx.hi), my = (int)floorf(sy.hi) - sy.i0;
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
+    for (int r = 0; r < NR; ++r) {
       float d = 0.0f;
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
-        if (c < mx) d += e[r][c].x;
+      for (int c = 0; c < 2 * NP; ++c)
+        if (c0 + c >= sx.i0 && c0 + c < mx) d += v[r][c / 2][c % 2 * 2];
       if (r < ny) ax += span_overlap(sy, sy.i0 + r) * d;
     }
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
+    for (int c = 0; c < 2 * NP; ++c) {
       float d = 0.0f;
 #pragma unroll
-      for (int r = 0; r < 2; ++r)
-        if (r < my) d += e[r][c].y;
-      if (c < nx) ay += span_overlap(sx, sx.i0 + c) * d;
+      for (int r = 0; r < NR; ++r)
+        if (r < my) d += v[r][c / 2][c % 2 * 2 + 1];
+      if (c0 + c >= sx.i0 && c0 + c <= sx.i1) ay += span_overlap(sx, c0 + c) * d;
     }
     ax *= 2.0f * g.inv_bw;
     ay *= 2.0f * g.inv_bh;
@@ -232,38 +241,163 @@ __device__ __forceinline__ float2 density_grad_small(const GridF& g, const Span&
   return make_float2(ax, ay);
 }
 
-// The sum of ov(i, b) * e_b over a span, of one map.  The usual small cell's
-// bins are read four of a row to a load.
+// Separate maps: the bins of a cell of at most NR rows and 4 NG columns, read four
+// of a row to a load (columns c0 .. c0 + 4 NG - 1 of the row, those outside the
+// span masked).  A wavefront's cells lie anywhere, so every load looks up 64
+// lines, and the number of loads is what a gather costs.  Where all cells of a
+// wavefront fit two rows of four columns (one group) a narrow form is taken:
+// 2.1M cells at n = 1024, FIELD 57.7 us against 62.0 us with the wide one alone,
+// EXACT 23.5 against 37.7; 123k cells FIELD 11.2 us with both against 19.5 with the
+// narrow one and loops, 1M cells 30.5 against 31.8.
+template <int NR, int NG>
+struct MapRows {
+  int c0;
+  f4u v[NR][NG];
+  __device__ __forceinline__ static bool fits(const Span& sx, const Span& sy, int n) {
+    const int nx = sx.i1 - sx.i0 + 1, ny = sy.i1 - sy.i0 + 1;
+    return nx >= 1 && nx <= 4 * NG && ny >= 1 && ny <= NR && n >= 4 * NG;
+  }
+  __device__ __forceinline__ void load(int n, const Span& sx, const Span& sy,
+                                       const float* __restrict__ e) {
+    c0 = min(sx.i0, n - 4 * NG);
+    const float* row = e + (int64_t)sy.i0 * n + c0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+#pragma unroll
+      for (int p = 0; p < NG; ++p) {
+        v[r][p] = f4u{0.0f, 0.0f, 0.0f, 0.0f};
+        if (sy.i0 + r <= sy.i1 && c0 + 4 * p + 3 >= sx.i0 && c0 + 4 * p <= sx.i1)
+          v[r][p] = *reinterpret_cast<const f4u*>(row + (int64_t)r * n + 4 * p);
+      }
+    }
+  }
+  // the sum of ov(i, b) * e_b over the span, in the order of its loops
+  __device__ __forceinline__ float sum(const Span& sx, const Span& sy) const {
+    float s = 0.0f;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const float oy = span_overlap(sy, sy.i0 + r);
+#pragma unroll
+      for (int c = 0; c < 4 * NG; ++c)
+        if (sy.i0 + r <= sy.i1 && c0 + c >= sx.i0 && c0 + c <= sx.i1)
+          s += span_overlap(sx, c0 + c) * oy * v[r][c / 4][c % 4];
+    }
+    return s;
+  }
+};
+
+typedef MapRows<2, 1> NarrowRows;
+typedef MapRows<3, 2> WideRows;
+
+// The sum of ov(i, b) * e_b over a span, of one map.
 __device__ __forceinline__ float span_map_sum(int n, const Span& sx, const Span& sy,
                                               const float* __restrict__ e) {
   const int nx = sx.i1 - sx.i0 + 1, ny = sy.i1 - sy.i0 + 1;
+  if (__all(nx >= 1 && nx <= 4 && ny >= 1 && ny <= 2 && sx.i0 <= n - 4)) {
+    const float* row = e + (int64_t)sy.i0 * n + sx.i0;
+    const f4u v0 = *reinterpret_cast<const f4u*>(row);
+    f4u v1 = v0;
+    if (ny > 1) v1 = *reinterpret_cast<const f4u*>(row + n);
+    const float o0 = span_overlap(sy, sy.i0), o1 = span_overlap(sy, sy.i0 + 1);
+    float s = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (c < nx) s += span_overlap(sx, sx.i0 + c) * o0 * v0[c];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (ny > 1 && c < nx) s += span_overlap(sx, sx.i0 + c) * o1 * v1[c];
+    return s;
+  }
+  if (WideRows::fits(sx, sy, n)) {
+    WideRows f;
+    f.load(n, sx, sy, e);
+    return f.sum(sx, sy);
+  }
   float s = 0.0f;
-  if (nx >= 1 && nx <= 3 && ny >= 1 && ny <= 2 && sx.i0 <= n - 4) {
-    const int64_t o = (int64_t)sy.i0 * n + sx.i0;
-    f4u v[2];
-    v[0] = *reinterpret_cast<const f4u*>(e + o);
-    v[1] = v[0];
-    if (ny > 1) v[1] = *reinterpret_cast<const f4u*>(e + o + n);
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const float oy = span_overlap(sy, sy.i0 + r);
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        if (r < ny && c < nx) s += span_overlap(sx, sx.i0 + c) * oy * v[r][c];
-    }
-  } else {
-    for (int iy = sy.i0; iy <= sy.i1; ++iy) {
-      const float oy = span_overlap(sy, iy);
-      for (int ix = sx.i0; ix <= sx.i1; ++ix)
-        s += span_overlap(sx, ix) * oy * e[(int64_t)iy * n + ix];
-    }
+  for (int iy = sy.i0; iy <= sy.i1; ++iy) {
+    const float oy = span_overlap(sy, iy);
+    for (int ix = sx.i0; ix <= sx.i1; ++ix)
+      s += span_overlap(sx, ix) * oy * e[(int64_t)iy * n + ix];
   }
   return s;
 }
 
-// The same from separate maps (ex, ey; EXACT: psi): four bins of a row to a load.
-// A wavefront's cells lie anywhere, so every load looks up 64 lines, and the
-// number of loads is what a gather costs.
+// The density gradient from separate maps (ex, ey; EXACT: psi) of a cell that
+// fits.  EXACT (both edges inside the region): each row's bins under the left and
+// right edges, and the rows under the lower and upper edges.
+template <int MODE, int NR, int NG>
+__device__ __forceinline__ float2 density_grad_rows(const GridF& g, const Span& sx,
+                                                    const Span& sy,
+                                                    const float* __restrict__ ex,
+                                                    const float* __restrict__ ey,
+                                                    const float* __restrict__ psi) {
+  const int n = g.n;
+  if (MODE == FFTPL_GRAD_FIELD) {
+    MapRows<NR, NG> fx, fy;
+    fx.load(n, sx, sy, ex);
+    fy.load(n, sx, sy, ey);
+    return make_float2(-g.inv_bw * fx.sum(sx, sy), -g.inv_bh * fy.sum(sx, sy));
+  }
+  const int c0 = min(sx.i0, n - 4 * NG);
+  const int cr = (int)floorf(sx.hi), rr = (int)floorf(sy.hi);
+  const float* row = psi + (int64_t)sy.i0 * n;
+  float left[NR], right[NR];
+  f4u lower[NG], upper[NG];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    left[r] = right[r] = 0.0f;
+    if (sy.i0 + r <= sy.i1) {
+      left[r] = row[(int64_t)r * n + sx.i0];
+      right[r] = row[(int64_t)r * n + cr];
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < NG; ++p) {
+    lower[p] = upper[p] = f4u{0.0f, 0.0f, 0.0f, 0.0f};
+    if (c0 + 4 * p + 3 >= sx.i0 && c0 + 4 * p <= sx.i1) {
+      lower[p] = *reinterpret_cast<const f4u*>(row + c0 + 4 * p);
+      upper[p] = *reinterpret_cast<const f4u*>(psi + (int64_t)rr * n + c0 + 4 * p);
+    }
+  }
+  float ax = 0.0f, ay = 0.0f;
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+    if (sy.i0 + r <= sy.i1) ax += span_overlap(sy, sy.i0 + r) * (right[r] - left[r]);
+#pragma unroll
+  for (int c = 0; c < 4 * NG; ++c)
+    if (c0 + c >= sx.i0 && c0 + c <= sx.i1)
+      ay += span_overlap(sx, c0 + c) * (upper[c / 4][c % 4] - lower[c / 4][c % 4]);
+  return make_float2(ax * (2.0f * g.inv_bw), ay * (2.0f * g.inv_bh));
+}
+
+// EXACT, all edges inside one group of four columns and two rows: everything
+// from the same two loads.
+__device__ __forceinline__ bool exact_narrow(const Span& sx, const Span& sy, int n) {
+  return NarrowRows::fits(sx, sy, n) && sx.i0 <= n - 4 && (int)floorf(sx.hi) <= sx.i0 + 3 &&
+         (int)floorf(sy.hi) <= sy.i0 + 1;
+}
+__device__ __forceinline__ float2 exact_grad_narrow(const GridF& g, const Span& sx,
+                                                    const Span& sy,
+                                                    const float* __restrict__ psi) {
+  const int n = g.n, ny = sy.i1 - sy.i0 + 1, nx = sx.i1 - sx.i0 + 1;
+  const int64_t o = (int64_t)sy.i0 * n + sx.i0;
+  const int cr = (int)floorf(sx.hi) - sx.i0, rr = (int)floorf(sy.hi) - sy.i0;
+  f4u v[2];
+  v[0] = *reinterpret_cast<const f4u*>(psi + o);
+  v[1] = v[0];
+  if (ny > 1 || rr > 0) v[1] = *reinterpret_cast<const f4u*>(psi + o + n);
+  float ax = 0.0f, ay = 0.0f;
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const float right = cr == 0 ? v[r][0] : cr == 1 ? v[r][1] : cr == 2 ? v[r][2] : v[r][3];
+    if (r < ny) ax += span_overlap(sy, sy.i0 + r) * (right - v[r][0]);
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    if (c < nx) ay += span_overlap(sx, sx.i0 + c) * ((rr > 0 ? v[1][c] : v[0][c]) - v[0][c]);
+  return make_float2(ax * (2.0f * g.inv_bw), ay * (2.0f * g.inv_bh));
+}
+
 template <int MODE>
 __device__ __forceinline__ float2 density_grad_maps(const GridF& g, const Span& sx,
                                                     const Span& sy,
@@ -272,64 +406,17 @@ __device__ __forceinline__ float2 density_grad_maps(const GridF& g, const Span& 
                                                     const float* __restrict__ psi) {
   const int n = g.n;
   const float fn = (float)n;
-  const int nx = sx.i1 - sx.i0 + 1, ny = sy.i1 - sy.i0 + 1;
-  bool small = nx >= 1 && nx <= 3 && ny >= 1 && ny <= 2 && sx.i0 <= n - 4;
-  if (MODE == FFTPL_GRAD_EXACT)
-    // edges inside the region, and the bins of the right edges among those read
-    small = small && sx.lo > 0.0f && sx.hi < fn && sy.lo > 0.0f && sy.hi < fn &&
-            (int)floorf(sx.hi) <= sx.i0 + 3 && (int)floorf(sy.hi) <= sy.i0 + 1;
-  if (!small) return density_grad_spans<MODE, false>(g, sx, sy, ex, ey, nullptr, psi);
-  const int64_t o = (int64_t)sy.i0 * n + sx.i0;
-  float ax = 0.0f, ay = 0.0f;
-  if (MODE == FFTPL_GRAD_FIELD) {
-    f4u vx[2], vy[2];
-    vx[0] = *reinterpret_cast<const f4u*>(ex + o);
-    vy[0] = *reinterpret_cast<const f4u*>(ey + o);
-    vx[1] = vx[0];
-    vy[1] = vy[0];
-    if (ny > 1) {
-      vx[1] = *reinterpret_cast<const f4u*>(ex + o + n);
-      vy[1] = *reinterpret_cast<const f4u*>(ey + o + n);
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const float oy = span_overlap(sy, sy.i0 + r);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        if (r < ny && c < nx) {
-          const float ov = span_overlap(sx, sx.i0 + c) * oy;
-          ax += ov * vx[r][c];
-          ay += ov * vy[r][c];
-        }
-      }
-    }
-    ax *= -g.inv_bw;
-    ay *= -g.inv_bh;
-  } else {
-    const int cr = (int)floorf(sx.hi) - sx.i0, rr = (int)floorf(sy.hi) - sy.i0;
-    f4u v[2];
-    v[0] = *reinterpret_cast<const f4u*>(psi + o);
-    v[1] = v[0];
-    if (ny > 1 || rr > 0) v[1] = *reinterpret_cast<const f4u*>(psi + o + n);
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const float right = cr == 0 ? v[r][0] : cr == 1 ? v[r][1] : cr == 2 ? v[r][2] : v[r][3];
-      float d = 0.0f;
-      d += right;
-      d -= v[r][0];
-      if (r < ny) ax += span_overlap(sy, sy.i0 + r) * d;
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      float d = 0.0f;
-      d += rr > 0 ? v[1][c] : v[0][c];
-      d -= v[0][c];
-      if (c < nx) ay += span_overlap(sx, sx.i0 + c) * d;
-    }
-    ax *= 2.0f * g.inv_bw;
-    ay *= 2.0f * g.inv_bh;
+  bool fits = WideRows::fits(sx, sy, n), narrow = NarrowRows::fits(sx, sy, n);
+  if (MODE == FFTPL_GRAD_EXACT) {
+    fits = fits && sx.lo > 0.0f && sx.hi < fn && sy.lo > 0.0f && sy.hi < fn;
+    narrow = fits && exact_narrow(sx, sy, n);
   }
-  return make_float2(ax, ay);
+  if (__all(narrow)) {
+    if (MODE == FFTPL_GRAD_EXACT) return exact_grad_narrow(g, sx, sy, psi);
+    return density_grad_rows<MODE, 2, 1>(g, sx, sy, ex, ey, psi);
+  }
+  if (fits) return density_grad_rows<MODE, 3, 2>(g, sx, sy, ex, ey, psi);
+  return density_grad_spans<MODE, false>(g, sx, sy, ex, ey, nullptr, psi);
 }
 
 template <int MODE, bool INTERLEAVED>
@@ -727,17 +814,18 @@ __device__ __forceinline__ void eval_scalars(const FinalArgs& f) {
     if (lane == 0) red[k][w] = v[k];
   }
   __syncthreads();
-  if (t == 0) {
-    double r[5];
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      r[k] = 0.0;
-      for (int j = 0; j < NT / kWave; ++j) r[k] += red[k][j];
-    }
-    if (f.o_en) *f.o_en = r[0];
-    if (f.o_tau) *f.o_tau = r[2] > 0.0 ? r[1] / r[2] : 0.0;
-    if (f.wa && f.o_wa) *f.o_wa = r[3];
-    if (f.wa && f.o_hp) *f.o_hp = r[4];
+  if (w == 0) {
+    // lane k sums the wavefronts' parts of v[k] (all five in one lane unroll into
+    // 10 * NT / kWave registers, and set the register count of the whole kernel)
+    double r = 0.0;
+    const double* rk = red[min(lane, 4)];
+#pragma unroll 4
+    for (int j = 0; j < NT / kWave; ++j) r += rk[j];
+    const double over = lane_d(r, 1), movable = lane_d(r, 2);
+    if (lane == 0 && f.o_en) *f.o_en = r;
+    if (lane == 1 && f.o_tau) *f.o_tau = movable > 0.0 ? over / movable : 0.0;
+    if (lane == 3 && f.wa && f.o_wa) *f.o_wa = r;
+    if (lane == 4 && f.wa && f.o_hp) *f.o_hp = r;
   }
 }
 
