@@ -691,13 +691,16 @@ int run_compact_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream_
   BandReq br[kMaxBatch];
   CompactReq cr[kMaxBatch];
   SpectralArgs sa[kMaxBatch];
-  bool place = false;
+  bool place = false, spread = false;
+  for (int i = 0; i < count; ++i)
+    spread = spread || compact_spreads(p, rs[i].xd.m);
   for (int i = 0; i < count; ++i) {
     const EvalReq& r = rs[i];
     const bool scan = r.xd.m <= kCompactScanCells;
     br[i].g = r.g;
     br[i].L = r.L;
     br[i].L.epos = nullptr;   // the gradient is gathered per cell
+    if (spread) br[i].L.xy = nullptr;   // (the spread reads x and y)
     if (scan)
       br[i].L.m = 0;
     else
@@ -734,11 +737,17 @@ int run_compact_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream_
     if (!scan) q.x.xy = r.L.xy;   // the place pass interleaves the positions
   }
   hipError_t e = hipSuccess;
-  if (place) {
+  if (spread) {
+    XchReq xr[kMaxBatch];
+    for (int i = 0; i < count; ++i) xr[i] = cr[i].x;
+    e = launch_compact_place(br, xr, count, s);
+    plan_mark(p, "k_compact_place", s);
+  } else if (place) {
     e = launch_band_place_batch(br, count, s);
     plan_mark(p, "k_band_place", s);
   }
-  if (e == hipSuccess) e = launch_compact_mid(p, cr, count, rs[0].prob->wl_model, fuse, s);
+  if (e == hipSuccess)
+    e = launch_compact_mid(p, cr, count, rs[0].prob->wl_model, fuse, spread, s);
   plan_mark(p, "k_compact_mid", s);
   if (e == hipSuccess) {
     if (p.mode == FFTPL_DCT_FFT) {
@@ -1086,7 +1095,7 @@ static int problem_wl(const fftpl_problem* prob, const float* x, const float* y,
   xr.net_wl = net_wl;
   xr.net_hp = net_hp;
   // positions straight from x, y where the compact evaluation reads them so
-  const bool direct = m > 0 && compact_design(1, xd);
+  const bool direct = m > 0 && m <= kCompactDirectCells && compact_design(1, xd);
   hipError_t e = direct ? hipSuccess : launch_xch_spread_batch(&xr, 1, s);
   if (e == hipSuccess) e = launch_xch_wa_batch(&xr, 1, prob->wl_model, s, direct);
   if (net_wl) return dev_status(e);

@@ -8,22 +8,25 @@
 // device evaluating.  Here the same steps take five launches on the caller's
 // stream alone (four for the smallest designs):
 //   place  the counting sort of the cells by band (k_band_place), skipped up to
-//          kCompactScanCells cells, whose band blocks read every cell;
+//          kCompactScanCells cells, whose band blocks read every cell; past
+//          kCompactDirectCells with the spread beside it (k_compact_place);
 //   mid    band blocks: scatter of a row pair, and for FFT plans its row transform
-//          straight from LDS; beside them in the same launch the net blocks, which
-//          read the positions by cell (they fit the L2 of every XCD), so that
-//          neither a spread nor a second stream is needed;
+//          straight from LDS (past n = 512 of up to four rows, the row pass on its
+//          own); beside them in the same launch the net blocks, which read the
+//          positions by cell where they fit the L2 of every XCD, so that neither
+//          a spread nor a second stream is needed;
 //   solve  the column and the inverse row pass (or the matrix-core solve);
 //   cells  per cell the density gradient gathered from the field map (it fits the
-//          L2 too) and the sum of its pins' gradients; one more block per design
-//          sums the scalars.
+//          L2 too, or nearly) and the sum of its pins' gradients; one more block
+//          per design sums the scalars.
 // Every per-cell, per-bin and per-net value is computed by the same code and
 // in the same order as on the general path.
 // Per evaluation, general -> compact, one after another: 2k cells (n = 64) 77.8
-// -> 22.6 us, 30k (n = 256, exact, LSE) 71.5 -> 32.9, 200k (n = 512) 78.3 -> 54.5,
-// 500k (n = 512) 136 -> 101 (with its scalars-only twin), eight of 17k to 62k
-// cells in a batch 172 -> 75.  What bounds it now is the device: at 200k cells
-// place 7, mid 23, columns 7, inverse rows 6, cells 13 us.
+// -> 20.3 us, 30k (n = 256, exact, LSE) 71.5 -> 29.1, 200k (n = 512) 78.3 -> 49.1,
+// 300k (n = 1024, clustered) 105 -> 82, 500k (n = 1024) 102 -> 94, eight of 17k to
+// 62k cells in a batch 172 -> 62.  What bounds it now is the device: at 200k cells
+// place 6, mid 17, columns 7, inverse rows 6, cells 8 us; at 500k place 11, mid 30,
+// rows 9, columns 13, inverse rows 10, cells 19.
 #include <algorithm>
 
 #include "band_device.hpp"
@@ -37,13 +40,14 @@ namespace {
 constexpr int NT = kXchWaThreads;   // the net blocks' threads, and the band blocks'
 constexpr int KB = 4;               // band entries a thread takes together
 constexpr int kList = 4 * NT;       // cells of a scanning band block's list
-constexpr int kBins = 2 * kCompactMaxN;
+// bins of a band: a row pair for n <= 512, up to four rows above
+constexpr int kBinsPair = 2 * kCompactPairN, kBinsMax = 4096;
 
 // LDS of a band block: the accumulators, then the scatter's arrays or the
 // row transform's (N = 0: no transform).
-template <int N>
+template <int N, int BINS>
 struct MidLds {
-  unsigned long long acc[kBins];
+  unsigned long long acc[BINS];
   union {
     WalkLds<NT, KB> walk;
     ScanLds<NT, kList> scan;
@@ -51,9 +55,36 @@ struct MidLds {
   };
 };
 
+// The place pass and, beside it in the same launch, the spread of the positions to
+// the pins: past kCompactDirectCells the positions and the rest of a net block's
+// data no longer fit an XCD's L2 together, and reading them by pin costs more
+// than the spread (net blocks of 500k cells, n = 1024: 34 us against 17 us).
+constexpr int kPlaceCells = 4;   // most cells per thread of a place block
+template <int NB>
+struct PlaceBatch {
+  int nblk = 0;
+  BandReq r[NB];
+  XchReq x[NB];
+};
+template <int NB>
+__global__ void __launch_bounds__(kBandThreads) k_compact_place(PlaceBatch<NB> pb) {
+  __shared__ float2 win[kCompactMaxCpb];
+  const int b = (int)blockIdx.x - pb.nblk;
+  if (b < 0) {
+    const BandReq& q = pb.r[blockIdx.y];
+    if (q.L.m > 0 && (int)blockIdx.x < q.L.nblk)
+      place_block<kPlaceCells>(q.g, q.L, blockIdx.x, q.x, q.y, q.w, q.h);
+    return;
+  }
+  const XchReq& rq = pb.x[blockIdx.y];
+  const int nb = rq.ncb * kXchSpreadSplit;
+  if (b < nb)
+    spread_part<kBandThreads, kCompactMaxCpb, kXchSpreadSplit>(rq, xcd_order(b, nb), win);
+}
+
 // Six wavefronts per SIMD: three blocks of 512 threads per CU instead of the
 // two that 94 registers leave (27.7 -> 23.9 us at 200k cells).
-template <int N, bool LSE, int NB>
+template <int N, int BINS, bool LSE, bool DIRECT, int NB>
 __global__ void __launch_bounds__(NT, 6) k_compact_mid(CompactBatch<NB> cb,
                                                     const float2* __restrict__ tw_g,
                                                     const float2* __restrict__ cs_g) {
@@ -61,17 +92,17 @@ __global__ void __launch_bounds__(NT, 6) k_compact_mid(CompactBatch<NB> cb,
   const CompactReq& q = cb.r[blockIdx.y];
   if ((int)blockIdx.x >= cb.nb) {
     const int k = (int)blockIdx.x - cb.nb;
-    if (k < q.x.nnb) wa_block<kStageS, LSE, true>(q.x, k, smem);
+    if (k < q.x.nnb) wa_block<kStageS, kStageHold, LSE, DIRECT>(q.x, k, smem);
     return;
   }
-  MidLds<N>& lds = *reinterpret_cast<MidLds<N>*>(smem);
+  MidLds<N, BINS>& lds = *reinterpret_cast<MidLds<N, BINS>*>(smem);
   const int t = threadIdx.x;
   const GridF& g = q.g;
   const int n = g.n, R = q.rows, band = xcd_order(blockIdx.x, cb.nb), r0 = band * R;
   const int bins = min(R, n - r0) * n;
   const size_t o = (size_t)r0 * n;
   // fixed charge and capacity of the thread's bins, in flight during the scatter
-  constexpr int PA = kBins / NT;
+  constexpr int PA = BINS / NT;
   float bv[PA], cv[PA];
 #pragma unroll
   for (int j = 0; j < PA; ++j) bv[j] = q.base ? q.base[o + min(t + j * NT, bins - 1)] : 0.0f;
@@ -88,7 +119,7 @@ __global__ void __launch_bounds__(NT, 6) k_compact_mid(CompactBatch<NB> cb,
   for (int k = t; k < bins; k += NT) lds.acc[k] = 0ull;
   __syncthreads();
   if (q.nblk > 0)
-    band_accumulate<NT, KB, true>(g, q, band, q.x.x, q.x.y, q.w, q.h, lds.acc, lds.walk);
+    band_accumulate<NT, KB, BINS == kBinsPair>(g, q, band, q.x.x, q.x.y, q.w, q.h, lds.acc, lds.walk);
   else
     band_scan<NT, kList>(g, q, band, q.x.x, q.x.y, q.w, q.h, lds.acc, lds.scan);
   __syncthreads();
@@ -102,7 +133,7 @@ __global__ void __launch_bounds__(NT, 6) k_compact_mid(CompactBatch<NB> cb,
   if constexpr (N > 0) {
     // the row pair's transform: rows of N = 512 lie one sample per thread as
     // they are; shorter rows go back through LDS
-    static_assert(N <= NT && kBins / NT == 2, "one sample of each row per thread");
+    static_assert(N <= NT && PA == 2, "one sample of each row per thread");
     float a1[1], a2[1], b1[1], b2[1], c1[1], c2[1];
     stage_tables<N, NT, false>(lds.rows.tw, tw_g, lds.rows.cs, cs_g, nullptr, nullptr, t);
     if constexpr (N == NT) {
@@ -138,10 +169,12 @@ __global__ void __launch_bounds__(NT, 6) k_compact_mid(CompactBatch<NB> cb,
   }
 }
 
-// TC threads, PC cells per thread: (256, 1), (512, 1), (512, 2) or (512, 4), the smallest
-// that holds a cell block.  A block of one cell per thread is a short chain of
-// loads, and its registers and LDS leave room for several blocks per CU (eight
-// designs of up to 62k cells 22.3 -> 17.1 us).
+// TC threads, PC cells per thread: (256, 1), (512, 1), (1024, 1) or (1024, 2), the
+// smallest that holds a cell block.  A block of one cell per thread is a short
+// chain of loads, and its registers and LDS leave room for several blocks per CU
+// (eight designs of up to 62k cells 22.3 -> 17.1 us); the largest blocks, one per
+// CU, take 1024 threads for the map reads in flight (500k cells, n = 1024: 25.0 ->
+// 20.4 us against (512, 4)).
 template <int MODE, int NB, int TC, int PC>
 __global__ void __launch_bounds__(TC) k_compact_cells(SumBatch<NB> sb) {
   const SumReq& rq = sb.r[blockIdx.y];
@@ -196,33 +229,60 @@ __global__ void __launch_bounds__(TC) k_compact_cells(SumBatch<NB> sb) {
   }
 }
 
-template <int N, bool LSE, int NB>
+template <int NB>
+hipError_t place_batch(const BandReq* br, const XchReq* xr, int count, hipStream_t s) {
+  PlaceBatch<NB> pb;
+  static_assert(sizeof(pb) <= 4096, "kernel arguments");
+  int max_nblk = 0, max_ncb = 0;
+  for (int i = 0; i < count; ++i) {
+    pb.r[i] = br[i];
+    pb.x[i] = xr[i];
+    if (br[i].L.cpk > kPlaceCells * kBandThreads || xr[i].cpb > kCompactMaxCpb)
+      return hipErrorInvalidValue;
+    if (br[i].L.m > 0) max_nblk = std::max(max_nblk, br[i].L.nblk);
+    max_ncb = std::max(max_ncb, xr[i].ncb);
+  }
+  pb.nblk = max_nblk;
+  hipLaunchKernelGGL((k_compact_place<NB>), dim3(max_nblk + max_ncb * kXchSpreadSplit, count),
+                     dim3(kBandThreads), 0, s, pb);
+  return hipGetLastError();
+}
+
+template <int N, int BINS, bool LSE, bool DIRECT, int NB>
 hipError_t mid_launch(const Plan& p, const CompactBatch<NB>& cb, int max_nnb, int max_cap,
                       bool scan, hipStream_t s) {
-  using L = MidLds<N>;
+  using L = MidLds<N, BINS>;
   size_t lds = sizeof(L::acc) + std::max(sizeof(L::walk), sizeof(L::rows));
   if (scan) lds = sizeof(L);
   lds = std::max(lds, sizeof(float2) * 2 * (size_t)max_cap);
-  hipLaunchKernelGGL((k_compact_mid<N, LSE, NB>), dim3(cb.nb + max_nnb, cb.count), dim3(NT), lds,
-                     s, cb, p.fft_tw, p.dct_cs);
+  hipLaunchKernelGGL((k_compact_mid<N, BINS, LSE, DIRECT, NB>), dim3(cb.nb + max_nnb, cb.count),
+                     dim3(NT), lds, s, cb, p.fft_tw, p.dct_cs);
   return hipGetLastError();
 }
 
 template <bool LSE, int NB>
 hipError_t mid_size(const Plan& p, const CompactBatch<NB>& cb, int max_nnb, int max_cap,
-                    bool scan, bool fuse_rows, hipStream_t s) {
+                    bool scan, bool fuse_rows, bool spread, hipStream_t s) {
+  constexpr int B = kBinsPair;
+  if (p.n > kCompactPairN)
+    return spread ? mid_launch<0, kBinsMax, LSE, false, NB>(p, cb, max_nnb, max_cap, scan, s)
+                  : mid_launch<0, kBinsMax, LSE, true, NB>(p, cb, max_nnb, max_cap, scan, s);
   switch (fuse_rows ? p.n : 0) {
-    case 64: return mid_launch<64, LSE, NB>(p, cb, max_nnb, max_cap, scan, s);
-    case 128: return mid_launch<128, LSE, NB>(p, cb, max_nnb, max_cap, scan, s);
-    case 256: return mid_launch<256, LSE, NB>(p, cb, max_nnb, max_cap, scan, s);
-    case 512: return mid_launch<512, LSE, NB>(p, cb, max_nnb, max_cap, scan, s);
-    default: return mid_launch<0, LSE, NB>(p, cb, max_nnb, max_cap, scan, s);
+    case 64: return mid_launch<64, B, LSE, true, NB>(p, cb, max_nnb, max_cap, scan, s);
+    case 128: return mid_launch<128, B, LSE, true, NB>(p, cb, max_nnb, max_cap, scan, s);
+    case 256: return mid_launch<256, B, LSE, true, NB>(p, cb, max_nnb, max_cap, scan, s);
+    case 512:
+      return spread ? mid_launch<512, B, LSE, false, NB>(p, cb, max_nnb, max_cap, scan, s)
+                    : mid_launch<512, B, LSE, true, NB>(p, cb, max_nnb, max_cap, scan, s);
+    default:
+      return spread ? mid_launch<0, B, LSE, false, NB>(p, cb, max_nnb, max_cap, scan, s)
+                    : mid_launch<0, B, LSE, true, NB>(p, cb, max_nnb, max_cap, scan, s);
   }
 }
 
 template <int NB>
 hipError_t mid_batch(const Plan& p, const CompactReq* reqs, int count, int wl_model,
-                     bool fuse_rows, hipStream_t s) {
+                     bool fuse_rows, bool spread, hipStream_t s) {
   CompactBatch<NB> cb;
   cb.count = count;
   cb.nb = reqs[0].nb;
@@ -236,8 +296,8 @@ hipError_t mid_batch(const Plan& p, const CompactReq* reqs, int count, int wl_mo
   }
   if (max_cap > kXchPinLds2) return hipErrorInvalidValue;
   return wl_model == FFTPL_WL_LSE
-             ? mid_size<true, NB>(p, cb, max_nnb, max_cap, scan, fuse_rows, s)
-             : mid_size<false, NB>(p, cb, max_nnb, max_cap, scan, fuse_rows, s);
+             ? mid_size<true, NB>(p, cb, max_nnb, max_cap, scan, fuse_rows, spread, s)
+             : mid_size<false, NB>(p, cb, max_nnb, max_cap, scan, fuse_rows, spread, s);
 }
 
 template <int NB, int TC, int PC>
@@ -263,8 +323,8 @@ hipError_t cells_batch(const SumReq* reqs, int count, int grad_mode, hipStream_t
   if (max_cpb > kCompactMaxCpb) return hipErrorInvalidValue;
   if (max_cpb <= 256) return cells_launch<NB, 256, 1>(sb, max_ncb, grad_mode, s);
   if (max_cpb <= 512) return cells_launch<NB, 512, 1>(sb, max_ncb, grad_mode, s);
-  if (max_cpb <= 1024) return cells_launch<NB, 512, 2>(sb, max_ncb, grad_mode, s);
-  return cells_launch<NB, 512, kCompactMaxCpb / 512>(sb, max_ncb, grad_mode, s);
+  if (max_cpb <= 1024) return cells_launch<NB, 1024, 1>(sb, max_ncb, grad_mode, s);
+  return cells_launch<NB, 1024, kCompactMaxCpb / 1024>(sb, max_ncb, grad_mode, s);
 }
 
 }  // namespace
@@ -273,14 +333,26 @@ bool compact_design(int n, const XchDims& d) {
   return n <= kCompactMaxN && d.m > 0 && d.cpb <= kCompactMaxCpb && d.cap <= kXchPinLds2;
 }
 
-bool compact_fuses_rows(const Plan& p) { return p.mode == FFTPL_DCT_FFT && p.n >= 64; }
+bool compact_fuses_rows(const Plan& p) {
+  return p.mode == FFTPL_DCT_FFT && p.n >= 64 && p.n <= kCompactPairN;
+}
 
-hipError_t launch_compact_mid(const Plan& p, const CompactReq* reqs, int count, int wl_model,
-                              bool fuse_rows, hipStream_t s) {
+bool compact_spreads(const Plan& p, int m) {
+  return m > kCompactDirectCells && (p.n >= kCompactPairN || !compact_fuses_rows(p));
+}
+
+hipError_t launch_compact_place(const BandReq* br, const XchReq* xr, int count, hipStream_t s) {
   if (count <= 0) return hipSuccess;
   if (count > kMaxBatch) return hipErrorInvalidValue;
-  return count == 1 ? mid_batch<1>(p, reqs, count, wl_model, fuse_rows, s)
-                    : mid_batch<kMaxBatch>(p, reqs, count, wl_model, fuse_rows, s);
+  return count == 1 ? place_batch<1>(br, xr, count, s) : place_batch<kMaxBatch>(br, xr, count, s);
+}
+
+hipError_t launch_compact_mid(const Plan& p, const CompactReq* reqs, int count, int wl_model,
+                              bool fuse_rows, bool spread, hipStream_t s) {
+  if (count <= 0) return hipSuccess;
+  if (count > kMaxBatch) return hipErrorInvalidValue;
+  return count == 1 ? mid_batch<1>(p, reqs, count, wl_model, fuse_rows, spread, s)
+                    : mid_batch<kMaxBatch>(p, reqs, count, wl_model, fuse_rows, spread, s);
 }
 
 hipError_t launch_compact_cells(const SumReq* reqs, int count, int grad_mode, hipStream_t s) {

@@ -83,14 +83,15 @@ int xch_dims(int m, int num_nets, int num_pins, int max_degree, XchDims* d) {
   // Netlists that do not fill two blocks of that size per CU are cut finer: a
   // block's time follows its pins (staging, the nets handed to its eight
   // wavefronts, the write-back), and small blocks share a CU three at a time.
-  // Designs of the compact evaluation's size are kept to blocks that stage in
-  // one round of four pins per thread.  Net blocks of 30k cells (78k pins)
+  // Designs whose net blocks read the positions by pin are kept to blocks that
+  // stage in one round of four pins per thread (past them the spread's runs want
+  // the larger blocks: 500k cells with 2.8M pins at n = 1024 130 -> 119 us).  Net blocks of 30k cells (78k pins)
   // alone: 15.1 us in 20 blocks of 4096 pins, 8.4 us in 153 of 512; eight such
   // designs in one launch prefer 1024 (41.9 -> 35.9 us), one design does not mind.
   {
     const int64_t even = ((int64_t)num_pins + kXchNetBlocks - 1) / kXchNetBlocks;
     npt = (int)std::min<int64_t>(npt, std::max<int64_t>(kXchSmallTarget, even));
-    if (cpb <= kCompactMaxCpb)
+    if (m <= kCompactDirectCells)
       npt = std::min(npt, std::max(kXchSmallTarget, 4 * kXchWaThreads + 1 - max_degree));
   }
   XchDims r;
@@ -393,71 +394,14 @@ int xch_build(const XchDims& d, const int32_t* net_ptr, const int32_t* pin_cell,
 // ---------------------------------------------------------------------------
 namespace {
 
-// T[a] = (x, y) of pin a's cell, over part b % kXchSpreadSplit of the A range of
-// cell block b / kXchSpreadSplit, b = xcd_order of the block.
 template <int NB>
 __global__ void __launch_bounds__(NT) k_xch_spread(XchBatch<NB> xb) {
   // design blockIdx.y of the batch; blocks past its cell blocks idle
   const XchReq& rq = xb.r[blockIdx.y];
-  const int m = rq.m, cpb = rq.cpb;
-  if ((int)blockIdx.x >= rq.ncb * kXchSpreadSplit) return;
-  const int32_t* __restrict__ cb_a_ptr = rq.cb_a_ptr;
-  const uint16_t* __restrict__ lc = rq.lc;
-  const float* __restrict__ x = rq.x;
-  const float* __restrict__ y = rq.y;
-  float2* __restrict__ T = rq.T;
+  const int nb = rq.ncb * kXchSpreadSplit;
+  if ((int)blockIdx.x >= nb) return;
   __shared__ float2 win[kXchCells];
-  const int sb = xcd_order(blockIdx.x, rq.ncb * kXchSpreadSplit);
-  const int cb = sb / kXchSpreadSplit, part = sb % kXchSpreadSplit;
-  const int t = threadIdx.x;
-  const int c0 = cb * cpb;
-  const int nc = min(cpb, m - c0);
-  {
-    constexpr int W = kXchCells / NT;
-    float xv[W], yv[W];
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-      const int i = c0 + min(t + k * NT, nc - 1);
-      xv[k] = x[i];
-      yv[k] = y[i];
-    }
-#pragma unroll
-    for (int k = 0; k < W; ++k)
-      if (t + k * NT < nc) win[t + k * NT] = make_float2(xv[k], yv[k]);
-  }
-  __syncthreads();
-  const int b0 = cb_a_ptr[cb], b1 = cb_a_ptr[cb + 1];
-  const int len = (b1 - b0 + kXchSpreadSplit - 1) / kXchSpreadSplit;
-  const int a0 = b0 + part * len, a1 = min(b1, a0 + len);
-  if (a0 >= a1) return;
-  // pairs of consecutive A positions aligned to 2, consecutive pairs on
-  // consecutive lanes: one 4-byte load of their cell indices and one 16-byte
-  // store of their positions per pair, both coalesced across the wavefront;
-  // a pair straddling either end of the range is stored only inside it (its
-  // index load stays inside the index allocation)
-  const int g0 = a0 >> 1, g1 = (a1 + 1) >> 1;
-  const uint32_t* lc2 = reinterpret_cast<const uint32_t*>(lc);
-  float4* T2 = reinterpret_cast<float4*>(T);
-  constexpr int U = 8;
-  for (int g = g0 + t; g < g1; g += U * NT) {
-    uint32_t q[U];
-#pragma unroll
-    for (int k = 0; k < U; ++k) q[k] = lc2[min(g + k * NT, g1 - 1)];
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int gg = g + k * NT;
-      if (gg >= g1) continue;
-      const float2 v0 = win[min((int)(q[k] & 0xffffu), kXchCells - 1)];
-      const float2 v1 = win[min((int)(q[k] >> 16), kXchCells - 1)];
-      const int a = gg * 2;
-      if (a >= a0 && a + 2 <= a1) {
-        T2[gg] = make_float4(v0.x, v0.y, v1.x, v1.y);
-      } else {
-        if (a >= a0) T[a] = v0;
-        if (a + 1 < a1) T[a + 1] = v1;
-      }
-    }
-  }
+  spread_part<NT, kXchCells, kXchSpreadSplit>(rq, xcd_order(blockIdx.x, nb), win);
 }
 
 template <int STAGE, bool LSE, int NB, bool DIRECT>
@@ -465,7 +409,7 @@ __global__ void __launch_bounds__(NW) k_xch_wa(XchBatch<NB> xb) {
   extern __shared__ float2 smem[];
   const XchReq& rq = xb.r[blockIdx.y];
   if ((int)blockIdx.x >= rq.nnb) return;
-  wa_block<STAGE, LSE, DIRECT>(rq, xcd_order(blockIdx.x, rq.nnb), smem);
+  wa_block<STAGE, DIRECT ? kStageHold : STAGE, LSE, DIRECT>(rq, xcd_order(blockIdx.x, rq.nnb), smem);
 }
 
 // The gradient of every cell (CellGradArgs): its density part plus the sum

@@ -1111,14 +1111,20 @@ struct CompactBatch {
   int count = 0, nb = 0;
   CompactReq r[NB];
 };
-constexpr int kCompactMaxN = 512;       // largest grid: a row pair per band
+constexpr int kCompactMaxN = 1024;      // largest grid
+constexpr int kCompactPairN = 512;      // largest grid of a row pair per band
+constexpr int kCompactDirectCells = 262144;   // most cells read by pin
 constexpr int kCompactMaxCpb = 2048;    // largest cell block
 constexpr int kCompactScanCells = 8192; // most cells read by every band block
 bool compact_design(int n, const XchDims& d);
+// the place pass and the spread in one launch (blocks of at most kCompactMaxCpb
+// cells, place blocks of at most 2048)
+hipError_t launch_compact_place(const BandReq* br, const XchReq* xr, int count, hipStream_t s);
 // scatter (and first row pass) beside the net blocks
 hipError_t launch_compact_mid(const Plan& p, const CompactReq* reqs, int count, int wl_model,
-                              bool fuse_rows, hipStream_t s);
+                              bool fuse_rows, bool spread, hipStream_t s);
 bool compact_fuses_rows(const Plan& p);
+bool compact_spreads(const Plan& p, int m);
 // per-cell gradients: density part gathered per cell, pin sums, the scalars
 hipError_t launch_compact_cells(const SumReq* reqs, int count, int grad_mode, hipStream_t s);
 hipError_t launch_band_place_batch(const BandReq* reqs, int count, hipStream_t s);

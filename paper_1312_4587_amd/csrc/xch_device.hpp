@@ -14,11 +14,74 @@ constexpr int kXchSmallDeg = 8;   // degree handled by one thread
 // or up to kXchPinCap
 constexpr int kStageS = (kXchPinLds2 + kXchWaThreads - 1) / kXchWaThreads;
 constexpr int kStageL = (kXchPinCap + kXchWaThreads - 1) / kXchWaThreads;
+constexpr int kStageHold = 4;   // of them staged together in the compact kernels
 
 // Weighted-average terms of one axis with the exponentials computed once:
 // e+ = exp((X - M)/gamma), e- = exp((L - X)/gamma) (fast exp2-based exp: the
 // arguments are <= 0 and the terms that matter are near 0).
 __device__ __forceinline__ float fexp(float v) { return __expf(v); }
+
+// T[a] = (x, y) of pin a's cell, over part b % SPLIT of the A range of cell block
+// b / SPLIT, by NT threads; the cells' positions staged in win[CELLS].
+template <int NT, int CELLS, int SPLIT>
+__device__ __forceinline__ void spread_part(const XchReq& rq, int b, float2* win) {
+  const int m = rq.m, cpb = rq.cpb;
+  const int32_t* __restrict__ cb_a_ptr = rq.cb_a_ptr;
+  const uint16_t* __restrict__ lc = rq.lc;
+  const float* __restrict__ x = rq.x;
+  const float* __restrict__ y = rq.y;
+  float2* __restrict__ T = rq.T;
+  const int cb = b / SPLIT, part = b % SPLIT;
+  const int t = threadIdx.x;
+  const int c0 = cb * cpb;
+  const int nc = min(cpb, m - c0);
+  {
+    constexpr int W = CELLS / NT;
+    float xv[W], yv[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      const int i = c0 + min(t + k * NT, nc - 1);
+      xv[k] = x[i];
+      yv[k] = y[i];
+    }
+#pragma unroll
+    for (int k = 0; k < W; ++k)
+      if (t + k * NT < nc) win[t + k * NT] = make_float2(xv[k], yv[k]);
+  }
+  __syncthreads();
+  const int b0 = cb_a_ptr[cb], b1 = cb_a_ptr[cb + 1];
+  const int len = (b1 - b0 + SPLIT - 1) / SPLIT;
+  const int a0 = b0 + part * len, a1 = min(b1, a0 + len);
+  if (a0 >= a1) return;
+  // pairs of consecutive A positions aligned to 2, consecutive pairs on
+  // consecutive lanes: one 4-byte load of their cell indices and one 16-byte
+  // store of their positions per pair, both coalesced across the wavefront;
+  // a pair straddling either end of the range is stored only inside it (its
+  // index load stays inside the index allocation)
+  const int g0 = a0 >> 1, g1 = (a1 + 1) >> 1;
+  const uint32_t* lc2 = reinterpret_cast<const uint32_t*>(lc);
+  float4* T2 = reinterpret_cast<float4*>(T);
+  constexpr int U = 8;
+  for (int g = g0 + t; g < g1; g += U * NT) {
+    uint32_t q[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) q[k] = lc2[min(g + k * NT, g1 - 1)];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int gg = g + k * NT;
+      if (gg >= g1) continue;
+      const float2 v0 = win[min((int)(q[k] & 0xffffu), CELLS - 1)];
+      const float2 v1 = win[min((int)(q[k] >> 16), CELLS - 1)];
+      const int a = gg * 2;
+      if (a >= a0 && a + 2 <= a1) {
+        T2[gg] = make_float4(v0.x, v0.y, v1.x, v1.y);
+      } else {
+        if (a >= a0) T[a] = v0;
+        if (a + 1 < a1) T[a + 1] = v1;
+      }
+    }
+  }
+}
 
 // One net block: cell positions and pin offsets staged in LDS in CSR order,
 // nets evaluated from LDS, gradients written to the pins' A positions in T.
@@ -28,7 +91,10 @@ __device__ __forceinline__ float fexp(float v) { return __expf(v); }
 // LDS: pos[cap], off[cap] (dynamic, 16 bytes per pin of the block).
 // LSE: the log-sum-exp model in place of the weighted average (same sums;
 // the gradient is e+/S+ - e-/S-, the value (M - L) + gamma (ln S+ + ln S-)).
-template <int STAGE, bool LSE, bool DIRECT>
+// Staging goes HOLD pins per thread at a time: with HOLD < STAGE chunks past the
+// block's last pin are skipped, and only the first chunk's A positions are kept
+// for the write-back (fewer registers, for blocks of mostly one chunk).
+template <int STAGE, int HOLD, bool LSE, bool DIRECT>
 __device__ __forceinline__ void wa_block(const XchReq& rq, int k, float2* smem) {
   constexpr int NW = kXchWaThreads, kSmall = kXchSmallDeg;
   const int t = threadIdx.x, nblk = rq.nnb;
@@ -68,10 +134,7 @@ __device__ __forceinline__ void wa_block(const XchReq& rq, int k, float2* smem) 
     // cell position read from T in B order (runs of consecutive A positions).
     // Loads are unconditional (index clamped into the block) so that each
     // batch is in flight at once; only the LDS stores are masked.
-    // (DIRECT: both in CSR order, positions by the pins' cells; chunks of HOLD
-    // pins per thread past the block's last one are skipped, and only the first
-    // chunk's A positions are kept for the write-back)
-    constexpr int HOLD = DIRECT && STAGE > 4 ? 4 : STAGE;
+    // (DIRECT: both in CSR order, positions by the pins' cells)
     int av[HOLD], lv[HOLD];
     const int blast = p1 - 1;
     if constexpr (DIRECT) {
@@ -116,28 +179,38 @@ __device__ __forceinline__ void wa_block(const XchReq& rq, int k, float2* smem) 
         }
       }
     } else {
-      float dx[STAGE], dy[STAGE];
 #pragma unroll
-      for (int j = 0; j < STAGE; ++j) {
-        const int b = min(p0 + t + j * NW, blast);
-        av[j] = a_of_b[b];
-        lv[j] = lcsr[b];
-        dx[j] = pin_dx[b];
-        dy[j] = pin_dy[b];
-      }
+      for (int j0 = 0; j0 < STAGE; j0 += HOLD) {
+        if (HOLD < STAGE && j0 * NW >= np) break;
+        float dx[HOLD], dy[HOLD];
+        int ai[HOLD], li[HOLD];
 #pragma unroll
-      for (int j = 0; j < STAGE; ++j) {
-        av[j] = min((unsigned)av[j], (unsigned)(num_pins - 1));
-        lv[j] = min(lv[j], cap - 1);
-      }
-      float2 q[STAGE];
+        for (int j = 0; j < HOLD; ++j) {
+          const int b = min(p0 + t + (j0 + j) * NW, blast);
+          ai[j] = a_of_b[b];
+          li[j] = lcsr[b];
+          dx[j] = pin_dx[b];
+          dy[j] = pin_dy[b];
+        }
 #pragma unroll
-      for (int j = 0; j < STAGE; ++j) q[j] = T[av[j]];
+        for (int j = 0; j < HOLD; ++j) {
+          ai[j] = min((unsigned)ai[j], (unsigned)(num_pins - 1));
+          li[j] = min(li[j], cap - 1);
+        }
+        float2 q[HOLD];
 #pragma unroll
-      for (int j = 0; j < STAGE; ++j) {
-        if (p0 + t + j * NW < p1) {
-          off[t + j * NW] = make_float2(dx[j], dy[j]);
-          pos[lv[j]] = q[j];
+        for (int j = 0; j < HOLD; ++j) q[j] = T[ai[j]];
+#pragma unroll
+        for (int j = 0; j < HOLD; ++j) {
+          const int l = t + (j0 + j) * NW;
+          if (p0 + l < p1) {
+            off[l] = make_float2(dx[j], dy[j]);
+            pos[li[j]] = q[j];
+          }
+          if (j0 == 0) {
+            av[j] = ai[j];
+            lv[j] = li[j];
+          }
         }
       }
     }
@@ -381,27 +454,21 @@ __device__ __forceinline__ void wa_block(const XchReq& rq, int k, float2* smem) 
     __syncthreads();
 
     // 3. gradients to the pins' A positions
-    if constexpr (DIRECT) {
 #pragma unroll
-      for (int j0 = 0; j0 < STAGE; j0 += HOLD) {
-        if (j0 * NW >= np) break;
+    for (int j0 = 0; j0 < STAGE; j0 += HOLD) {
+      if (HOLD < STAGE && j0 * NW >= np) break;
 #pragma unroll
-        for (int j = 0; j < HOLD; ++j) {
-          if (j0 > 0) {
-            const int b = min(p0 + t + (j0 + j) * NW, blast);
-            av[j] = a_of_b[b];
-            lv[j] = lcsr[b];
-          }
+      for (int j = 0; j < HOLD; ++j) {
+        if (j0 > 0) {
+          const int b = min(p0 + t + (j0 + j) * NW, blast);
+          av[j] = a_of_b[b];
+          lv[j] = lcsr[b];
         }
-#pragma unroll
-        for (int j = 0; j < HOLD; ++j)
-          if (p0 + t + (j0 + j) * NW < p1)
-            T[min((unsigned)av[j], (unsigned)(num_pins - 1))] = pos[min(lv[j], cap - 1)];
       }
-    } else {
 #pragma unroll
-      for (int j = 0; j < STAGE; ++j)
-        if (p0 + t + j * NW < p1) T[av[j]] = pos[lv[j]];
+      for (int j = 0; j < HOLD; ++j)
+        if (p0 + t + (j0 + j) * NW < p1)
+          T[min((unsigned)av[j], (unsigned)(num_pins - 1))] = pos[min(lv[j], cap - 1)];
     }
   }
   // the block's totals: both sums through one barrier

@@ -89,6 +89,51 @@ def test_eval_sizes(F, m, n, mode):
     _check(inst, _eval(F, inst, mode, shift=1), mode)
 
 
+# compact evaluations past n = 512 (bands of three and four rows, the row pass on
+# its own), with the positions read by pin up to 262,144 cells, spread past them
+# and, past 524,288, the general path; the matrix-core solve among them; cells of
+# several bins each way
+@pytest.mark.parametrize("m,n,mode,dct", [
+    (1, 1024, "field", "fft"), (8192, 1024, "exact", "fft"), (30000, 640, "field", "gemm_f32"),
+    (262144, 1024, "exact", "fft"), (262145, 1024, "field", "fft"), (262145, 576, "exact", "gemm_f32"),
+    (270000, 1024, "field", "gemm_bf16x3"), (524288, 1024, "exact", "fft"),
+    (524289, 1024, "field", "fft"), (20, 8, "field", "fft"), (20, 64, "exact", "fft")])
+def test_eval_large_grids(F, m, n, mode, dct):
+    inst = gen.make_instance((97, m, n), num_cells=m, util=0.8, n=n,
+                             num_nets=int(1.05 * m) if m > 9 else 0, num_macros=2,
+                             macro_area_frac=0.1, hi_frac=0.002 if m > 20000 else 0.0,
+                             hi_range=(20, 400))
+    say("eval", m, n, mode, dct)
+    _check(inst, _eval(F, inst, mode, dct=dct), mode)
+
+
+def test_batch_spreads_together(F):
+    # designs whose positions are spread to the pins beside ones read by the band
+    # blocks, placed first, and on the general path
+    import torch
+    sizes = [(3000, 0), (270000, 0), (30000, 0), (20000, 4800)]
+    insts = [gen.make_instance((98, k), num_cells=m, util=0.7, n=1024, num_nets=m,
+                               hi_frac=0.001 if d else 0.0, hi_range=(d, d))
+             for k, (m, d) in enumerate(sizes)]
+    probs = [F.Problem.from_instance(i) for i in insts]
+    cells = [DeviceCells(i) for i in insts]
+    plan, single = F.Plan(1024, max_batch=4), F.Plan(1024)
+    gxs, gys = ([torch.empty(i.num_cells, device="cuda") for i in insts] for _ in range(2))
+    out = torch.empty((len(insts), 4), dtype=torch.float64, device="cuda")
+    say("batch with a spread")
+    F.eval_batch(plan, probs, [c.x for c in cells], [c.y for c in cells], [2.0] * len(insts),
+                 [i.gamma for i in insts], "exact", gxs, gys, out)
+    for k, i in enumerate(insts):
+        gx, gy = (torch.empty(i.num_cells, device="cuda") for _ in range(2))
+        o4 = torch.empty(4, dtype=torch.float64, device="cuda")
+        F.eval(single, probs[k], cells[k].x, cells[k].y, 2.0, i.gamma, "exact", gx, gy, o4)
+        torch.cuda.synchronize()
+        assert torch.equal(gx, gxs[k]) and torch.equal(gy, gys[k])
+        assert torch.allclose(o4, out[k], rtol=1e-12, atol=0.0)
+    plan.close()
+    single.close()
+
+
 # net blocks at their size rules: one staging round, several, the largest that
 # two share a CU, and past it (the general path); pins above 2,048 per block
 @pytest.mark.parametrize("hi", [900, 1100, 3000, 4700])
