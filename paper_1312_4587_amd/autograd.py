@@ -25,7 +25,7 @@ class _Objective(torch.autograd.Function):
         ctx.save_for_backward(x, y)
         ctx.plan, ctx.prob, ctx.lam, ctx.gamma = plan, prob, float(lam), float(gamma)
         ctx.mark_non_differentiable(out4)
-        return out4[1] + ctx.lam * out4[0], out4
+        return torch.add(out4[1], out4[0], alpha=ctx.lam), out4
 
     @staticmethod
     def backward(ctx, g_loss, g_out4):
@@ -34,8 +34,8 @@ class _Objective(torch.autograd.Function):
         gy = torch.empty_like(y)
         out4 = torch.empty(4, dtype=torch.float64, device=x.device)
         fftpl.eval(ctx.plan, ctx.prob, x, y, ctx.lam, ctx.gamma, "exact", gx, gy, out4)
-        s = g_loss.to(torch.float32)
-        return gx * s, gy * s, None, None, None, None
+        # scaled in place by the 0-dim float64 gradient (the products stay float32)
+        return gx.mul_(g_loss), gy.mul_(g_loss), None, None, None, None
 
 
 def objective(x, y, plan: fftpl.Plan, prob: fftpl.Problem, lam: float, gamma: float):
