@@ -82,17 +82,22 @@ __global__ void __launch_bounds__(kBandThreads) k_compact_place(PlaceBatch<NB> p
     spread_part<kBandThreads, kCompactMaxCpb, kXchSpreadSplit>(rq, xcd_order(b, nb), win);
 }
 
-// Six wavefronts per SIMD: three blocks of 512 threads per CU instead of the
-// two that 94 registers leave (27.7 -> 23.9 us at 200k cells).
+// DIRECT: six wavefronts per SIMD, three blocks of 512 threads per CU instead of
+// the two that 94 registers leave (27.7 -> 23.9 us at 200k cells).  Spread
+// positions: two blocks per CU, every pin staged in one round, and neighbouring net
+// blocks on one XCD for the runs they share (30.5 -> 25.4 us at 500k cells, n =
+// 1024; the whole evaluation 93.3 -> 87.7).
 template <int N, int BINS, bool LSE, bool DIRECT, int NB>
-__global__ void __launch_bounds__(NT, 6) k_compact_mid(CompactBatch<NB> cb,
+__global__ void __launch_bounds__(NT, DIRECT ? 6 : 4) k_compact_mid(CompactBatch<NB> cb,
                                                     const float2* __restrict__ tw_g,
                                                     const float2* __restrict__ cs_g) {
   extern __shared__ float2 smem[];
   const CompactReq& q = cb.r[blockIdx.y];
   if ((int)blockIdx.x >= cb.nb) {
     const int k = (int)blockIdx.x - cb.nb;
-    if (k < q.x.nnb) wa_block<kStageS, kStageHold, LSE, DIRECT>(q.x, k, smem);
+    constexpr int HOLD = DIRECT ? kStageHold : kStageS;
+    if (k < q.x.nnb)
+      wa_block<kStageS, HOLD, LSE, DIRECT>(q.x, DIRECT ? k : xcd_order(k, q.x.nnb), smem);
     return;
   }
   MidLds<N, BINS>& lds = *reinterpret_cast<MidLds<N, BINS>*>(smem);
