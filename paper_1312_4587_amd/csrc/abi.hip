@@ -342,6 +342,9 @@ int fftpl_density_map(const fftpl_grid* grid, int32_t num_cells, const float* x,
   }
   const GridF g = make_gridf(*grid);
   hipStream_t s = as_stream(stream);
+  if (density_scans(grid->n, num_cells))   // no band lists
+    return dev_status(launch_band_scatter(g, band_shape(grid->n, num_cells), x, y, w, h, base,
+                                          rho, s));
   if (grid->n <= kBandMaxN) {
     // the banded scatter of the evaluation, its band lists in a temporary
     // stream-ordered allocation released on the stream after the scatter
@@ -696,7 +699,7 @@ int run_compact_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream_
     spread = spread || compact_spreads(p, rs[i].xd.m);
   for (int i = 0; i < count; ++i) {
     const EvalReq& r = rs[i];
-    const bool scan = r.xd.m <= kCompactScanCells;
+    const bool scan = r.xd.m <= kScanCells;
     br[i].g = r.g;
     br[i].L = r.L;
     br[i].L.epos = nullptr;   // the gradient is gathered per cell

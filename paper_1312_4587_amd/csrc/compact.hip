@@ -8,7 +8,7 @@
 // device evaluating.  Here the same steps take five launches on the caller's
 // stream alone (four for the smallest designs):
 //   place  the counting sort of the cells by band (k_band_place), skipped up to
-//          kCompactScanCells cells, whose band blocks read every cell; past
+//          kScanCells cells, whose band blocks read every cell; past
 //          kCompactDirectCells with the spread beside it (k_compact_place);
 //   mid    band blocks: scatter of a row pair, and for FFT plans its row transform
 //          straight from LDS (past n = 512 of up to four rows, the row pass on its

@@ -871,6 +871,8 @@ struct BandLayout {
 };
 BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
                        size_t* bytes_out);
+constexpr int kScanCells = 8192;   // most cells read by every band block (no band lists)
+bool density_scans(int n, int m);   // the map alone takes no band lists
 // Bands and counting blocks of a design (the pointers stay null).
 BandLayout band_shape(int n, int m);
 
@@ -1115,7 +1117,6 @@ constexpr int kCompactMaxN = 1024;      // largest grid
 constexpr int kCompactPairN = 512;      // largest grid of a row pair per band
 constexpr int kCompactDirectCells = 262144;   // most cells read by pin
 constexpr int kCompactMaxCpb = 2048;    // largest cell block
-constexpr int kCompactScanCells = 8192; // most cells read by every band block
 bool compact_design(int n, const XchDims& d);
 // the place pass and the spread in one launch (blocks of at most kCompactMaxCpb
 // cells, place blocks of at most 2048)

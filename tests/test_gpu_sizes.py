@@ -43,6 +43,28 @@ def test_density_map_block_sizes(F, m, n):
     assert rel_l2(host(rho).reshape(n, n), oracle.density_map(inst, b0)) < RTOL
 
 
+# small maps in one launch, without band lists (n <= 512, up to 8192 cells), and the
+# first designs past it; no cells; each into an old map and again
+@pytest.mark.parametrize("m,n", [(0, 16), (1, 1), (2047, 31), (2049, 64), (8192, 512),
+                                 (8193, 512), (8192, 513), (5000, 7)])
+def test_density_map_small(F, m, n):
+    import torch
+    inst = gen.make_instance((100, m, n), num_cells=max(m, 1), util=0.7, n=n, num_nets=0,
+                             num_macros=2, macro_area_frac=0.1)
+    inst = dataclasses.replace(inst, **{k: getattr(inst, k)[:m] for k in "xywh"})
+    c = DeviceCells(inst)
+    b0, _ = oracle.fixed_maps(inst)
+    base = torch.as_tensor(np.asarray(b0, np.float32).ravel()).cuda()
+    rho = torch.full((n * n,), 7.0, device="cuda")
+    want = oracle.density_map(inst, b0) if m else np.asarray(b0)
+    say("density", m, n)
+    for b, ref in ((base, want), (None, want - b0)):
+        F.density_map(F.Grid.of(inst), c.x, c.y, c.w, c.h, b, rho)
+        torch.cuda.synchronize()
+        # (m = 0 without a base is the zero map)
+        assert rel_l2(host(rho).reshape(n, n), ref) < RTOL or not (ref.any() or host(rho).any())
+
+
 def _eval(F, inst, mode, dct="fft", shift=0, **prob_kw):
     """One evaluation with the positions `shift` floats into a larger array."""
     import torch
