@@ -31,24 +31,24 @@ BF16_PEAK_TFLOPS = 2500.0
 PMC_FETCH_SCALE, PMC_WRITE_SCALE = 2.0, 1.0
 PMC_TRAFFIC = {
     # kernel: (source files, sha1, FETCH_SIZE KiB, WRITE_SIZE KiB)
-    "k_band_place": (("band_scatter.hip", "fftpl_internal.hpp"),
-        "363d6c18c810a50f8ba1358a41d225290199574c", 16523.6, 64791.1),
-    "k_xch_spread": (("exchange.hip", "fftpl_internal.hpp"),
-        "aa1810760312d0fe8d4d95a86c95e7764cd01c4a", 28609.1, 96907.1),
-    "k_band_accum": (("band_scatter.hip", "fftpl_internal.hpp"),
-        "363d6c18c810a50f8ba1358a41d225290199574c", 27911.0, 4096.0),
-    "k_xch_wa": (("exchange.hip", "fftpl_internal.hpp"),
-        "aa1810760312d0fe8d4d95a86c95e7764cd01c4a", 178984.5, 112289.7),
-    "k_rows_dct2": (("spectral_fft.hip", "fftpl_internal.hpp"),
-        "63506664793af2e33294635574c5e783f13c917a", 6235.8, 4112.0),
-    "k_cols_solve": (("spectral_fft.hip", "fftpl_internal.hpp"),
-        "63506664793af2e33294635574c5e783f13c917a", 2180.6, 8192.0),
-    "k_rows_inverse": (("spectral_fft.hip", "fftpl_internal.hpp"),
-        "63506664793af2e33294635574c5e783f13c917a", 6264.1, 8196.0),
-    "k_band_gather": (("band_scatter.hip", "fftpl_internal.hpp"),
-        "363d6c18c810a50f8ba1358a41d225290199574c", 30994.6, 21000.0),
-    "k_xch_cellsum": (("exchange.hip", "fftpl_internal.hpp"),
-        "aa1810760312d0fe8d4d95a86c95e7764cd01c4a", 80868.2, 16406.5),
+    "k_band_place": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
+        "9d5a2ea099bd3ab525d954a0a87291a45e1ff051", 16523.3, 64267.3),
+    "k_xch_spread": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
+        "7ac8b01745a55e9ea304ba68542bf88609efc6dc", 21223.2, 96857.6),
+    "k_band_accum": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
+        "9d5a2ea099bd3ab525d954a0a87291a45e1ff051", 21681.1, 4096.0),
+    "k_xch_wa": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
+        "7ac8b01745a55e9ea304ba68542bf88609efc6dc", 144059.9, 101040.5),
+    "k_rows_dct2": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
+        "cdf6359e2693ebe0da55563fe8c530ff12da432c", 6234.0, 4112.0),
+    "k_cols_solve": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
+        "cdf6359e2693ebe0da55563fe8c530ff12da432c", 2180.0, 8192.0),
+    "k_rows_inverse": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
+        "cdf6359e2693ebe0da55563fe8c530ff12da432c", 6270.0, 8196.0),
+    "k_band_gather": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
+        "9d5a2ea099bd3ab525d954a0a87291a45e1ff051", 23893.6, 18698.7),
+    "k_xch_cellsum": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
+        "7ac8b01745a55e9ea304ba68542bf88609efc6dc", 80532.3, 16406.3),
 }
 
 
@@ -224,6 +224,14 @@ def band_entries(inst):
     return int(np.sum(np.where(ok, i1 // rows - i0 // rows + 1, 0)))
 
 
+def place_cells(m):
+    """Cells per block of k_band_place."""
+    c = 512
+    while c < 4096 and 256 * c < m:
+        c *= 2
+    return c
+
+
 def kernel_bytes(inst, nent):
     """Design bytes per launch of every kernel of the atomic-free evaluation:
     each array the kernel's own layout reads or writes, once (index arrays,
@@ -241,9 +249,10 @@ def kernel_bytes(inst, nent):
         "k_wa_slots_big": 12 * p_big + 8 * p_big + 4 * (E + 1),
         "k_interleave": 8 * m + 8 * m,
         # cells in; entries, each cell's first entry and the per-(band, block)
-        # slice offsets and counts out (4096 cells per block)
+        # slice offsets and counts out (512 cells per block, doubled up to 4096 while
+        # there are more blocks than 256)
         "k_band_place": 16 * m + 16 * nent + 4 * m
-        + 8 * (-(-inst.n // (-(-inst.n // 256))) + 1) * (-(-m // 4096)),
+        + 8 * (-(-inst.n // max(2, -(-inst.n // 256))) + 1) * (-(-m // place_cells(m))),
         "k_band_accum": 16 * nent + 4 * n2 + 4 * n2,
         "k_rows_dct2": 4 * n2 + 4 * n2 + 8 * n2,        # rho, base+cap in; bT out
         "k_cols_solve": 4 * n2 + 8 * n2,                # bT in; P, Q out
@@ -297,15 +306,19 @@ def stage_bytes(inst):
 
 # The kernels that carry each step (whichever path or spectral variant ran).
 # k_xch_cellsum sums each cell's pin gradients (a8) and adds lambda times the
-# density gradient (a9); its time is booked to a8.
+# density gradient (a9); its time is booked to a8.  The compact evaluation (designs
+# up to 524,288 cells) runs the net blocks beside the scatter (k_compact_mid, booked
+# to a8, with the first row pass in it up to n = 512) and the cells' density gradient
+# beside their pin sums (k_compact_cells, booked to a6).
 STAGE_KERNELS = {
-    "a2_scatter": ("k_band_place", "k_band_accum", "k_fill", "k_scatter"),
+    "a2_scatter": ("k_band_place", "k_compact_place", "k_band_accum", "k_band_scan", "k_fill",
+                   "k_scatter"),
     "a3_a5_spectral": ("k_rows_dct2", "k_cols_solve", "k_rows_inverse", "k_gemm_rowsum",
                        "k_gemm_prep", "k_gemm_w", "k_gemm_bfly", "k_gemm_g", "k_gemm_uv",
                        "k_gemm_psi_ey", "k_gemm_ex"),
-    "a6_gather": ("k_band_gather", "k_gather", "k_gather_pins"),
-    "a8_wirelength": ("k_xch_spread", "k_xch_wa", "k_xch_cellsum", "k_interleave",
-                      "k_wa_slots_small", "k_wa_slots_big", "k_wa_atomic"),
+    "a6_gather": ("k_band_gather", "k_gather", "k_gather_pins", "k_compact_cells"),
+    "a8_wirelength": ("k_xch_spread", "k_xch_wa", "k_xch_cellsum", "k_compact_mid",
+                      "k_interleave", "k_wa_slots_small", "k_wa_slots_big", "k_wa_atomic"),
 }
 
 

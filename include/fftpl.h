@@ -252,7 +252,8 @@ int fftpl_dark_nodes(double xl, double yl, double xh, double yh, int32_t num_rec
  * overwritten.  For n <= 1024 it runs the evaluation's banded scatter
  * (counting sort by band, fixed-point LDS sums: the same bits on every run)
  * with its band lists in a temporary allocation made and released on
- * `stream` (hipMallocAsync / hipFreeAsync; FFTPL_E_NOMEM if it fails); the
+ * `stream` (hipMallocAsync / hipFreeAsync; FFTPL_E_NOMEM if it fails; none up to
+ * 8192 cells with n <= 512); the
  * caller that keeps a workspace uses fftpl_problem_density, the caller that
  * cannot allocate fftpl_density_map_noalloc.  For n > 1024 it accumulates
  * with float atomics: the rounding order (not the value beyond float32
@@ -393,7 +394,8 @@ int fftpl_netlist_index(int32_t num_cells, int32_t num_pins, const int32_t* pin_
 /* Exchange index of a netlist (Section II: the netlist as a hypergraph; the
  * index is a blocked form of the transpose of its pin-net incidence), for the
  * fastest fftpl_eval path.  Cells are cut into blocks of consecutive cells
- * (a multiple of 256 cells, at most 9216, about one block per compute unit)
+ * (a multiple of 256 cells, at most 9216, about one block per compute unit, two
+ * up to 262,144 cells)
  * and nets into blocks of whole nets (at most 9728 pins per block); the
  * index lists the pins by (cell block, net block) and, per net block, by cell
  * block, so that positions and gradients move between cells and nets in runs
@@ -430,12 +432,13 @@ int fftpl_xindex_build(int32_t num_cells, int32_t num_nets, int32_t num_pins,
  * other scalars, without the gather); this needs a workspace and an index in
  * prob (FFTPL_E_INVAL otherwise).  A workspace or index that prob gives but
  * that cannot be used is an error (see fftpl_problem), not a silent change
- * of path.  With a workspace and an index the
- * wirelength branch (pin positions, net blocks) runs on the plan's own stream
- * concurrently with the density branch (scatter, solve, per-cell density
- * gradient) on `stream`, and is joined back before the per-cell sums; the
- * density map, the
- * cell sums and the scalars do not depend on the order of any atomic adds,
+ * of path.  With a workspace and an index, designs of up to 524,288 cells are
+ * evaluated in a few launches on `stream` alone; past them (and with nets too large
+ * for the compact net blocks) the wirelength branch (pin positions, net blocks)
+ * runs on the plan's own stream concurrently with the density branch (scatter,
+ * solve, per-cell density gradient) on `stream`, and is joined back before the
+ * per-cell sums.  On either path the density map, the cell sums and the scalars
+ * do not depend on the order of any atomic adds,
  * so repeated evaluations give identical results. */
 int fftpl_eval(fftpl_plan* plan, const fftpl_problem* prob, const float* x,
                const float* y, float lambda, float gamma, int32_t grad_mode,
