@@ -307,7 +307,7 @@ def stage_bytes(inst):
 # The kernels that carry each step (whichever path or spectral variant ran).
 # k_xch_cellsum sums each cell's pin gradients (a8) and adds lambda times the
 # density gradient (a9); its time is booked to a8.  The compact evaluation (designs
-# up to 524,288 cells) runs the net blocks beside the scatter (k_compact_mid, booked
+# up to 1,048,576 cells) runs the net blocks beside the scatter (k_compact_mid, booked
 # to a8, with the first row pass in it up to n = 512) and the cells' density gradient
 # beside their pin sums (k_compact_cells, booked to a6).
 STAGE_KERNELS = {

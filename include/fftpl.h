@@ -432,7 +432,7 @@ int fftpl_xindex_build(int32_t num_cells, int32_t num_nets, int32_t num_pins,
  * other scalars, without the gather); this needs a workspace and an index in
  * prob (FFTPL_E_INVAL otherwise).  A workspace or index that prob gives but
  * that cannot be used is an error (see fftpl_problem), not a silent change
- * of path.  With a workspace and an index, designs of up to 524,288 cells are
+ * of path.  With a workspace and an index, designs of up to 1,048,576 cells are
  * evaluated in a few launches on `stream` alone; past them (and with nets too large
  * for the compact net blocks) the wirelength branch (pin positions, net blocks)
  * runs on the plan's own stream concurrently with the density branch (scatter,

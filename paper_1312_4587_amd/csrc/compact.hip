@@ -1,11 +1,10 @@
 // The compact evaluation: the exchange path of designs whose kernels are all
 // shorter than the work of launching them.
 //
-// The general exchange path runs nine kernels on two streams.  Up to some
-// hundred thousand cells each of them lasts 3 to 20 us, most of it the latency of
-// a few dependent loads, and the host spends longer enqueueing the nine
-// launches and the four cross-stream event calls (75 to 89 us measured) than the
-// device evaluating.  Here the same steps take five launches on the caller's
+// The general exchange path runs nine kernels on two streams.  Up to a million
+// cells each of them lasts 3 to 30 us, much of it the latency of a few dependent
+// loads, and the host enqueues the nine launches and the four cross-stream event
+// calls in 75 to 89 us, for small designs longer than the device evaluates.  Here the same steps take five launches on the caller's
 // stream alone (four for the smallest designs):
 //   place  the counting sort of the cells by band (k_band_place), skipped up to
 //          kScanCells cells, whose band blocks read every cell; past
@@ -59,27 +58,27 @@ struct MidLds {
 // the pins: past kCompactDirectCells the positions and the rest of a net block's
 // data no longer fit an XCD's L2 together, and reading them by pin costs more
 // than the spread (net blocks of 500k cells, n = 1024: 34 us against 17 us).
-constexpr int kPlaceCells = 4;   // most cells per thread of a place block
 template <int NB>
 struct PlaceBatch {
   int nblk = 0;
   BandReq r[NB];
   XchReq x[NB];
 };
-template <int NB>
+// CB: cells per thread of a place block; CELLS: most cells of a spread block.
+template <int NB, int CB, int CELLS>
 __global__ void __launch_bounds__(kBandThreads) k_compact_place(PlaceBatch<NB> pb) {
-  __shared__ float2 win[kCompactMaxCpb];
+  __shared__ float2 win[CELLS];
   const int b = (int)blockIdx.x - pb.nblk;
   if (b < 0) {
     const BandReq& q = pb.r[blockIdx.y];
     if (q.L.m > 0 && (int)blockIdx.x < q.L.nblk)
-      place_block<kPlaceCells>(q.g, q.L, blockIdx.x, q.x, q.y, q.w, q.h);
+      place_block<CB>(q.g, q.L, blockIdx.x, q.x, q.y, q.w, q.h);
     return;
   }
   const XchReq& rq = pb.x[blockIdx.y];
   const int nb = rq.ncb * kXchSpreadSplit;
   if (b < nb)
-    spread_part<kBandThreads, kCompactMaxCpb, kXchSpreadSplit>(rq, xcd_order(b, nb), win);
+    spread_part<kBandThreads, CELLS, kXchSpreadSplit>(rq, xcd_order(b, nb), win);
 }
 
 // DIRECT: six wavefronts per SIMD, three blocks of 512 threads per CU instead of
@@ -174,10 +173,10 @@ __global__ void __launch_bounds__(NT, DIRECT ? 6 : 4) k_compact_mid(CompactBatch
   }
 }
 
-// TC threads, PC cells per thread: (256, 1), (512, 1), (1024, 1) or (1024, 2), the
+// TC threads, PC cells per thread: (256, 1), (512, 1), (1024, 1), (1024, 2) or (1024, 4), the
 // smallest that holds a cell block.  A block of one cell per thread is a short
 // chain of loads, and its registers and LDS leave room for several blocks per CU
-// (eight designs of up to 62k cells 22.3 -> 17.1 us); the largest blocks, one per
+// (eight designs of up to 62k cells 22.3 -> 17.1 us); the larger blocks, one per
 // CU, take 1024 threads for the map reads in flight (500k cells, n = 1024: 25.0 ->
 // 20.4 us against (512, 4)).
 template <int MODE, int NB, int TC, int PC>
@@ -238,18 +237,23 @@ template <int NB>
 hipError_t place_batch(const BandReq* br, const XchReq* xr, int count, hipStream_t s) {
   PlaceBatch<NB> pb;
   static_assert(sizeof(pb) <= 4096, "kernel arguments");
-  int max_nblk = 0, max_ncb = 0;
+  int max_nblk = 0, max_ncb = 0, max_cpk = 0, max_cpb = 0;
   for (int i = 0; i < count; ++i) {
     pb.r[i] = br[i];
     pb.x[i] = xr[i];
-    if (br[i].L.cpk > kPlaceCells * kBandThreads || xr[i].cpb > kCompactMaxCpb)
-      return hipErrorInvalidValue;
+    max_cpk = std::max(max_cpk, br[i].L.cpk);
+    max_cpb = std::max(max_cpb, xr[i].cpb);
     if (br[i].L.m > 0) max_nblk = std::max(max_nblk, br[i].L.nblk);
     max_ncb = std::max(max_ncb, xr[i].ncb);
   }
   pb.nblk = max_nblk;
-  hipLaunchKernelGGL((k_compact_place<NB>), dim3(max_nblk + max_ncb * kXchSpreadSplit, count),
-                     dim3(kBandThreads), 0, s, pb);
+  if (max_cpk > kCellBatch * kBandThreads || max_cpb > kCompactMaxCpb)
+    return hipErrorInvalidValue;
+  const dim3 grid(max_nblk + max_ncb * kXchSpreadSplit, count), block(kBandThreads);
+  if (max_cpk <= 4 * kBandThreads && max_cpb <= 2048)
+    hipLaunchKernelGGL((k_compact_place<NB, 4, 2048>), grid, block, 0, s, pb);
+  else
+    hipLaunchKernelGGL((k_compact_place<NB, kCellBatch, kCompactMaxCpb>), grid, block, 0, s, pb);
   return hipGetLastError();
 }
 
@@ -329,6 +333,7 @@ hipError_t cells_batch(const SumReq* reqs, int count, int grad_mode, hipStream_t
   if (max_cpb <= 256) return cells_launch<NB, 256, 1>(sb, max_ncb, grad_mode, s);
   if (max_cpb <= 512) return cells_launch<NB, 512, 1>(sb, max_ncb, grad_mode, s);
   if (max_cpb <= 1024) return cells_launch<NB, 1024, 1>(sb, max_ncb, grad_mode, s);
+  if (max_cpb <= 2048) return cells_launch<NB, 1024, 2>(sb, max_ncb, grad_mode, s);
   return cells_launch<NB, 1024, kCompactMaxCpb / 1024>(sb, max_ncb, grad_mode, s);
 }
 

@@ -1116,10 +1116,12 @@ struct CompactBatch {
 constexpr int kCompactMaxN = 1024;      // largest grid
 constexpr int kCompactPairN = 512;      // largest grid of a row pair per band
 constexpr int kCompactDirectCells = 262144;   // most cells read by pin
-constexpr int kCompactMaxCpb = 2048;    // largest cell block
+// largest cell block: 1,048,576 cells (n = 1024: 550k cells 109 -> 97 us against the
+// general path, 1M 126 -> 115, 1M clustered, exact 153 -> 115; 1.6M 153 -> 159,
+// 2.1M 183 -> 201, where two streams use the memory better)
+constexpr int kCompactMaxCpb = 4096;
 bool compact_design(int n, const XchDims& d);
-// the place pass and the spread in one launch (blocks of at most kCompactMaxCpb
-// cells, place blocks of at most 2048)
+// the place pass and the spread in one launch (blocks of at most kCompactMaxCpb cells)
 hipError_t launch_compact_place(const BandReq* br, const XchReq* xr, int count, hipStream_t s);
 // scatter (and first row pass) beside the net blocks
 hipError_t launch_compact_mid(const Plan& p, const CompactReq* reqs, int count, int wl_model,

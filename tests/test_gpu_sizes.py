@@ -129,6 +129,20 @@ def test_eval_large_grids(F, m, n, mode, dct):
     _check(inst, _eval(F, inst, mode, dct=dct), mode)
 
 
+# cell blocks of up to 4096 cells (1,048,576 cells, place blocks of 4096 too), and
+# the general path past them
+@pytest.mark.parametrize("m,n,mode,dct", [
+    (600001, 1024, "exact", "fft"), (524289, 512, "exact", "fft"),
+    (1048576, 1024, "field", "fft"), (1048577, 1024, "exact", "fft"),
+    (1000000, 704, "field", "gemm_f32")])
+def test_eval_million_cells(F, m, n, mode, dct):
+    inst = gen.make_instance((101, m, n), num_cells=m, util=0.8, n=n, num_nets=int(1.02 * m),
+                             num_macros=2, macro_area_frac=0.1, hi_frac=0.001,
+                             hi_range=(20, 400))
+    say("eval", m, n, mode, dct)
+    _check(inst, _eval(F, inst, mode, dct=dct), mode)
+
+
 def test_batch_spreads_together(F):
     # designs whose positions are spread to the pins beside ones read by the band
     # blocks, placed first, and on the general path
