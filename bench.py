@@ -32,23 +32,23 @@ PMC_FETCH_SCALE, PMC_WRITE_SCALE = 2.0, 1.0
 PMC_TRAFFIC = {
     # kernel: (source files, sha1, FETCH_SIZE KiB, WRITE_SIZE KiB)
     "k_band_place": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
-        "9d5a2ea099bd3ab525d954a0a87291a45e1ff051", 16523.3, 64267.3),
+        "cc1112fc3745d12a71cfc36426742563e57ded7b", 16523.3, 64267.3),
     "k_xch_spread": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
-        "7ac8b01745a55e9ea304ba68542bf88609efc6dc", 21223.2, 96857.6),
+        "9cfa7591317c3244ef367aacd37a711085365c55", 21223.2, 96857.6),
     "k_band_accum": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
-        "9d5a2ea099bd3ab525d954a0a87291a45e1ff051", 21681.1, 4096.0),
+        "cc1112fc3745d12a71cfc36426742563e57ded7b", 21681.1, 4096.0),
     "k_xch_wa": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
-        "7ac8b01745a55e9ea304ba68542bf88609efc6dc", 144059.9, 101040.5),
+        "9cfa7591317c3244ef367aacd37a711085365c55", 144059.9, 101040.5),
     "k_rows_dct2": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
-        "cdf6359e2693ebe0da55563fe8c530ff12da432c", 6234.0, 4112.0),
+        "590b0ae9774c7f08cb7c4c8dfa812361a5f4816a", 6234.0, 4112.0),
     "k_cols_solve": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
-        "cdf6359e2693ebe0da55563fe8c530ff12da432c", 2180.0, 8192.0),
+        "590b0ae9774c7f08cb7c4c8dfa812361a5f4816a", 2180.0, 8192.0),
     "k_rows_inverse": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
-        "cdf6359e2693ebe0da55563fe8c530ff12da432c", 6270.0, 8196.0),
+        "590b0ae9774c7f08cb7c4c8dfa812361a5f4816a", 6270.0, 8196.0),
     "k_band_gather": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
-        "9d5a2ea099bd3ab525d954a0a87291a45e1ff051", 23893.6, 18698.7),
+        "cc1112fc3745d12a71cfc36426742563e57ded7b", 23893.6, 18698.7),
     "k_xch_cellsum": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
-        "7ac8b01745a55e9ea304ba68542bf88609efc6dc", 80532.3, 16406.3),
+        "9cfa7591317c3244ef367aacd37a711085365c55", 80532.3, 16406.3),
 }
 
 
