@@ -32,23 +32,23 @@ PMC_FETCH_SCALE, PMC_WRITE_SCALE = 2.0, 1.0
 PMC_TRAFFIC = {
     # kernel: (source files, sha1, FETCH_SIZE KiB, WRITE_SIZE KiB)
     "k_band_place": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
-        "cc1112fc3745d12a71cfc36426742563e57ded7b", 16523.3, 64267.3),
+        "c2d96f5412b5e1b6a8df1c2529ecc0a33ab76ae3", 16523.3, 64267.3),
     "k_xch_spread": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
-        "9cfa7591317c3244ef367aacd37a711085365c55", 21223.2, 96857.6),
+        "48cc1784c4b86027881a74d5f3c613f533730779", 21223.2, 96857.6),
     "k_band_accum": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
-        "cc1112fc3745d12a71cfc36426742563e57ded7b", 21681.1, 4096.0),
+        "c2d96f5412b5e1b6a8df1c2529ecc0a33ab76ae3", 21681.1, 4096.0),
     "k_xch_wa": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
-        "9cfa7591317c3244ef367aacd37a711085365c55", 144059.9, 101040.5),
+        "48cc1784c4b86027881a74d5f3c613f533730779", 144059.9, 101040.5),
     "k_rows_dct2": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
-        "590b0ae9774c7f08cb7c4c8dfa812361a5f4816a", 6234.0, 4112.0),
+        "0134ed6e9ea28d5c84f9ccce250a6cd7290afe83", 6234.0, 4112.0),
     "k_cols_solve": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
-        "590b0ae9774c7f08cb7c4c8dfa812361a5f4816a", 2180.0, 8192.0),
+        "0134ed6e9ea28d5c84f9ccce250a6cd7290afe83", 2180.0, 8192.0),
     "k_rows_inverse": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
-        "590b0ae9774c7f08cb7c4c8dfa812361a5f4816a", 6270.0, 8196.0),
+        "0134ed6e9ea28d5c84f9ccce250a6cd7290afe83", 6270.0, 8196.0),
     "k_band_gather": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
-        "cc1112fc3745d12a71cfc36426742563e57ded7b", 23893.6, 18698.7),
+        "c2d96f5412b5e1b6a8df1c2529ecc0a33ab76ae3", 23893.6, 18698.7),
     "k_xch_cellsum": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
-        "9cfa7591317c3244ef367aacd37a711085365c55", 80532.3, 16406.3),
+        "48cc1784c4b86027881a74d5f3c613f533730779", 80532.3, 16406.3),
 }
 
 

@@ -342,9 +342,9 @@ int fftpl_density_map(const fftpl_grid* grid, int32_t num_cells, const float* x,
   }
   const GridF g = make_gridf(*grid);
   hipStream_t s = as_stream(stream);
-  if (density_scans(grid->n, num_cells))   // no band lists
-    return dev_status(launch_band_scatter(g, band_shape(grid->n, num_cells), x, y, w, h, base,
-                                          rho, s));
+  if (density_scans(grid->n, num_cells, kScanCellsAlloc))   // no band lists
+    return dev_status(launch_band_scan(g, band_shape(grid->n, num_cells), x, y, w, h, base,
+                                       rho, s));
   if (grid->n <= kBandMaxN) {
     // the banded scatter of the evaluation, its band lists in a temporary
     // stream-ordered allocation released on the stream after the scatter

@@ -154,7 +154,10 @@ __global__ void __launch_bounds__(NTA) k_band_accum(BandBatch<NB> bb) {
 // replace: the stateless map of 1000 to 8192 cells, n = 32 to 128, 25 -> 10.3 us
 // (n = 512, 8192 cells 24.9 -> 14.2).  On larger grids so few cells are many bins
 // each and the blocks' adds outweigh it (n = 1024, 8192 cells 24.7 -> 34.9 us).
-bool density_scans(int n, int m) { return n <= 512 && m <= kScanCells; }
+// Where the lists would have to be allocated for the call the line lies at
+// kScanCellsAlloc: 12k cells 31.2 -> 13.9 us, 16k 29.8 -> 17.2, 20k 30.0 -> 23.3, 32k
+// 30.3 -> 34.0 (the larger the map's cells, the earlier: n = 512, 32k cells 38.6).
+bool density_scans(int n, int m, int most) { return n <= 512 && m <= most; }
 
 __global__ void __launch_bounds__(512) k_band_scan(BandReq q) {
   constexpr int BINS = 1024;   // of a band
@@ -443,9 +446,28 @@ hipError_t noalloc_scratch(void** ptr) {
   return hipSuccess;
 }
 
+hipError_t launch_band_scan(const GridF& g, const BandLayout& L, const float* x,
+                            const float* y, const float* w, const float* h, const float* base,
+                            float* rho, hipStream_t s, Plan* tp) {
+  BandReq q;
+  q.g = g;
+  q.L = L;
+  q.x = x;
+  q.y = y;
+  q.w = w;
+  q.h = h;
+  q.base = base;
+  q.rho = rho;
+  hipLaunchKernelGGL(k_band_scan, dim3(L.nb), dim3(512), 0, s, q);
+  if (tp) plan_mark(*tp, "k_band_scan", s);
+  return hipGetLastError();
+}
+
 hipError_t launch_band_scatter(const GridF& g, const BandLayout& L, const float* x,
                                const float* y, const float* w, const float* h,
                                const float* base, float* rho, hipStream_t s, Plan* tp) {
+  if (density_scans(g.n, L.m, kScanCells))
+    return launch_band_scan(g, L, x, y, w, h, base, rho, s, tp);
   BandReq q;
   q.g = g;
   q.L = L;
@@ -456,11 +478,6 @@ hipError_t launch_band_scatter(const GridF& g, const BandLayout& L, const float*
   q.h = h;
   q.base = base;
   q.rho = rho;
-  if (density_scans(g.n, L.m)) {
-    hipLaunchKernelGGL(k_band_scan, dim3(L.nb), dim3(512), 0, s, q);
-    if (tp) plan_mark(*tp, "k_band_scan", s);
-    return hipGetLastError();
-  }
   return launch_band_scatter_batch(&q, 1, s, tp);
 }
 

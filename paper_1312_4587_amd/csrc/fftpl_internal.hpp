@@ -872,7 +872,8 @@ struct BandLayout {
 BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
                        size_t* bytes_out);
 constexpr int kScanCells = 8192;   // most cells read by every band block (no band lists)
-bool density_scans(int n, int m);   // the map alone takes no band lists
+constexpr int kScanCellsAlloc = 16384;   // the same where the lists would be allocated
+bool density_scans(int n, int m, int most);   // the map alone takes no band lists
 // Bands and counting blocks of a design (the pointers stay null).
 BandLayout band_shape(int n, int m);
 
@@ -914,6 +915,9 @@ hipError_t launch_band_gather_batch(const BandReq* reqs, int count, int grad_mod
 // first-band entry (after launch_band_scatter and the solve).
 hipError_t launch_band_gather(const GridF& g, const BandLayout& L, const float* exy,
                               const float* psi, int grad_mode, hipStream_t s);
+hipError_t launch_band_scan(const GridF& g, const BandLayout& L, const float* x,
+                            const float* y, const float* w, const float* h, const float* base,
+                            float* rho, hipStream_t s, Plan* tp = nullptr);
 hipError_t launch_band_scatter(const GridF& g, const BandLayout& L, const float* x,
                                const float* y, const float* w, const float* h,
                                const float* base, float* rho, hipStream_t s,

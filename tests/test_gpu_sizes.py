@@ -43,10 +43,10 @@ def test_density_map_block_sizes(F, m, n):
     assert rel_l2(host(rho).reshape(n, n), oracle.density_map(inst, b0)) < RTOL
 
 
-# small maps in one launch, without band lists (n <= 512, up to 8192 cells), and the
+# small maps in one launch, without band lists (n <= 512, up to 16384 cells), and the
 # first designs past it; no cells; each into an old map and again
 @pytest.mark.parametrize("m,n", [(0, 16), (1, 1), (2047, 31), (2049, 64), (8192, 512),
-                                 (8193, 512), (8192, 513), (5000, 7)])
+                                 (8193, 512), (8192, 513), (5000, 7), (16384, 128), (16385, 128)])
 def test_density_map_small(F, m, n):
     import torch
     inst = gen.make_instance((100, m, n), num_cells=max(m, 1), util=0.7, n=n, num_nets=0,
