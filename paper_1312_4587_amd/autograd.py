@@ -34,8 +34,9 @@ class _Objective(torch.autograd.Function):
         gy = torch.empty_like(y)
         out4 = torch.empty(4, dtype=torch.float64, device=x.device)
         fftpl.eval(ctx.plan, ctx.prob, x, y, ctx.lam, ctx.gamma, "exact", gx, gy, out4)
-        # scaled in place by the 0-dim float64 gradient (the products stay float32)
-        return gx.mul_(g_loss), gy.mul_(g_loss), None, None, None, None
+        # times the 0-dim float64 gradient (the products stay float32); out of place,
+        # as a batch of incoming gradients makes more than one result of gx
+        return torch.mul(gx, g_loss), torch.mul(gy, g_loss), None, None, None, None
 
 
 def objective(x, y, plan: fftpl.Plan, prob: fftpl.Problem, lam: float, gamma: float):
