@@ -90,7 +90,9 @@ template <int N, int BINS, bool LSE, bool DIRECT, int NB>
 __global__ void __launch_bounds__(NT, DIRECT ? 6 : 4) k_compact_mid(CompactBatch<NB> cb,
                                                     const float2* __restrict__ tw_g,
                                                     const float2* __restrict__ cs_g) {
-  extern __shared__ float2 smem[];
+  // (16 bytes: the scan's list is read and written in float4)
+  extern __shared__ __align__(16) float2 smem[];
+  static_assert(alignof(MidLds<N, BINS>) <= 16, "as aligned as smem");
   const CompactReq& q = cb.r[blockIdx.y];
   if ((int)blockIdx.x >= cb.nb) {
     const int k = (int)blockIdx.x - cb.nb;
