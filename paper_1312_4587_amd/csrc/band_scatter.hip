@@ -50,6 +50,14 @@ BandLayout band_shape(int n, int m) {
   return L;
 }
 
+// Entries of blk_off and of blk_cnt: as many as any design of up to m cells takes
+// on this grid (one just past a step of cpk has fewer counting blocks than the
+// last one before it), so that the memory of a design holds every smaller one.
+static size_t blk_entries(const BandLayout& L) {
+  const int most = std::min(kNumCus, (L.m + kBandThreads - 1) / kBandThreads);
+  return (size_t)std::max(L.nblk, most) * (L.nb + 1);
+}
+
 BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
                        size_t* bytes_out) {
   BandLayout L = band_shape(n, m);
@@ -76,9 +84,9 @@ BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
   const size_t o_eg = off;
   off = align256(off + sizeof(float2) * nreg);
   const size_t o_bo = off;
-  off = align256(off + sizeof(int32_t) * (size_t)L.nblk * (L.nb + 1));
+  off = align256(off + sizeof(int32_t) * blk_entries(L));
   const size_t o_bc = off;
-  off = align256(off + sizeof(int32_t) * (size_t)L.nblk * (L.nb + 1));
+  off = align256(off + sizeof(int32_t) * blk_entries(L));
   if (bytes_out) *bytes_out = off;
   if (work) {
     char* b = static_cast<char*>(work);
@@ -415,9 +423,9 @@ BandLayout band_layout_density(int n, int m, void* work, size_t* bytes_out) {
   const size_t o_ep = off;
   off = align256(off + sizeof(int32_t) * (size_t)m);
   const size_t o_bo = off;
-  off = align256(off + sizeof(int32_t) * (size_t)L.nblk * (L.nb + 1));
+  off = align256(off + sizeof(int32_t) * blk_entries(L));
   const size_t o_bc = off;
-  off = align256(off + sizeof(int32_t) * (size_t)L.nblk * (L.nb + 1));
+  off = align256(off + sizeof(int32_t) * blk_entries(L));
   if (bytes_out) *bytes_out = off;
   if (work) {
     char* b = static_cast<char*>(work);

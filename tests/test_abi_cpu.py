@@ -225,3 +225,19 @@ def test_roctx_ranges_only_in_the_flagged_build(tmp_path):
         nm = subprocess.run(["nm", obj], capture_output=True, text=True).stdout
         refs[bool(flag)] = ("roctxRangePush" in nm, "roctxRangePop" in nm)
     assert refs[False] == (False, False) and refs[True] == (True, True)
+
+
+# one workspace sized for the largest design serves every smaller one of its grid
+@pytest.mark.parametrize("n", [1, 16, 64, 256, 257, 512, 513, 1024])
+def test_work_bytes_never_shrink_as_cells_are_added(n):
+    lib = _lib()
+
+    def need(m):
+        v = ctypes.c_uint64()
+        assert lib.fftpl_problem_work_bytes(n, m, 3000, 12000, ctypes.byref(v)) == 0
+        return v.value
+
+    edges = [512 * 256 * k + d for k in (1, 2, 4, 8, 16) for d in (-1, 0, 1, 2)]
+    sizes = sorted(set(list(range(0, 3000000, 9973)) + edges + [255, 256, 257, 511, 512, 513]))
+    got = [need(m) for m in sizes]
+    assert [m for m, a, b in zip(sizes[1:], got, got[1:]) if b < a] == []
