@@ -97,19 +97,73 @@ __device__ __forceinline__ void place_block(const GridF& g, const LT& L, int k,
   }
 }
 
+// owner[a .. e - 1] = t for the window positions of every thread t's slice
+// (ascending over t, together all of the window's).  Short slices (`longs` unset)
+// are written by their own threads.  Otherwise each writes its first position and
+// a running maximum over the positions, KB per thread, fills in the rest: a
+// crowded band's slices are long, and writing them one after another took most
+// of its walk (a wavefront per slice: 37 of the 78 us of 123k cells crowded into
+// 12 bands of n = 512).  Every thread must call it; ends with a barrier.
+constexpr int kOwnFill = 32;   // most entries of a short slice
+template <int NTB, int KB>
+__device__ __forceinline__ void fill_owner(unsigned short* owner, int a, int e, bool longs) {
+  typedef unsigned short Chunk __attribute__((ext_vector_type(KB > 1 ? KB : 2)));
+  const int t = threadIdx.x;
+  if (!longs) {
+    for (int v = a; v < e; ++v) owner[v] = (unsigned short)t;
+    __syncthreads();
+    return;
+  }
+  __shared__ unsigned short wmax[NTB / kWave];
+  const int lane = t & (kWave - 1), w = t / kWave;
+  Chunk o = 0;
+  if constexpr (KB > 1)
+    reinterpret_cast<Chunk*>(owner)[t] = o;
+  else
+    owner[t] = 0;
+  __syncthreads();
+  if (a < e) owner[a] = (unsigned short)t;
+  __syncthreads();
+  if constexpr (KB > 1)
+    o = reinterpret_cast<Chunk*>(owner)[t];
+  else
+    o[0] = owner[t];
+#pragma unroll
+  for (int j = 1; j < KB; ++j) o[j] = max(o[j], o[j - 1]);
+  int m = o[KB - 1];
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int u = __shfl_up(m, off, kWave);
+    if (lane >= off) m = max(m, u);
+  }
+  if (lane == kWave - 1) wmax[w] = (unsigned short)m;
+  int before = __shfl_up(m, 1, kWave);   // of the wavefront's lower lanes
+  if (lane == 0) before = 0;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NTB / kWave; ++k)
+    if (k < w) before = max(before, (int)wmax[k]);
+#pragma unroll
+  for (int j = 0; j < KB; ++j) o[j] = max(o[j], (unsigned short)before);
+  if constexpr (KB > 1)
+    reinterpret_cast<Chunk*>(owner)[t] = o;
+  else
+    owner[t] = o[0];
+  __syncthreads();
+}
+
 // The entries of band `band` (band = nb: the tall cells) lie in one slice per
 // region: slice k holds blk_cnt[band][k] entries from index
 // k * stride + blk_off[band][k].  A block of NTB threads walks them in chunks
 // of NTB slices: the chunk's counts are scanned, and the chunk's entries are
-// taken in windows of NTB * KB.  For each window every slice writes its own
-// number into an LDS owner map at the window positions it covers (slices
-// longer than a wavefront are written by the whole wavefront), so a
+// taken in windows of NTB * KB.  For each window every slice enters its own
+// number into an LDS owner map at the window positions it covers, so a
 // thread finds the slice of its entry with one LDS read (a binary search over
 // the scan, ten dependent LDS reads per entry, cost the walk more than its
 // loads).  Thread t takes window entries t, t + NTB, ...: KB of them, whose
 // indices are all known before f(index) uses any, so the caller can issue
 // their loads together.  Every thread of the block must call it; `owner`
-// holds NTB * KB entries.  LT: BandLayout, or a request with its fields.
+// holds NTB * KB entries, 16-byte aligned.  LT: BandLayout, or a request with its fields.
 template <int NTB, int KB, typename LT, typename F>
 __device__ __forceinline__ void walk_band(const LT& L, int band, int64_t stride,
                                           int* pre, int64_t* start, unsigned short* owner,
@@ -122,24 +176,12 @@ __device__ __forceinline__ void walk_band(const LT& L, int band, int64_t stride,
     const int c = k < L.nblk ? L.blk_cnt[(size_t)band * L.nblk + k] : 0;
     const int o = k < L.nblk ? L.blk_off[(size_t)band * L.nblk + k] : 0;
     int tot;
-    const int ex = block_exclusive_scan<NTB>(c, &tot);
+    bool longs;   // any slice longer than kOwnFill
+    const int ex = block_exclusive_scan<NTB>(c, &tot, c > kOwnFill, &longs);
     pre[t] = ex;
     start[t] = (int64_t)k * stride + o;
     for (int w0 = 0; w0 < tot; w0 += W) {
-      // a slice of up to 64 window entries is written by its own thread,
-      // a longer one by its whole wavefront
-      const int a = max(ex, w0), e = min(ex + c, w0 + W);
-      const bool big = e - a > kWave;
-      if (!big)
-        for (int v = a; v < e; ++v) owner[v - w0] = (unsigned short)t;
-      unsigned long long bm = __ballot(big);
-      while (bm) {
-        const int l = __ffsll((long long)bm) - 1;
-        bm &= bm - 1;
-        const int ba = __shfl(a, l), be = __shfl(e, l), bt = __shfl(t, l);
-        for (int v = ba + (t & (kWave - 1)); v < be; v += kWave) owner[v - w0] = (unsigned short)bt;
-      }
-      __syncthreads();
+      fill_owner<NTB, KB>(owner, max(ex, w0) - w0, min(ex + c, w0 + W) - w0, longs);
       int64_t idx[KB];
 #pragma unroll
       for (int j = 0; j < KB; ++j) {
@@ -217,7 +259,7 @@ template <int NTB, int KB>
 struct WalkLds {
   int64_t start[NTB];
   int pre[NTB];
-  unsigned short owner[NTB * KB];
+  alignas(16) unsigned short owner[NTB * KB];
 };
 
 // Adds the cells of band `band` (rows r0 .. r0 + R - 1) into acc (R rows of n

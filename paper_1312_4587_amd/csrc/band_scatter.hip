@@ -209,7 +209,7 @@ __global__ void __launch_bounds__(NTG) k_band_gather(BandBatch<NB> bb) {
   __shared__ float2 rows[5 * kBandMaxN];
   __shared__ int pre[NTG];
   __shared__ int64_t start[NTG];
-  __shared__ unsigned short owner[NTG * B];
+  __shared__ __align__(16) unsigned short owner[NTG * B];
   const int t = threadIdx.x;
   const int n = g.n, R = L.rows, band = xcd_order(blockIdx.x, gridDim.x);
   const int r0 = band * R, nr = min(R + 1, n - r0);

@@ -601,11 +601,14 @@ __device__ __forceinline__ int xcd_order(int b, int nb) {
   return b / (kNumXcd * G) * (kNumXcd * G) + (b % kNumXcd) * G + b / kNumXcd % G;
 }
 
-// Exclusive prefix sum over a block of NT threads; *total gets the block sum.
+// Exclusive prefix sum over a block of NT threads; *total gets the block sum,
+// *any (if given) whether any thread's flag is set.
 template <int NT>
-__device__ __forceinline__ int block_exclusive_scan(int v, int* total) {
+__device__ __forceinline__ int block_exclusive_scan(int v, int* total, bool flag = false,
+                                                    bool* any = nullptr) {
   constexpr int NW = NT / kWave;
   __shared__ int wsum[NW];
+  __shared__ int wany[NW];
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
   int inc = v;
 #pragma unroll
@@ -613,16 +616,22 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* total) {
     const int u = __shfl_up(inc, off, kWave);
     if (lane >= off) inc += u;
   }
-  if (lane == kWave - 1) wsum[w] = inc;
+  const bool wave_any = any && __any(flag);
+  if (lane == kWave - 1) {
+    wsum[w] = inc;
+    if (any) wany[w] = wave_any;
+  }
   __syncthreads();
-  int woff = 0, tot = 0;
+  int woff = 0, tot = 0, or_all = 0;
 #pragma unroll
   for (int k = 0; k < NW; ++k) {
     if (k < w) woff += wsum[k];
     tot += wsum[k];
+    if (any) or_all |= wany[k];
   }
   __syncthreads();
   *total = tot;
+  if (any) *any = or_all != 0;
   return woff + inc - v;
 }
 
