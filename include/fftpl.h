@@ -253,7 +253,7 @@ int fftpl_dark_nodes(double xl, double yl, double xh, double yh, int32_t num_rec
  * (counting sort by band, fixed-point LDS sums: the same bits on every run)
  * with its band lists in a temporary allocation made and released on
  * `stream` (hipMallocAsync / hipFreeAsync; FFTPL_E_NOMEM if it fails; none up to
- * 16384 cells with n <= 512); the
+ * 16384 cells with n <= 256 or 8192 with n <= 512); the
  * caller that keeps a workspace uses fftpl_problem_density, the caller that
  * cannot allocate fftpl_density_map_noalloc.  For n > 1024 it accumulates
  * with float atomics: the rounding order (not the value beyond float32

@@ -342,9 +342,9 @@ int fftpl_density_map(const fftpl_grid* grid, int32_t num_cells, const float* x,
   }
   const GridF g = make_gridf(*grid);
   hipStream_t s = as_stream(stream);
-  if (density_scans(grid->n, num_cells, kScanCellsAlloc))   // no band lists
-    return dev_status(launch_band_scan(g, band_shape(grid->n, num_cells), x, y, w, h, base,
-                                       rho, s));
+  if (density_scans(grid->n, num_cells, true))   // no band lists
+    return dev_status(launch_band_scan(g, band_shape(grid->n, num_cells, false), x, y, w, h,
+                                       base, rho, s));
   if (grid->n <= kBandMaxN) {
     // the banded scatter of the evaluation, its band lists in a temporary
     // stream-ordered allocation released on the stream after the scatter
@@ -620,13 +620,13 @@ int check_eval(const Plan& p, const fftpl_problem* prob, const float* x, const f
   r->out4 = out4;
   r->path = path;
   r->g = make_gridf(prob->grid);
-  r->L = band_layout(p.n, m, prob->num_nets, prob->num_pins,
-                     path == FFTPL_PATH_ATOMIC ? nullptr : prob->work, nullptr);
   if (path == FFTPL_PATH_EXCHANGE) {
     r->xd = xd;
     r->X = xch_index(xd, prob->xindex);
     r->compact = compact_design(p.n, xd);
   }
+  r->L = band_layout(p.n, m, prob->num_nets, prob->num_pins,
+                     path == FFTPL_PATH_ATOMIC ? nullptr : prob->work, nullptr, r->compact);
   return FFTPL_OK;
 }
 

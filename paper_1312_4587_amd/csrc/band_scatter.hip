@@ -28,12 +28,15 @@ namespace fftpl {
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-BandLayout band_shape(int n, int m) {
+BandLayout band_shape(int n, int m, bool pairs) {
   BandLayout L;
   L.n = n;
-  // Two rows at least (a row pair is what one FFT block transforms), at most
-  // 4 for n <= 1024: rows * n <= 4096 bins, at most 256 bands, the last short.
-  L.rows = n <= 512 ? 2 : (n + 255) / 256;
+  // As few rows as leave at most 256 bands, at most 4 for n <= 1024: rows * n <=
+  // 4096 bins, the last band short.  pairs: two rows at least, which is what a
+  // band block of the compact evaluation transforms; on grids of up to 256 that
+  // is half the blocks, each with twice the cells (the map alone, 1M cells, n = 64:
+  // 98 us in pairs, 51 us in single rows; crowded cells, n = 256, 446 and 231).
+  L.rows = pairs && n <= kCompactPairN ? 2 : (n + 255) / 256;
   L.nb = (n + L.rows - 1) / L.rows;
   L.m = m;
   // Cells per counting block: the fewest (512 threads times 1, 2, 4 or 8
@@ -51,16 +54,18 @@ BandLayout band_shape(int n, int m) {
 }
 
 // Entries of blk_off and of blk_cnt: as many as any design of up to m cells takes
-// on this grid (one just past a step of cpk has fewer counting blocks than the
-// last one before it), so that the memory of a design holds every smaller one.
+// on this grid, in bands of either shape (a design just past a step of cpk has fewer
+// counting blocks than the last one before it), so that the memory of a design
+// holds every smaller one.
 static size_t blk_entries(const BandLayout& L) {
   const int most = std::min(kNumCus, (L.m + kBandThreads - 1) / kBandThreads);
-  return (size_t)std::max(L.nblk, most) * (L.nb + 1);
+  const int bands = std::max(L.nb, std::min(L.n, kMaxBandCount));
+  return (size_t)std::max(L.nblk, most) * (bands + 1);
 }
 
 BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
-                       size_t* bytes_out) {
-  BandLayout L = band_shape(n, m);
+                       size_t* bytes_out, bool pairs) {
+  BandLayout L = band_shape(n, m, pairs);
   L.nwa = (num_nets + 255) / 256;
   // wirelength partials: 4 per 256 nets (slot path) or 2 per net block of at
   // least kXchSmallTarget pins (exchange path)
@@ -121,12 +126,14 @@ __global__ void __launch_bounds__(kBandThreads) k_band_place(BandBatch<NB> bb) {
 }
 
 // NTA threads taking KB entries each, at most BINS bins per band: (1024, 8,
-// 4096), or (512, 4, 1024) for n <= 512 and up to 1024 cells per band on
+// 4096), or (512, 4, 1024) for batches with n <= 512 and up to 1024 cells per band on
 // average.  Such a band holds a few hundred entries, less than the larger
 // block's fixed work (owner map, scan over the threads, clears), and the smaller
 // block leaves room for four per CU: a batch of eight designs at n = 256 takes
-// 12.4 us instead of 51.5 us, one design at n = 512 about as long as before
-// (200k cells 7.8 -> 8.2 us, 123k 7.9 -> 7.6 us).
+// 12.4 us instead of 51.5 us.  One design has at most one block per CU and nothing
+// to share it with: the larger block takes as long where the cells are spread (200k
+// cells, n = 512, 7.8 us against 8.2) and less where they crowd into a few bands
+// (123k cells in a dozen bands 56 us, the whole map, against 74).
 template <int NB, int NTA, int KB, int BINS>
 __global__ void __launch_bounds__(NTA) k_band_accum(BandBatch<NB> bb) {
   const BandReq& q = bb.r[blockIdx.y];
@@ -159,36 +166,36 @@ __global__ void __launch_bounds__(NTA) k_band_accum(BandBatch<NB> bb) {
 // The density map of a small design in one launch: each band's block reads every
 // cell, so there are no band lists and no memory to hold them.  Up to
 // kScanCells cells the reads cost less than the place pass and the launch they
-// replace: the stateless map of 1000 to 8192 cells, n = 32 to 128, 25 -> 10.3 us
-// (n = 512, 8192 cells 24.9 -> 14.2).  On larger grids so few cells are many bins
+// replace: the stateless map of 1000 to 8192 cells, n = 32 to 128, 25 -> 9.6 us
+// (n = 512, 8192 cells 23.6 -> 12.9).  On larger grids so few cells are many bins
 // each and the blocks' adds outweigh it (n = 1024, 8192 cells 24.7 -> 34.9 us).
 // Where the lists would have to be allocated for the call the line lies at
-// kScanCellsAlloc: 12k cells 31.2 -> 13.9 us, 16k 29.8 -> 17.2, 20k 30.0 -> 23.3, 32k
-// 30.3 -> 34.0 (the larger the map's cells, the earlier: n = 512, 32k cells 38.6).
-bool density_scans(int n, int m, int most) { return n <= 512 && m <= most; }
+// kScanCellsAlloc for n <= 256: n = 64, 16384 cells 30 -> 11.1 us, 20k 30 -> 23.
+// Past n = 256 a few large cells, each added by one thread, are enough to lose it
+// (n = 300, 12288 cells, one in a hundred 30 bins wide: 33 us, through lists 26).
+// There is at most one block per CU: 1024 threads, for cells that crowd into a few
+// bands (16384 cells, n = 256: 17.7 us, with 512 threads on row pairs 30.9, by way
+// of the lists 24.8).
+bool density_scans(int n, int m, bool alloc) {
+  return n <= 512 && m <= (alloc && n <= 256 ? kScanCellsAlloc : kScanCells);
+}
 
-__global__ void __launch_bounds__(512) k_band_scan(BandReq q) {
-  constexpr int BINS = 1024;   // of a band
+constexpr int kScanThreads = 1024;
+__global__ void __launch_bounds__(kScanThreads) k_band_scan(BandReq q) {
+  constexpr int NTS = kScanThreads, LIST = 2048, BINS = 1024;   // bins of a band
   __shared__ unsigned long long acc[BINS];
-  __shared__ ScanLds<512, 2048> lds;
+  __shared__ ScanLds<NTS, LIST> lds;
   const int t = threadIdx.x, n = q.g.n, R = q.L.rows;
   const int band = xcd_order(blockIdx.x, gridDim.x), r0 = band * R;
   const int cells = min(R, n - r0) * n;
   const size_t o = (size_t)r0 * n;
-  constexpr int PA = BINS / 512;
-  float bv[PA];
-#pragma unroll
-  for (int j = 0; j < PA; ++j)
-    bv[j] = q.base ? q.base[o + min(t + j * 512, cells - 1)] : 0.0f;
-  for (int k = t; k < cells; k += 512) acc[k] = 0ull;
+  static_assert(BINS == NTS, "one bin per thread");
+  const float bv = q.base ? q.base[o + min(t, cells - 1)] : 0.0f;
+  if (t < cells) acc[t] = 0ull;
   __syncthreads();
-  band_scan<512, 2048>(q.g, q.L, band, q.x, q.y, q.w, q.h, acc, lds);
+  band_scan<NTS, LIST>(q.g, q.L, band, q.x, q.y, q.w, q.h, acc, lds);
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < PA; ++j) {
-    const int k = t + j * 512;
-    if (k < cells) q.rho[o + k] = bv[j] + (float)((double)acc[k] * kAccUnit);
-  }
+  if (t < cells) q.rho[o + t] = bv + (float)((double)acc[t] * kAccUnit);
 }
 
 // Density gradient of every cell listed in band b with b its first band,
@@ -340,7 +347,7 @@ static hipError_t band_scatter_nb(const BandBatch<NB>& bb, int max_nblk, int max
     if (tp) plan_mark(*tp, "k_band_place", s);
   }
   const int n = bb.r[0].L.n, nb = bb.r[0].L.nb;
-  if (n <= 512 && max_m <= 1024 * (int64_t)nb)
+  if (bb.count > 1 && n <= 512 && max_m <= 1024 * (int64_t)nb)
     hipLaunchKernelGGL((k_band_accum<NB, 512, 4, 1024>), dim3(nb, bb.count), dim3(512), 0, s, bb);
   else
     hipLaunchKernelGGL((k_band_accum<NB, 1024, B, 4096>), dim3(nb, bb.count), dim3(1024), 0, s, bb);
@@ -414,7 +421,7 @@ void* g_scratch_ptr[kMaxDevicesNoalloc] = {};
 
 // Band lists of the density scatter alone (no wirelength or gather arrays).
 BandLayout band_layout_density(int n, int m, void* work, size_t* bytes_out) {
-  BandLayout L = band_shape(n, m);
+  BandLayout L = band_shape(n, m, false);
   size_t off = 0;
   const size_t o_en = off;
   off = align256(off + sizeof(float4) * (size_t)L.nblk * L.region);
@@ -466,7 +473,7 @@ hipError_t launch_band_scan(const GridF& g, const BandLayout& L, const float* x,
   q.h = h;
   q.base = base;
   q.rho = rho;
-  hipLaunchKernelGGL(k_band_scan, dim3(L.nb), dim3(512), 0, s, q);
+  hipLaunchKernelGGL(k_band_scan, dim3(L.nb), dim3(kScanThreads), 0, s, q);
   if (tp) plan_mark(*tp, "k_band_scan", s);
   return hipGetLastError();
 }
@@ -474,7 +481,7 @@ hipError_t launch_band_scan(const GridF& g, const BandLayout& L, const float* x,
 hipError_t launch_band_scatter(const GridF& g, const BandLayout& L, const float* x,
                                const float* y, const float* w, const float* h,
                                const float* base, float* rho, hipStream_t s, Plan* tp) {
-  if (density_scans(g.n, L.m, kScanCells))
+  if (density_scans(g.n, L.m, false))
     return launch_band_scan(g, L, x, y, w, h, base, rho, s, tp);
   BandReq q;
   q.g = g;

@@ -855,6 +855,7 @@ inline int wa_big_grid(int num_nets) {
 // list every band block walks), then one block per band accumulates its rows
 // in LDS and writes them out.  Needs n <= kBandMaxN.
 constexpr int kMaxBands = 4;
+constexpr int kMaxBandCount = 256;     // most bands of a grid
 constexpr int kBandMaxN = 1024;
 constexpr int kBandThreads = 512;      // threads of a counting / placing block
 constexpr int kCellBatch = 8;          // most cells whose loads a thread issues together
@@ -879,12 +880,14 @@ struct BandLayout {
   int nwa = 0;                   // blocks of each wirelength kernel
 };
 BandLayout band_layout(int n, int m, int num_nets, int num_pins, void* work,
-                       size_t* bytes_out);
+                       size_t* bytes_out, bool pairs = false);
 constexpr int kScanCells = 8192;   // most cells read by every band block (no band lists)
 constexpr int kScanCellsAlloc = 16384;   // the same where the lists would be allocated
-bool density_scans(int n, int m, int most);   // the map alone takes no band lists
-// Bands and counting blocks of a design (the pointers stay null).
-BandLayout band_shape(int n, int m);
+// whether the map alone takes no band lists; alloc: they would be allocated for it
+bool density_scans(int n, int m, bool alloc);
+// Bands (pairs: of two rows at least) and counting blocks of a design (the pointers
+// stay null).
+BandLayout band_shape(int n, int m, bool pairs);
 
 // ---- batches: several designs of one grid side in one launch per stage ----
 // Kernels take a batch of per-design descriptors by value (the kernel
