@@ -193,17 +193,22 @@ __global__ void __launch_bounds__(kGatherThreads)
 // FIELD from two maps that together are larger than an XCD's L2 (4 MB).  The two
 // are read one after the other: a block keeps its cells in LDS (each lane its
 // own), gathers Ex for all of them and then Ey, and as the blocks of the grid
-// run in step, most of the chip works on one map at a time.  Cells and results
-// pass the caches by (non-temporal).  m = 2.1M, n = 1024, random order: 72.5 ->
-// 62.8 us (L2 misses bound both); m = 1M: 41.4 -> 33.4; n = 2048: 155 -> 142.
+// run in step, most of the chip works on one map at a time.  Results pass the
+// caches by (non-temporal; the cells too made clustered ones slower, 37 -> 42 us).
+// m = 2.1M, n = 1024, random order: 72.5 -> 60 us (L2 misses bound both); m = 1M:
+// 41.4 -> 30; n = 2048: 155 -> 134.
 // Blocks of four or five cells per lane drift apart and measured the same at
 // 2.1M; one launch half per map (cells read twice) 54 us, but 24.9 in place of
-// 19.0 us when the cells are ordered by position.
+// 19.3 us when the cells are ordered by position.
+// A large cell's bins are shared out over its wavefront, in the first pass and for
+// both maps: by its own lane, 2.1M cells with one in a hundred 30 bins wide took
+// 1140 us (585 where one pass summed both maps), now 103.
 // Smaller maps (n = 512: 2 MB both) stay in the L2 together, 27.5 us in one pass
 // against 34.8 in two; fewer cells than the chip has lanes (8 blocks of 256 on
 // each of 256 compute units) are one cell per lane in flight at once, and gain
 // nothing (n = 1024: 20.9 against 19.7 us at 262k, 18.1 against 23.9 at 123k; at
-// 524k 26.3 against 23.5).
+// 524k 26.3 against 23.5).  All cells in one place, both maps in the L1, is what it
+// loses (2.1M 13.0 -> 17.6).
 constexpr int kGatherPhaseCells = 2;
 constexpr int kTwoMapsMinN = 1024;
 constexpr int kTwoMapsMinCells = 524288;
@@ -218,12 +223,13 @@ __global__ void __launch_bounds__(kGatherThreads, 8)
   const int n = g.n, t = threadIdx.x;
   const int64_t i0 = (int64_t)blockIdx.x * kGatherThreads + t;
   const int64_t step = (int64_t)gridDim.x * kGatherThreads;
+  const int lane = t & (kWave - 1);
 #pragma unroll
   for (int c = 0; c < kGatherPhaseCells; ++c) {
     const int64_t i = min(i0 + c * step, (int64_t)m - 1);
-    cell[c][t] = make_float4(__builtin_nontemporal_load(x + i), __builtin_nontemporal_load(y + i),
-                             __builtin_nontemporal_load(w + i), __builtin_nontemporal_load(h + i));
+    cell[c][t] = make_float4(x[i], y[i], w[i], h[i]);
   }
+  unsigned done = 0;   // the lane's large cells, both sums taken in the first pass
 #pragma unroll 1
   for (int p = 0; p < 2; ++p) {
     const float* __restrict__ e = p ? ey : ex;
@@ -232,10 +238,35 @@ __global__ void __launch_bounds__(kGatherThreads, 8)
 #pragma unroll 1
     for (int c = 0; c < kGatherPhaseCells; ++c) {
       const int64_t i = i0 + c * step;
-      if (i >= m) break;
       const float4 q = cell[c][t];
       const Span sx = cell_span(q.x, q.z, g.xl, g.inv_bw, n);
       const Span sy = cell_span(q.y, q.w, g.yl, g.inv_bh, n);
+      if (p == 0) {
+        // large cells: each by the whole wavefront, eight columns of eight rows at a time
+        const bool large = i < m && sx.i0 <= sx.i1 && sy.i0 <= sy.i1 && !WideRows::fits(sx, sy, n);
+        for (unsigned long long bm = __ballot(large); bm; bm &= bm - 1) {
+          const int l = __ffsll((long long)bm) - 1;
+          const Span bx = span_from_edges(__shfl(sx.lo, l), __shfl(sx.hi, l), n);
+          const Span by = span_from_edges(__shfl(sy.lo, l), __shfl(sy.hi, l), n);
+          float ax = 0.0f, ay = 0.0f;
+          for (int iy = by.i0 + (lane >> 3); iy <= by.i1; iy += 8) {
+            const float oy = span_overlap(by, iy);
+            for (int ix = bx.i0 + (lane & 7); ix <= bx.i1; ix += 8) {
+              const float ov = span_overlap(bx, ix) * oy;
+              ax += ov * ex[(int64_t)iy * n + ix];
+              ay += ov * ey[(int64_t)iy * n + ix];
+            }
+          }
+          ax = scale * (-g.inv_bw * wave_sum_dpp(ax));
+          ay = scale * (-g.inv_bh * wave_sum_dpp(ay));
+          if (lane == l) {
+            gx[i] = accumulate ? gx[i] + ax : ax;
+            gy[i] = accumulate ? gy[i] + ay : ay;
+            done |= 1u << c;
+          }
+        }
+      }
+      if (i >= m || (done >> c & 1)) continue;
       const float a = scale * (-inv * span_map_sum(n, sx, sy, e));
       if (accumulate)
         out[i] += a;

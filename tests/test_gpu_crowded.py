@@ -1,6 +1,7 @@
-"""Designs whose cells crowd into a few bands of the density scatter (early in a
-placement), against the FP64 oracle: relative L2 <= 1e-5, the bar of every float32
-result here.  The library's sums do not depend on the order of its lists, so the
+"""Designs that load the lanes and blocks of a kernel unevenly, against the FP64
+oracle (relative L2 <= 1e-5, the bar of every float32 result here): cells crowded
+into a few bands of the density scatter, as early in a placement, and large cells
+among small ones.  The library's sums do not depend on the order of its lists, so the
 calls that share them agree bit for bit."""
 import dataclasses
 
@@ -79,3 +80,34 @@ def test_map_and_evaluation_share_a_workspace(F, m, n, dct):
     assert rel_l2(host(runs[0][0]), want["gx"]) < RTOL
     assert rel_l2(host(runs[0][1]), want["gy"]) < RTOL
     plan.close()
+
+
+# large cells among small ones in the gather that reads one map after the other: a
+# wavefront shares out the bins of each (past eight columns or three rows), several to
+# a wavefront, none, partly and wholly outside the region
+@pytest.mark.parametrize("m,n,share,run", [(524288, 1024, 0.01, 1), (524301, 1030, 0.0001, 1),
+                                           (524299, 1024, 0.01, 64)])
+def test_field_gather_of_large_cells(F, m, n, share, run):
+    import torch
+    inst = gen.make_instance((113, m, n), num_cells=m, util=0.7, n=n, num_nets=0)
+    rng = np.random.default_rng((114, m))
+    # unit bins and dyadic edges, so that float32 and the oracle see the same bins
+    big = np.repeat(rng.random(m // run + 1) < share, run)[:m]
+    w, h = (np.where(big, rng.integers(1, 40 * 32, m), rng.integers(1, 64, m)) / 32
+            for _ in range(2))
+    x, y = (rng.integers(-64, 64 * (n + 1), m) / 64 for _ in range(2))
+    x, y, w, h = (np.asarray(a, np.float32) for a in (x, y, w, h))
+    inst = dataclasses.replace(inst, x=x, y=y, w=w, h=h, xl=0.0, yl=0.0, bin_w=1.0, bin_h=1.0)
+    ex, ey = (rng.standard_normal((n, n)).astype(np.float32) for _ in range(2))
+    c = DeviceCells(inst)
+    gx, gy = torch.full((m,), 7.0, device="cuda"), torch.full((m,), -3.0, device="cuda")
+    dx, dy = (torch.as_tensor(v.ravel()).cuda() for v in (ex, ey))
+    say("gather of large cells", m, n, share, run)
+    for accumulate in (0, 1):
+        F.field_gather(F.Grid.of(inst), c.x, c.y, c.w, c.h, dx, dy, None, "field", 0.5,
+                       accumulate, gx, gy)
+    torch.cuda.synchronize()
+    rx, ry = oracle.field_gradient(inst, ex.astype(np.float64), ey.astype(np.float64))
+    assert rel_l2(host(gx), rx) < RTOL and rel_l2(host(gy), ry) < RTOL
+    # the small cells by themselves: the large ones would hide them in the norm
+    assert rel_l2(host(gx)[~big], rx[~big]) < RTOL and rel_l2(host(gy)[~big], ry[~big]) < RTOL
