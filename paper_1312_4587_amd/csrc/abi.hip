@@ -695,8 +695,7 @@ int run_compact_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream_
   CompactReq cr[kMaxBatch];
   SpectralArgs sa[kMaxBatch];
   bool place = false, spread = false;
-  for (int i = 0; i < count; ++i)
-    spread = spread || compact_spreads(p, rs[i].xd.m);
+  for (int i = 0; i < count; ++i) spread = spread || compact_spreads(rs[i].xd.m);
   for (int i = 0; i < count; ++i) {
     const EvalReq& r = rs[i];
     const bool scan = r.xd.m <= kScanCells;

@@ -1,7 +1,7 @@
 """Designs that load the lanes and blocks of a kernel unevenly, against the FP64
 oracle (relative L2 <= 1e-5, the bar of every float32 result here): cells crowded
-into a few bands of the density scatter, as early in a placement, and large cells
-among small ones.  The library's sums do not depend on the order of its lists, so the
+into a few bands of the density scatter, as early in a placement, large cells among
+small ones, and many cells on small grids.  The library's sums do not depend on the order of its lists, so the
 calls that share them agree bit for bit."""
 import dataclasses
 
@@ -111,3 +111,37 @@ def test_field_gather_of_large_cells(F, m, n, share, run):
     assert rel_l2(host(gx), rx) < RTOL and rel_l2(host(gy), ry) < RTOL
     # the small cells by themselves: the large ones would hide them in the norm
     assert rel_l2(host(gx)[~big], rx[~big]) < RTOL and rel_l2(host(gy)[~big], ry[~big]) < RTOL
+
+
+# compact evaluations whose positions are spread to the pins: grids of up to 256, with
+# the row transform fused into the scatter and not, and past n = 512; the cells over
+# the region, clustered, and crowded into a few bands
+@pytest.mark.parametrize("where", ["uniform", "cluster", "crowd"])
+@pytest.mark.parametrize("m,n,mode,dct", [
+    (262145, 256, "field", "fft"), (300000, 128, "exact", "fft"), (300000, 64, "field", "fft"),
+    (300000, 32, "exact", "fft"), (270001, 192, "field", "gemm_f32"),
+    (300000, 512, "exact", "fft"), (300000, 1024, "field", "fft"),
+    (300000, 576, "exact", "gemm_f32")])
+def test_eval_spread_forms(F, m, n, mode, dct, where):
+    import torch
+    inst = gen.make_instance((115, m, n), num_cells=m, util=0.8, n=n, num_nets=m, num_macros=2,
+                             macro_area_frac=0.1, hi_frac=0.002, hi_range=(20, 400))
+    if where != "uniform":
+        rng, s = np.random.default_rng((116, m)), 0.15 if where == "cluster" else 0.01
+        x, y = (np.clip(0.5 + s * rng.standard_normal(m), 0.01, 0.99) for _ in range(2))
+        inst = dataclasses.replace(inst, x=(inst.xl + x * n * inst.bin_w).astype(np.float32),
+                                   y=(inst.yl + y * n * inst.bin_h).astype(np.float32))
+    plan, prob, c = F.Plan(n, dct), F.Problem.from_instance(inst), DeviceCells(inst)
+    gx, gy = (torch.empty(m, device="cuda") for _ in range(2))
+    out = torch.empty(4, dtype=torch.float64, device="cuda")
+    say("eval", m, n, mode, dct, where)
+    F.eval(plan, prob, c.x, c.y, 1.5, inst.gamma, mode, gx, gy, out)
+    torch.cuda.synchronize()
+    want = oracle.evaluate(inst, lam=1.5, grad_mode=mode)
+    assert rel_l2(host(plan.maps()[0]), want["rho"]) < RTOL
+    assert rel_l2(host(gx), want["gx"]) < RTOL and rel_l2(host(gy), want["gy"]) < RTOL
+    o = host(out)
+    for k, name in enumerate(("energy", "wa", "hpwl")):
+        assert abs(o[k] - want[name]) <= RTOL * abs(want[name])
+    assert abs(o[3] - want["overflow"]) < RTOL
+    plan.close()
