@@ -698,7 +698,7 @@ int run_compact_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream_
   for (int i = 0; i < count; ++i) spread = spread || compact_spreads(rs[i].xd.m);
   for (int i = 0; i < count; ++i) {
     const EvalReq& r = rs[i];
-    const bool scan = r.xd.m <= kScanCells;
+    const bool scan = compact_scans(p.n, r.xd.m);
     br[i].g = r.g;
     br[i].L = r.L;
     br[i].L.epos = nullptr;   // the gradient is gathered per cell

@@ -1143,6 +1143,7 @@ hipError_t launch_compact_place(const BandReq* br, const XchReq* xr, int count, 
 hipError_t launch_compact_mid(const Plan& p, const CompactReq* reqs, int count, int wl_model,
                               bool fuse_rows, bool spread, hipStream_t s);
 bool compact_fuses_rows(const Plan& p);
+bool compact_scans(int n, int m);   // whether the band blocks read the cells themselves
 bool compact_spreads(int m);   // whether the positions are spread to the pins
 // per-cell gradients: density part gathered per cell, pin sums, the scalars
 hipError_t launch_compact_cells(const SumReq* reqs, int count, int grad_mode, hipStream_t s);

@@ -113,16 +113,18 @@ def test_field_gather_of_large_cells(F, m, n, share, run):
     assert rel_l2(host(gx)[~big], rx[~big]) < RTOL and rel_l2(host(gy)[~big], ry[~big]) < RTOL
 
 
-# compact evaluations whose positions are spread to the pins: grids of up to 256, with
-# the row transform fused into the scatter and not, and past n = 512; the cells over
-# the region, clustered, and crowded into a few bands
+# compact evaluations by form, most of them with the positions spread to the pins: grids
+# of up to 256, with the row transform fused into the scatter and not, and past n =
+# 512; the cells over the region, clustered, and crowded into a few bands
 @pytest.mark.parametrize("where", ["uniform", "cluster", "crowd"])
 @pytest.mark.parametrize("m,n,mode,dct", [
     (262145, 256, "field", "fft"), (300000, 128, "exact", "fft"), (300000, 64, "field", "fft"),
     (300000, 32, "exact", "fft"), (270001, 192, "field", "gemm_f32"),
     (300000, 512, "exact", "fft"), (300000, 1024, "field", "fft"),
-    (300000, 576, "exact", "gemm_f32")])
-def test_eval_spread_forms(F, m, n, mode, dct, where):
+    (300000, 576, "exact", "gemm_f32"),
+    # cells of many bins each: read by the band blocks, and by way of the lists
+    (2048, 1024, "field", "fft"), (2049, 1024, "exact", "fft"), (2049, 576, "field", "gemm_f32")])
+def test_eval_compact_forms(F, m, n, mode, dct, where):
     import torch
     inst = gen.make_instance((115, m, n), num_cells=m, util=0.8, n=n, num_nets=m, num_macros=2,
                              macro_area_frac=0.1, hi_frac=0.002, hi_range=(20, 400))
