@@ -786,7 +786,16 @@ int run_compact_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream_
 // density branch reaches it.  With per-kernel timing on, everything runs on
 // `s` so that consecutive events bracket single kernels.
 int run_exchange_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream_t s) {
-  if (rs[0].compact) return run_compact_group(p, rs, count, grad_mode, s);
+  int compact = 0;
+  for (int i = 0; i < count; ++i) compact += rs[i].compact;
+  if (compact == count) return run_compact_group(p, rs, count, grad_mode, s);
+  // some are too large for the compact form: all take this one together (apart, 1.2M
+  // and 200k cells in turn, four requests of n = 1024, took 473 us, so 394), and
+  // request i's maps are in slot i
+  for (int i = 0; i < count; ++i)
+    if (rs[i].compact)
+      rs[i].L = band_layout(p.n, rs[i].xd.m, rs[i].xd.num_nets, rs[i].xd.num_pins,
+                            rs[i].prob->work, nullptr, false);
   const bool grads = rs[0].gx != nullptr;
   const size_t nn = (size_t)p.n * p.n;
   const bool overlap = !p.timing;
@@ -954,7 +963,6 @@ bool joins_group(const EvalReq* g, int count, const EvalReq& r, int max_batch) {
   if (count >= max_batch || r.path != FFTPL_PATH_EXCHANGE) return false;
   if (count == 0) return true;
   const bool big = g[0].xd.cap > kXchPinLds2;
-  if (r.compact != g[0].compact) return false;
   if (r.prob->wl_model != g[0].prob->wl_model || (r.xd.cap > kXchPinLds2) != big) return false;
   for (int i = 0; i < count; ++i)
     if (ranges_overlap(g[i].prob->work, g[i].prob->work_bytes, r.prob->work,

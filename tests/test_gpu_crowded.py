@@ -147,3 +147,31 @@ def test_eval_compact_forms(F, m, n, mode, dct, where):
         assert abs(o[k] - want[name]) <= RTOL * abs(want[name])
     assert abs(o[3] - want["overflow"]) < RTOL
     plan.close()
+
+
+# a batch with a design past the compact form's cells among smaller ones is one group
+# still: request i's maps in slot i, every result that of its own evaluation
+@pytest.mark.parametrize("sizes,n,mode", [([3000, 1048577, 40000], 256, "field"),
+                                          ([1048577, 300000, 5000], 1024, "exact")])
+def test_batch_with_a_design_past_the_compact_form(F, sizes, n, mode):
+    import torch
+    insts = [gen.make_instance((117, k), num_cells=m, util=0.7, n=n, num_nets=m)
+             for k, m in enumerate(sizes)]
+    probs = [F.Problem.from_instance(i) for i in insts]
+    cells = [DeviceCells(i) for i in insts]
+    plan, single = F.Plan(n, max_batch=4), F.Plan(n)
+    gxs, gys = ([torch.empty(m, device="cuda") for m in sizes] for _ in range(2))
+    out = torch.empty((len(sizes), 4), dtype=torch.float64, device="cuda")
+    say("batch", sizes, n, mode)
+    F.eval_batch(plan, probs, [c.x for c in cells], [c.y for c in cells], [2.0] * len(sizes),
+                 [i.gamma for i in insts], mode, gxs, gys, out)
+    for k, i in enumerate(insts):
+        gx, gy = (torch.empty(i.num_cells, device="cuda") for _ in range(2))
+        o4 = torch.empty(4, dtype=torch.float64, device="cuda")
+        F.eval(single, probs[k], cells[k].x, cells[k].y, 2.0, i.gamma, mode, gx, gy, o4)
+        torch.cuda.synchronize()
+        assert torch.equal(gx, gxs[k]) and torch.equal(gy, gys[k])
+        assert torch.allclose(o4, out[k], rtol=1e-12, atol=0.0)
+        assert torch.equal(single.maps()[0], plan.maps(k)[0])
+    plan.close()
+    single.close()
