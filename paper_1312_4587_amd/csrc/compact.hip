@@ -334,6 +334,7 @@ hipError_t cells_batch(const SumReq* reqs, int count, int grad_mode, hipStream_t
     sb.r[i] = reqs[i];
     max_ncb = std::max(max_ncb, reqs[i].ncb);
     max_cpb = std::max(max_cpb, reqs[i].cpb);
+    if (sum_block_pins(reqs[i]) > kSumBlockPins) max_cpb = std::max(max_cpb, 1024);
   }
   if (max_cpb > kCompactMaxCpb) return hipErrorInvalidValue;
   if (max_cpb <= 256) return cells_launch<NB, 256, 1>(sb, max_ncb, grad_mode, s);

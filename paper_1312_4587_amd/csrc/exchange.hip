@@ -520,6 +520,7 @@ SumReq sum_req(const XchDims& d, const XchIndex& X, const float2* T, const CellG
   q.m = d.m;
   q.cpb = d.cpb;
   q.ncb = d.ncb;
+  q.num_pins = d.num_pins;
   q.cb_a_ptr = X.cb_a_ptr;
   q.lc = X.lc;
   q.T = T;
@@ -562,6 +563,7 @@ hipError_t launch_xch_cellsum_batch(const SumReq* reqs, int count, int grad_mode
   for (int i = 0; i < count; ++i) {
     if (reqs[i].m > 0) max_ncb = std::max(max_ncb, reqs[i].ncb);
     max_cpb = std::max(max_cpb, reqs[i].cpb);
+    if (sum_block_pins(reqs[i]) > kSumBlockPins) max_cpb = kXchCells;
   }
   if (max_ncb == 0) return hipSuccess;
   if (count == 1) {

@@ -1,7 +1,7 @@
 """Designs that load the lanes and blocks of a kernel unevenly, against the FP64
 oracle (relative L2 <= 1e-5, the bar of every float32 result here): cells crowded
 into a few bands of the density scatter, as early in a placement, large cells among
-small ones, and many cells on small grids.  The library's sums do not depend on the order of its lists, so the
+small ones, many cells on small grids, and many pins on few cells.  The library's sums do not depend on the order of its lists, so the
 calls that share them agree bit for bit."""
 import dataclasses
 
@@ -175,3 +175,27 @@ def test_batch_with_a_design_past_the_compact_form(F, sizes, n, mode):
         assert torch.equal(single.maps()[0], plan.maps(k)[0])
     plan.close()
     single.close()
+
+
+# many pins: more than 16384 in each block of cells
+@pytest.mark.parametrize("m,n,nets,hi", [(300, 16, 14000, 8), (2000, 64, 60000, 8)])
+def test_eval_with_many_pins(F, m, n, nets, hi):
+    import torch
+    inst = gen.make_instance((118, m, nets), num_cells=m, util=0.7, n=n, num_nets=nets,
+                             hi_frac=0.0002 if hi > 8 else 0.0, hi_range=(hi, hi))
+    plan, prob, c = F.Plan(n), F.Problem.from_instance(inst), DeviceCells(inst)
+    gx, gy, wx, wy = (torch.empty(m, device="cuda") for _ in range(4))
+    out = torch.empty(4, dtype=torch.float64, device="cuda")
+    wl, hp = (torch.empty(1, dtype=torch.float64, device="cuda") for _ in range(2))
+    say("eval", m, n, inst.num_pins)
+    F.eval(plan, prob, c.x, c.y, 1.5, inst.gamma, "field", gx, gy, out)
+    F.problem_wl_grad(prob, c.x, c.y, inst.gamma, 0, wx, wy, wl, hp)
+    torch.cuda.synchronize()
+    want = oracle.evaluate(inst, lam=1.5, grad_mode="field")
+    assert rel_l2(host(gx), want["gx"]) < RTOL and rel_l2(host(gy), want["gy"]) < RTOL
+    for got, name in ((out[0], "energy"), (out[1], "wa"), (out[2], "hpwl"), (wl, "wa"),
+                      (hp, "hpwl")):
+        assert abs(float(got) - want[name]) <= RTOL * abs(want[name])
+    W, rx, ry = oracle.wa_wirelength(inst)
+    assert rel_l2(host(wx), rx) < RTOL and rel_l2(host(wy), ry) < RTOL
+    plan.close()
