@@ -695,7 +695,8 @@ int run_compact_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream_
   CompactReq cr[kMaxBatch];
   SpectralArgs sa[kMaxBatch];
   bool place = false, spread = false;
-  for (int i = 0; i < count; ++i) spread = spread || compact_spreads(rs[i].xd.m);
+  for (int i = 0; i < count; ++i)
+    spread = spread || compact_spreads(rs[i].xd.m, rs[i].xd.num_pins);
   for (int i = 0; i < count; ++i) {
     const EvalReq& r = rs[i];
     const bool scan = compact_scans(p.n, r.xd.m);
@@ -1105,7 +1106,7 @@ static int problem_wl(const fftpl_problem* prob, const float* x, const float* y,
   xr.net_wl = net_wl;
   xr.net_hp = net_hp;
   // positions straight from x, y where the compact evaluation reads them so
-  const bool direct = m > 0 && m <= kCompactDirectCells && compact_design(1, xd);
+  const bool direct = compact_design(1, xd) && !compact_spreads(m, xd.num_pins);
   hipError_t e = direct ? hipSuccess : launch_xch_spread_batch(&xr, 1, s);
   if (e == hipSuccess) e = launch_xch_wa_batch(&xr, 1, prob->wl_model, s, direct);
   if (net_wl) return dev_status(e);

@@ -360,8 +360,15 @@ bool compact_fuses_rows(const Plan& p) {
 }
 
 // On every grid: read by pin, 1M cells on n = 256 took 111 us and 140 clustered (75
-// and 93 with the spread), on n = 128 117 (83).
-bool compact_spreads(int m) { return m > kCompactDirectCells; }
+// and 93 with the spread), on n = 128 117 (83).  Many pins want it too, whose net blocks
+// are more than the chip holds at once: 262k cells, n = 512, with 2.2M pins 73 -> 67 us,
+// 3.9M 97 -> 81, 7.5M 175 -> 110 (with 1.7M 62 with it, 67 without, but the wirelength
+// gradient alone 40.4 and 39.9; with 1.2M 38 and 34).  Positions of up to kScanCells
+// cells stay in the L1s (64 KB) and are read by pin in any number (2000 cells, 7.5M
+// pins: 520 us, 580 with the spread).
+bool compact_spreads(int m, int num_pins) {
+  return m > kCompactDirectCells || (m > kScanCells && num_pins > kCompactDirectPins);
+}
 
 hipError_t launch_compact_place(const BandReq* br, const XchReq* xr, int count, hipStream_t s) {
   if (count <= 0) return hipSuccess;

@@ -91,7 +91,7 @@ int xch_dims(int m, int num_nets, int num_pins, int max_degree, XchDims* d) {
   {
     const int64_t even = ((int64_t)num_pins + kXchNetBlocks - 1) / kXchNetBlocks;
     npt = (int)std::min<int64_t>(npt, std::max<int64_t>(kXchSmallTarget, even));
-    if (m <= kCompactDirectCells)
+    if (!compact_spreads(m, num_pins))
       npt = std::min(npt, std::max(kXchSmallTarget, 4 * kXchWaThreads + 1 - max_degree));
   }
   XchDims r;

@@ -1137,6 +1137,7 @@ struct CompactBatch {
 constexpr int kCompactMaxN = 1024;      // largest grid
 constexpr int kCompactPairN = 512;      // largest grid of a row pair per band
 constexpr int kCompactDirectCells = 262144;   // most cells read by pin
+constexpr int kCompactDirectPins = 2097152;   // and, past kScanCells cells, most pins reading them
 // largest cell block: 1,048,576 cells (n = 1024: 550k cells 109 -> 97 us against the
 // general path, 1M 126 -> 115, 1M clustered, exact 153 -> 115; 1.6M 153 -> 159,
 // 2.1M 183 -> 201, where two streams use the memory better)
@@ -1149,7 +1150,7 @@ hipError_t launch_compact_mid(const Plan& p, const CompactReq* reqs, int count, 
                               bool fuse_rows, bool spread, hipStream_t s);
 bool compact_fuses_rows(const Plan& p);
 bool compact_scans(int n, int m);   // whether the band blocks read the cells themselves
-bool compact_spreads(int m);   // whether the positions are spread to the pins
+bool compact_spreads(int m, int num_pins);   // whether the positions are spread to the pins
 // per-cell gradients: density part gathered per cell, pin sums, the scalars
 hipError_t launch_compact_cells(const SumReq* reqs, int count, int grad_mode, hipStream_t s);
 hipError_t launch_band_place_batch(const BandReq* reqs, int count, hipStream_t s);

@@ -177,8 +177,11 @@ def test_batch_with_a_design_past_the_compact_form(F, sizes, n, mode):
     single.close()
 
 
-# many pins: more than 16384 in each block of cells
-@pytest.mark.parametrize("m,n,nets,hi", [(300, 16, 14000, 8), (2000, 64, 60000, 8)])
+# many pins: more than 16384 in each block of cells, and more than 2,097,152 in all,
+# which are handed their cells' positions up to 262,144 cells too
+@pytest.mark.parametrize("m,n,nets,hi", [(300, 16, 14000, 8), (2000, 64, 60000, 8),
+                                         (8193, 64, 720000, 8), (8192, 64, 720000, 8),
+                                         (100000, 256, 700000, 3000)])
 def test_eval_with_many_pins(F, m, n, nets, hi):
     import torch
     inst = gen.make_instance((118, m, nets), num_cells=m, util=0.7, n=n, num_nets=nets,
