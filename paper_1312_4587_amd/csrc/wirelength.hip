@@ -216,13 +216,21 @@ __device__ __forceinline__ void wa_big_nets(int blk, int nblk, int num_nets,
     const float wpy = sy.tp / sy.sp, wmy = sy.tm / sy.sm;
     const float rspx = 1.0f / sx.sp, rsmx = 1.0f / sx.sm;
     const float rspy = 1.0f / sy.sp, rsmy = 1.0f / sy.sm;
+    // the next pins' cells and offsets are read before the current ones are added: the
+    // wavefront is alone with its net, and every add waits for its lane exchange
+    int c = pin_cell[min(b0 + lane, b1 - 1)];
+    float dx = pin_dx[min(b0 + lane, b1 - 1)], dy = pin_dy[min(b0 + lane, b1 - 1)];
     for (int p0 = b0; p0 < b1; p0 += kWave) {
-      const int p = p0 + lane, pc = min(p, b1 - 1);
-      const int c = pin_cell[pc];
+      const int p = p0 + lane, pn = min(p + kWave, b1 - 1);
       const float2 q = io.pos(c);
-      const float X = (q.x - r.x) + pin_dx[pc], Y = (q.y - r.y) + pin_dy[pc];
+      const int cn = pin_cell[pn];
+      const float dxn = pin_dx[pn], dyn = pin_dy[pn];
+      const float X = (q.x - r.x) + dx, Y = (q.y - r.y) + dy;
       io.put_wave(p, b1, c, pin_wl_grad<LSE>(X, mx, lx, wpx, wmx, rspx, rsmx, inv_gamma),
                   pin_wl_grad<LSE>(Y, my, ly, wpy, wmy, rspy, rsmy, inv_gamma));
+      c = cn;
+      dx = dxn;
+      dy = dyn;
     }
     if (lane == src) {
       acc_wa += net_wl_value<LSE>(mx, lx, wpx, wmx, sx.sp, sx.sm, gamma) +
