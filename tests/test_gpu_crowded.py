@@ -202,3 +202,28 @@ def test_eval_with_many_pins(F, m, n, nets, hi):
     W, rx, ry = oracle.wa_wirelength(inst)
     assert rel_l2(host(wx), rx) < RTOL and rel_l2(host(wy), ry) < RTOL
     plan.close()
+
+
+# tall cells, past four bands high, in lists longer than a window of any block
+@pytest.mark.parametrize("m,n,share", [(30000, 256, 0.1), (60000, 512, 0.06),
+                                       (60000, 1024, 0.01)])
+def test_many_tall_cells(F, m, n, share):
+    import torch
+    inst = gen.make_instance((119, m, n), num_cells=m, util=0.7, n=n, num_nets=m)
+    h = inst.h.copy()
+    k = np.random.default_rng((120, m)).random(m) < share
+    h[k] = (24 * inst.bin_h) if n < 1024 else 40 * inst.bin_h
+    inst = dataclasses.replace(inst, h=h)
+    plan, prob, c = F.Plan(n), F.Problem.from_instance(inst), DeviceCells(inst)
+    gx, gy = (torch.empty(m, device="cuda") for _ in range(2))
+    out = torch.empty(4, dtype=torch.float64, device="cuda")
+    rho = torch.empty(n * n, device="cuda")
+    say("tall cells", m, n, int(k.sum()))
+    F.problem_density(prob, c.x, c.y, rho)
+    F.eval(plan, prob, c.x, c.y, 1.5, inst.gamma, "field", gx, gy, out)
+    torch.cuda.synchronize()
+    want = oracle.evaluate(inst, lam=1.5, grad_mode="field")
+    assert rel_l2(host(rho).reshape(n, n), want["rho"]) < RTOL
+    assert torch.equal(plan.maps()[0].reshape(-1), rho)
+    assert rel_l2(host(gx), want["gx"]) < RTOL and rel_l2(host(gy), want["gy"]) < RTOL
+    plan.close()
