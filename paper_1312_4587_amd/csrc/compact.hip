@@ -346,14 +346,18 @@ hipError_t cells_batch(const SumReq* reqs, int count, int grad_mode, hipStream_t
 
 }  // namespace
 
+// Past n = 512 cells of many bins each are left to the general path: a thread gathers
+// its cell's bins from a map larger than an XCD's L2, where the band gather has the
+// neighbouring cells' rows in common.  n = 1024, 2500 cells, exact 313 us against 235,
+// 4000 225 against 196 (171 against 164 with the fields), 8000 143 against 148 (115
+// against 129).
 bool compact_design(int n, const XchDims& d) {
+  if (n > kCompactPairN && (int64_t)n * n > 128 * (int64_t)d.m) return false;
   return n <= kCompactMaxN && d.m > 0 && d.cpb <= kCompactMaxCpb && d.cap <= kXchPinLds2;
 }
 
-// Past n = 512 the cells of a small design are many bins each, and each is added in the
-// bands it meets by one thread: n = 1024, 2000 cells 261 us, by way of the lists 287,
-// 4000 178 and 171, 8192 133 and 115.
-bool compact_scans(int n, int m) { return m <= (n <= kCompactPairN ? kScanCells : kScanCells / 4); }
+// Past n = 512 the row transform is on its own, and few cells are many bins each.
+bool compact_scans(int n, int m) { return n <= kCompactPairN && m <= kScanCells; }
 
 bool compact_fuses_rows(const Plan& p) {
   return p.mode == FFTPL_DCT_FFT && p.n >= 64 && p.n <= kCompactPairN;

@@ -122,8 +122,10 @@ def test_field_gather_of_large_cells(F, m, n, share, run):
     (300000, 32, "exact", "fft"), (270001, 192, "field", "gemm_f32"),
     (300000, 512, "exact", "fft"), (300000, 1024, "field", "fft"),
     (300000, 576, "exact", "gemm_f32"),
-    # cells of many bins each: read by the band blocks, and by way of the lists
-    (2048, 1024, "field", "fft"), (2049, 1024, "exact", "fft"), (2049, 576, "field", "gemm_f32")])
+    # cells of many bins each: the first designs of their grids in the compact form, and
+    # the last on the general path
+    (8192, 1024, "field", "fft"), (8191, 1024, "exact", "fft"), (2592, 576, "field", "gemm_f32"),
+    (2591, 576, "exact", "gemm_f32")])
 def test_eval_compact_forms(F, m, n, mode, dct, where):
     import torch
     inst = gen.make_instance((115, m, n), num_cells=m, util=0.8, n=n, num_nets=m, num_macros=2,
