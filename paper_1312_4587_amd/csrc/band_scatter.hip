@@ -297,16 +297,6 @@ hipError_t launch_band_gather_batch(const BandReq* reqs, int count, int grad_mod
   return band_gather_nb(bb, nb, grad_mode, s);
 }
 
-hipError_t launch_band_gather(const GridF& g, const BandLayout& L, const float* exy,
-                              const float* psi, int grad_mode, hipStream_t s) {
-  BandReq q;
-  q.g = g;
-  q.L = L;
-  q.exy = reinterpret_cast<const float2*>(exy);
-  q.psi = psi;
-  return launch_band_gather_batch(&q, 1, grad_mode, s);
-}
-
 // xy[i] = (x[i], y[i]): the wirelength pass then gathers one float2 per pin.
 __global__ void __launch_bounds__(256)
     k_interleave(int m, const float* __restrict__ x, const float* __restrict__ y,

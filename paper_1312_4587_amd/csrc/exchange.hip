@@ -578,13 +578,6 @@ hipError_t launch_xch_cellsum_batch(const SumReq* reqs, int count, int grad_mode
   return cellsum_size(sb, max_ncb, max_cpb, grad_mode, dens, s);
 }
 
-hipError_t launch_xch_cellsum(const XchDims& d, const XchIndex& X, const float2* T,
-                              const CellGradArgs& a, int grad_mode, hipStream_t s) {
-  if (d.m <= 0) return hipSuccess;
-  const SumReq q = sum_req(d, X, T, a);
-  return launch_xch_cellsum_batch(&q, 1, grad_mode, true, s);
-}
-
 XchReq xch_req(const XchDims& d, const XchIndex& X, const float* x, const float* y, float2* T,
                const int32_t* net_ptr, const int32_t* pin_cell, const float* pin_dx,
                const float* pin_dy, float gamma, double* part) {
@@ -637,13 +630,6 @@ hipError_t launch_xch_spread_batch(const XchReq* reqs, int count, hipStream_t s)
   xb.count = count;
   for (int i = 0; i < count; ++i) xb.r[i] = reqs[i];
   return spread_nb(xb, max_ncb, s);
-}
-
-hipError_t launch_xch_spread(const XchDims& d, const XchIndex& X, const float* x,
-                             const float* y, float2* T, hipStream_t s) {
-  if (d.ncb <= 0) return hipSuccess;
-  const XchReq q = xch_req(d, X, x, y, T, nullptr, nullptr, nullptr, nullptr, 1.0f, nullptr);
-  return launch_xch_spread_batch(&q, 1, s);
 }
 
 // more than 64 KiB of dynamic LDS has to be allowed explicitly, once per
@@ -710,13 +696,6 @@ hipError_t launch_xch_wa_batch(const XchReq* reqs, int count, int wl_model, hipS
   if (count > kMaxBatch) return hipErrorInvalidValue;
   return wl_model == FFTPL_WL_LSE ? wa_model<true>(reqs, count, direct, s)
                                   : wa_model<false>(reqs, count, direct, s);
-}
-
-hipError_t launch_xch_wa(const XchDims& d, const XchIndex& X, const int32_t* net_ptr,
-                         const float* pin_dx, const float* pin_dy, float gamma, int wl_model,
-                         float2* T, double* wa_part, hipStream_t s) {
-  const XchReq q = xch_req(d, X, nullptr, nullptr, T, net_ptr, nullptr, pin_dx, pin_dy, gamma, wa_part);
-  return launch_xch_wa_batch(&q, 1, wl_model, s);
 }
 
 }  // namespace fftpl

@@ -920,13 +920,10 @@ constexpr size_t kNoallocScratchBytes = (size_t)64 << 20;
 constexpr int kMaxDevicesNoalloc = 64;
 BandLayout band_layout_density(int n, int m, void* work, size_t* bytes_out);
 hipError_t noalloc_scratch(void** ptr);
+// egrad[entry] = density gradient (before lambda) of each cell at its
+// first-band entry (after launch_band_scatter_batch and the solve).
 hipError_t launch_band_gather_batch(const BandReq* reqs, int count, int grad_mode,
                                     hipStream_t s);
-
-// egrad[entry] = density gradient (before lambda) of each cell at its
-// first-band entry (after launch_band_scatter and the solve).
-hipError_t launch_band_gather(const GridF& g, const BandLayout& L, const float* exy,
-                              const float* psi, int grad_mode, hipStream_t s);
 hipError_t launch_band_scan(const GridF& g, const BandLayout& L, const float* x,
                             const float* y, const float* w, const float* h, const float* base,
                             float* rho, hipStream_t s, Plan* tp = nullptr);
@@ -1018,12 +1015,6 @@ int xch_build(const XchDims& d, const int32_t* net_ptr, const int32_t* pin_cell,
 // a net above max_degree, or more than nnb blocks.
 int pack_net_blocks(const int32_t* ptr, int E, int P, int max_degree, int cap, int nnb,
                     int32_t* first);
-hipError_t launch_xch_spread(const XchDims& d, const XchIndex& X, const float* x,
-                             const float* y, float2* T, hipStream_t s);
-hipError_t launch_xch_wa(const XchDims& d, const XchIndex& X, const int32_t* net_ptr,
-                         const float* pin_dx, const float* pin_dy, float gamma, int wl_model,
-                         float2* T, double* wa_part, hipStream_t s);
-// gwa[c] = sum over cell c's pins of T[qa[j]] (after launch_xch_wa).
 // The per-cell part of the gradient after the wirelength: g = scale * the
 // density gradient (egrad at the cell's first-band entry, or computed from the
 // maps for a cell without one) + the cell's wirelength sum.
@@ -1047,10 +1038,6 @@ struct CellGradArgs {
   // overwriting them
   int accumulate = 0;
 };
-// g (CellGradArgs) for every cell, the wirelength part being the sum over
-// the cell's pins of their gradients in T (after launch_xch_wa).
-hipError_t launch_xch_cellsum(const XchDims& d, const XchIndex& X, const float2* T,
-                              const CellGradArgs& a, int grad_mode, hipStream_t s);
 
 // One design's pin exchange: the spread (cells -> pins) and the net blocks.
 struct XchReq {
@@ -1106,7 +1093,9 @@ XchReq xch_req(const XchDims& d, const XchIndex& X, const float* x, const float*
                const float* pin_dy, float gamma, double* part);
 SumReq sum_req(const XchDims& d, const XchIndex& X, const float2* T, const CellGradArgs& a);
 // count <= kMaxBatch designs per launch; the net blocks of one launch share
-// the wirelength model.  dens = false: the cell sums without density part.
+// the wirelength model.  The cell sums write g (CellGradArgs) for every cell, its
+// wirelength part the sum of its pins' gradients in T (after launch_xch_wa_batch);
+// dens = false: that part alone.
 hipError_t launch_xch_spread_batch(const XchReq* reqs, int count, hipStream_t s);
 // direct: positions by pin_cell from x, y (no spread; cap <= kXchPinLds2)
 hipError_t launch_xch_wa_batch(const XchReq* reqs, int count, int wl_model, hipStream_t s,
