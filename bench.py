@@ -208,9 +208,15 @@ def autograd_run():
             "saved_tensors": "positions only (backward recomputes density and solve)"}
 
 
+def band_rows(inst):
+    """Rows of a band of the evaluation's scatter: a row pair in the compact form
+    (n <= 512, up to 1,048,576 cells), else as few as leave 256 bands."""
+    return 2 if inst.n <= 512 and inst.num_cells <= 1048576 else (inst.n + 255) // 256
+
+
 def band_entries(inst):
     """Number of (cell, band) entries the banded scatter lists: bookkeeping
-    for the byte counts only (float32 edges, bands of ceil(n/256) rows)."""
+    for the byte counts only (float32 edges)."""
     import numpy as np
     inv = np.float32(1.0 / inst.bin_h)
     c = (inst.y.astype(np.float32) - np.float32(inst.yl)) * inv
@@ -219,7 +225,7 @@ def band_entries(inst):
     hi = np.clip(c + half, -1, inst.n)
     i0 = np.floor(lo).astype(np.int64)
     i1 = np.ceil(hi).astype(np.int64) - 1
-    rows = (inst.n + 255) // 256
+    rows = band_rows(inst)
     ok = i1 >= i0
     return int(np.sum(np.where(ok, i1 // rows - i0 // rows + 1, 0)))
 
@@ -252,7 +258,7 @@ def kernel_bytes(inst, nent):
         # slice offsets and counts out (512 cells per block, doubled up to 4096 while
         # there are more blocks than 256)
         "k_band_place": 16 * m + 16 * nent + 4 * m
-        + 8 * (-(-inst.n // max(2, -(-inst.n // 256))) + 1) * (-(-m // place_cells(m))),
+        + 8 * (-(-inst.n // band_rows(inst)) + 1) * (-(-m // place_cells(m))),
         "k_band_accum": 16 * nent + 4 * n2 + 4 * n2,
         "k_rows_dct2": 4 * n2 + 4 * n2 + 8 * n2,        # rho, base+cap in; bT out
         "k_cols_solve": 4 * n2 + 8 * n2,                # bT in; P, Q out

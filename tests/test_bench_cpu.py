@@ -4,6 +4,7 @@ import os
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 
 import bench
@@ -64,3 +65,16 @@ def test_more_than_one_gpu_is_refused():
     assert r.returncode == 2
     assert "one GPU" in r.stderr
     assert r.stdout == ""
+
+
+# the byte counts' bands are those of the scatter: row pairs up to n = 512 in the compact
+# form (small_2k), four rows at n = 1024
+@pytest.mark.parametrize("name,rows", [("small_2k", 2), ("mid_200k", 2), ("large_2m", 4)])
+def test_band_entries_follow_the_bands(name, rows):
+    inst = gen.make_config(name)
+    inv = np.float32(1.0 / inst.bin_h)
+    c = (inst.y - np.float32(inst.yl)) * inv
+    half = np.float32(0.5) * (inst.h * inv)
+    first = np.floor(np.clip(c - half, 0, inst.n)) // rows
+    last = (np.ceil(np.clip(c + half, -1, inst.n)) - 1) // rows
+    assert bench.band_entries(inst) == int((last - first + 1)[last >= first].sum())
