@@ -684,7 +684,8 @@ SumReq cell_request(Plan& p, const EvalReq& r, const SpectralArgs& sa, int slot)
 }
 
 // The compact form of the exchange path for count requests (all compact; see
-// compact.hip): the same results in five launches on `s` alone.
+// compact.hip): the same results in four to six launches (more with the matrix-core
+// solve) on `s` alone.
 int run_compact_group(Plan& p, EvalReq* rs, int count, int grad_mode, hipStream_t s) {
   const bool grads = rs[0].gx != nullptr;
   const size_t nn = (size_t)p.n * p.n;

@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(kBandThreads) k_band_place(BandBatch<NB> bb) {
 // average.  Such a band holds a few hundred entries, less than the larger
 // block's fixed work (owner map, scan over the threads, clears), and the smaller
 // block leaves room for four per CU: a batch of eight designs at n = 256 takes
-// 12.4 us instead of 51.5 us.  One design has at most one block per CU and nothing
+// 14.5 us instead of 53.2.  One design has at most one block per CU and nothing
 // to share it with: the larger block takes as long where the cells are spread (200k
 // cells, n = 512, 7.8 us against 8.2) and less where they crowd into a few bands
 // (123k cells in a dozen bands 56 us, the whole map, against 74).

@@ -4,16 +4,18 @@
 // The general exchange path runs nine kernels on two streams.  Up to a million
 // cells each of them lasts 3 to 30 us, much of it the latency of a few dependent
 // loads, and the host enqueues the nine launches and the four cross-stream event
-// calls in 75 to 89 us, for small designs longer than the device evaluates.  Here the same steps take five launches on the caller's
-// stream alone (four for the smallest designs):
+// calls in 75 to 89 us, for small designs longer than the device evaluates.  Here the
+// same steps take four to six launches (more with the matrix-core solve) on the
+// caller's stream alone:
 //   place  the counting sort of the cells by band (k_band_place), skipped up to
-//          kScanCells cells, whose band blocks read every cell; past
-//          kCompactDirectCells with the spread beside it (k_compact_place);
+//          kScanCells cells (n <= 512), whose band blocks read every cell; past
+//          kCompactDirectCells cells or kCompactDirectPins pins with the spread
+//          beside it (k_compact_place);
 //   mid    band blocks: scatter of a row pair, and for FFT plans its row transform
 //          straight from LDS (past n = 512 of up to four rows, the row pass on its
-//          own); beside them in the same launch the net blocks, which read the
-//          positions by cell where they fit the L2 of every XCD, so that neither
-//          a spread nor a second stream is needed;
+//          own, as for n < 64); beside them in the same launch the net blocks, which
+//          up to that many cells and pins read the positions by cell, from the L2 of
+//          every XCD, so that neither a spread nor a second stream is needed;
 //   solve  the column and the inverse row pass (or the matrix-core solve);
 //   cells  per cell the density gradient gathered from the field map (it fits the
 //          L2 too, or nearly) and the sum of its pins' gradients; one more block
@@ -22,10 +24,10 @@
 // in the same order as on the general path.
 // Per evaluation, general -> compact, one after another: 2k cells (n = 64) 77.8
 // -> 20.3 us, 30k (n = 256, exact, LSE) 71.5 -> 29.1, 200k (n = 512) 78.3 -> 49.1,
-// 300k (n = 1024, clustered) 105 -> 82, 500k (n = 1024) 102 -> 94, eight of 17k to
-// 62k cells in a batch 172 -> 62.  What bounds it now is the device: at 200k cells
-// place 6, mid 17, columns 7, inverse rows 6, cells 8 us; at 500k place 11, mid 30,
-// rows 9, columns 13, inverse rows 10, cells 19.
+// 500k (n = 1024) 106 -> 88, clustered 111 -> 85, eight of 17k to 62k cells in a batch
+// 172 -> 61.  What bounds it now is the device: at 200k cells place 7, mid 21, columns
+// 7, inverse rows 6, cells 9 us; at 500k place 11, mid 26, rows 9, columns 13, inverse
+// rows 10, cells 19.
 #include <algorithm>
 
 #include "band_device.hpp"

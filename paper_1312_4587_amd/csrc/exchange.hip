@@ -80,14 +80,15 @@ int xch_dims(int m, int num_nets, int num_pins, int max_degree, XchDims* d) {
     const int64_t step = (per_cu + kXchCellStep - 1) / kXchCellStep * kXchCellStep;
     cpb = (int)std::min<int64_t>(kXchCells, std::max<int64_t>(kXchCellStep, step));
   }
-  // Netlists that do not fill two blocks of that size per CU are cut finer: a
+  // Netlists that do not fill one block of that size per CU are cut finer: a
   // block's time follows its pins (staging, the nets handed to its eight
   // wavefronts, the write-back), and small blocks share a CU three at a time.
   // Designs whose net blocks read the positions by pin are kept to blocks that
   // stage in one round of four pins per thread (past them the spread's runs want
-  // the larger blocks: 500k cells with 2.8M pins at n = 1024 130 -> 119 us).  Net blocks of 30k cells (78k pins)
-  // alone: 15.1 us in 20 blocks of 4096 pins, 8.4 us in 153 of 512; eight such
-  // designs in one launch prefer 1024 (41.9 -> 35.9 us), one design does not mind.
+  // the larger blocks: 500k cells with 2.8M pins at n = 1024 130 -> 119 us).  Net
+  // blocks of 30k cells (78k pins) alone: 15.1 us in 20 blocks of 4096 pins, 8.4 us
+  // in 153 of 512; eight such designs in one launch prefer 1024 (41.9 -> 35.9 us),
+  // one design does not mind.
   {
     const int64_t even = ((int64_t)num_pins + kXchNetBlocks - 1) / kXchNetBlocks;
     npt = (int)std::min<int64_t>(npt, std::max<int64_t>(kXchSmallTarget, even));
@@ -632,9 +633,9 @@ hipError_t launch_xch_spread_batch(const XchReq* reqs, int count, hipStream_t s)
   return spread_nb(xb, max_ncb, s);
 }
 
-// more than 64 KiB of dynamic LDS has to be allowed explicitly, once per
-// device and kernel instantiation (setting it twice from racing threads is
-// harmless)
+// The largest net blocks' LDS (up to 152 KiB) is asked for explicitly, once per device
+// and kernel instantiation (twice from racing threads is harmless).  The runtime takes
+// what fits a CU without it too, and the 76 KiB of the other net blocks rely on that.
 template <typename K>
 static hipError_t allow_big_lds(K* kernel, std::atomic<bool>* flags) {
   int dev = 0;

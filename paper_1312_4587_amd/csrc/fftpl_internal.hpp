@@ -289,7 +289,8 @@ struct MapRows {
 typedef MapRows<2, 1> NarrowRows;
 typedef MapRows<3, 2> WideRows;
 
-// The sum of ov(i, b) * e_b over a span, of one map.
+// The sum of ov(i, b) * e_b over a span, of one map.  The narrow form is written out:
+// where all cells of the wavefront fit, NarrowRows' masks cost 2.1M cells 62 us for 60.
 __device__ __forceinline__ float span_map_sum(int n, const Span& sx, const Span& sy,
                                               const float* __restrict__ e) {
   const int nx = sx.i1 - sx.i0 + 1, ny = sy.i1 - sy.i0 + 1;
