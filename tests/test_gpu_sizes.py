@@ -23,8 +23,8 @@ def F():
     return fftpl
 
 
-# cells per counting block 512 | 1024 | 2048 | 4096, the band kernels' small and
-# large forms (n <= 512 and up to 1024 cells per band), odd and tiny grids
+# cells per counting block 512 | 1024 | 2048 | 4096, bands of one row (up to n = 256)
+# to four, odd and tiny grids
 @pytest.mark.parametrize("m,n", [(1, 8), (511, 1), (513, 3), (2000, 100), (131072, 256),
                                  (131073, 512), (131073, 513), (262145, 512), (262145, 300),
                                  (524289, 512), (524289, 1024), (1048577, 1000)])
@@ -43,8 +43,8 @@ def test_density_map_block_sizes(F, m, n):
     assert rel_l2(host(rho).reshape(n, n), oracle.density_map(inst, b0)) < RTOL
 
 
-# small maps in one launch, without band lists (n <= 512, up to 16384 cells), and the
-# first designs past it; no cells; each into an old map and again
+# small maps in one launch, without band lists (up to 16384 cells with n <= 256, 8192
+# with n <= 512), and the first designs past it; no cells; each into an old map and again
 @pytest.mark.parametrize("m,n", [(0, 16), (1, 1), (2047, 31), (2049, 64), (8192, 512),
                                  (8193, 512), (8192, 513), (5000, 7), (16384, 128), (16385, 128)])
 def test_density_map_small(F, m, n):
@@ -96,8 +96,8 @@ def _check(inst, got, mode, **kw):
 
 
 # the compact evaluation's forms: cells read by every band block up to 8192,
-# then a place pass; row transforms fused from n = 64; cell blocks of up to
-# 2048 cells (524,288 cells), past them and past its grids the general path
+# then a place pass; row transforms fused from n = 64; cell blocks of 256 to 2048
+# cells (524,288 cells) and of 4096; positions read by pin up to 262,144 cells
 @pytest.mark.parametrize("m,n,mode", [
     (1, 8, "field"), (257, 16, "exact"), (1000, 32, "field"), (4097, 64, "field"),
     (8192, 128, "exact"), (8193, 128, "field"), (40000, 256, "exact"), (131073, 512, "field"),
@@ -112,9 +112,9 @@ def test_eval_sizes(F, m, n, mode):
 
 
 # compact evaluations past n = 512 (bands of three and four rows, the row pass on
-# its own), with the positions read by pin up to 262,144 cells, spread past them
-# and, past 524,288, the general path; the matrix-core solve among them; cells of
-# several bins each way
+# its own), with the positions read by pin up to 262,144 cells and spread past them;
+# the matrix-core solve among them; cells of several bins each way, and one cell on
+# n = 1024, which is left to the general path
 @pytest.mark.parametrize("m,n,mode,dct", [
     (1, 1024, "field", "fft"), (8192, 1024, "exact", "fft"), (30000, 640, "field", "gemm_f32"),
     (262144, 1024, "exact", "fft"), (262145, 1024, "field", "fft"), (262145, 576, "exact", "gemm_f32"),
@@ -263,9 +263,9 @@ def test_stateless_wirelength_sizes(F, m, degs):
     assert np.array_equal(np.isnan(host(ax)), hit)
 
 
-# the standalone gather's fast forms (a row's bins in one load: up to three bins
-# wide and two high, away from the last columns) and its loops, grids too narrow
-# for the wide loads, and one map after the other from 524288 cells at n >= 1024
+# the standalone gather's fast forms (a row's bins in one or two loads: four columns of
+# two rows, eight of three) and its loops, grids too narrow for the wide loads, and
+# one map after the other from 524288 cells at n >= 1024
 @pytest.mark.parametrize("mode", ["field", "exact"])
 @pytest.mark.parametrize("m,n", [(1, 1), (300, 3), (300, 4), (2000, 37), (524287, 1024),
                                  (524288, 1024), (524545, 1030)])
