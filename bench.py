@@ -32,23 +32,23 @@ PMC_FETCH_SCALE, PMC_WRITE_SCALE = 2.0, 1.0
 PMC_TRAFFIC = {
     # kernel: (source files, sha1, FETCH_SIZE KiB, WRITE_SIZE KiB)
     "k_band_place": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
-        "c2d96f5412b5e1b6a8df1c2529ecc0a33ab76ae3", 16523.3, 64267.3),
+        "827f5ece8c6e5f8d02d9b5e43ce63fb510af01ff", 16523.8, 64465.2),
     "k_xch_spread": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
-        "48cc1784c4b86027881a74d5f3c613f533730779", 21223.2, 96857.6),
+        "d0576a1135919b3caba07320d0b9bb359721ec16", 21220.5, 96910.5),
     "k_band_accum": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
-        "c2d96f5412b5e1b6a8df1c2529ecc0a33ab76ae3", 21681.1, 4096.0),
+        "827f5ece8c6e5f8d02d9b5e43ce63fb510af01ff", 21699.8, 4096.0),
     "k_xch_wa": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
-        "48cc1784c4b86027881a74d5f3c613f533730779", 144059.9, 101040.5),
+        "d0576a1135919b3caba07320d0b9bb359721ec16", 144004.3, 101135.6),
     "k_rows_dct2": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
-        "0134ed6e9ea28d5c84f9ccce250a6cd7290afe83", 6234.0, 4112.0),
+        "ab89b377579b539ba935666d07fdf6c001af02f7", 6234.0, 4112.0),
     "k_cols_solve": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
-        "0134ed6e9ea28d5c84f9ccce250a6cd7290afe83", 2180.0, 8192.0),
+        "ab89b377579b539ba935666d07fdf6c001af02f7", 2180.0, 8192.0),
     "k_rows_inverse": (("spectral_fft.hip", "fft_device.hpp", "fftpl_internal.hpp"),
-        "0134ed6e9ea28d5c84f9ccce250a6cd7290afe83", 6270.0, 8196.0),
+        "ab89b377579b539ba935666d07fdf6c001af02f7", 6270.0, 8196.0),
     "k_band_gather": (("band_scatter.hip", "band_device.hpp", "fftpl_internal.hpp"),
-        "c2d96f5412b5e1b6a8df1c2529ecc0a33ab76ae3", 23893.6, 18698.7),
+        "827f5ece8c6e5f8d02d9b5e43ce63fb510af01ff", 23912.6, 18839.9),
     "k_xch_cellsum": (("exchange.hip", "xch_device.hpp", "fftpl_internal.hpp"),
-        "48cc1784c4b86027881a74d5f3c613f533730779", 80532.3, 16406.3),
+        "d0576a1135919b3caba07320d0b9bb359721ec16", 81067.9, 16406.3),
 }
 
 

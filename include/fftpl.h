@@ -432,11 +432,12 @@ int fftpl_xindex_build(int32_t num_cells, int32_t num_nets, int32_t num_pins,
  * other scalars, without the gather); this needs a workspace and an index in
  * prob (FFTPL_E_INVAL otherwise).  A workspace or index that prob gives but
  * that cannot be used is an error (see fftpl_problem), not a silent change
- * of path.  With a workspace and an index, designs of up to 1,048,576 cells are
- * evaluated in a few launches on `stream` alone; past them (and with nets too large
- * for the compact net blocks) the wirelength branch (pin positions, net blocks)
- * runs on the plan's own stream concurrently with the density branch (scatter,
- * solve, per-cell density gradient) on `stream`, and is joined back before the
+ * of path.  With a workspace and an index, designs of up to 1,048,576 cells (past
+ * n = 512, of at least n * n / 128) are evaluated in a few launches on `stream` alone;
+ * the others (and designs with nets too large for the compact net blocks, and a
+ * batch's group with any of them) run the wirelength branch (pin positions, net
+ * blocks) on the plan's own stream concurrently with the density branch (scatter,
+ * solve, per-cell density gradient) on `stream`, joined back before the
  * per-cell sums.  On either path the density map, the cell sums and the scalars
  * do not depend on the order of any atomic adds,
  * so repeated evaluations give identical results. */
